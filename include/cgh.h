@@ -48,8 +48,11 @@
  *                       per axis is at most about 2^-24 (1 + 1.5 Prev |m|)
  *                       + 2^-46 Prev m^2 revolutions (Prev = P_j / 2 pi):
  *                       below 5e-7 rev for |m| <= 16384 at pitch 8 um,
- *                       633 nm and z_j >= 0.2 m.  The cosine's argument stays within a
- *                       few revolutions for every accepted input.
+ *                       633 nm and z_j >= 0.2 m.  The forward takes the cosine of the
+ *                       two axis phases' sum by the addition theorem and sums over the
+ *                       points on the fp16 matrix cores with hi + lo operands, as
+ *                       CGH_SEPARABLE_F16X3 (whose error is the smaller of the two forms);
+ *                       up to 8 points it takes one cosine per interaction.
  *      CGH_SEPARABLE    not the per-interaction cosine: the phase separates
  *                       exactly into x and y parts (each formed as in
  *                       CGH_COMPENSATED), cos(X + Y) = cXcY - sXsY turns the sum

@@ -11,6 +11,7 @@
 
 #include "../../include/cgh.h"
 #include "cgh_internal.h"
+#include "contract.h"
 
 namespace cgh {
 
@@ -415,32 +416,22 @@ int backward_separable(const Plan& p, const Workspace& w, const float* z, const 
   return hip_status(e);
 }
 
-// Half-precision separable variants: the same contractions on 16-bit planes
-// (A_j, resp. G, divided by a power of two recorded in w.hmax).
-int forward_separable_half(const Plan& p, const Workspace& w, float* hologram, hipStream_t s,
-                           bool timed) {
-  const int hm = half_mode(p.variant);
-  hipError_t e = launch_absmax(w.amp, p.npad, w.hmax, s);  // w.hmax cleared by prep
-  if (e == hipSuccess) e = launch_sep_tables_half(hm, p, w, s);
+// The forward as one contraction with its operands formed in the kernel
+// (contract_fwd.hip), with the residual in its store.
+int forward_contract(const Plan& p, const ContractFwd& c, int kernel, const float* x,
+                     const float* y, const float* z, const float* a, double pitch,
+                     double wavelength, float* hologram, const float* target, float* residual,
+                     hipStream_t s, bool timed) {
+  hipError_t e = launch_contract_fwd_tables(p, c, x, y, z, a, pitch, wavelength, s);
   if (e != hipSuccess) return CGH_EHIP;
-  const EventPair ev = profile_begin(CGH_KERNEL_FWD_SEPARABLE, s, timed);
-  if (p.sep_splits == 1) {
-    e = launch_gemm_half(hm, w.hy_hi, w.hy_lo, p.k2, w.hx_hi, w.hx_lo, p.k2, hologram, p.nx, 0,
-                         p.nyp, p.nxp, (int)p.k2, 1, p.ny, p.nx, w.hmax, nullptr, s);
-  } else {
-    const int64_t plane = (int64_t)p.nyp * p.nxp;
-    e = launch_gemm_half(hm, w.hy_hi, w.hy_lo, p.k2, w.hx_hi, w.hx_lo, p.k2, w.sep_c, p.nxp,
-                         plane, p.nyp, p.nxp, (int)p.k2, p.sep_splits, p.nyp, p.nxp, w.hmax, nullptr,
-                         s);
-  }
-  profile_end(CGH_KERNEL_FWD_SEPARABLE, ev, s);
-  if (e != hipSuccess) return CGH_EHIP;
-  if (p.sep_splits > 1)
-    e = launch_sep_sum_slices(w.sep_c, p.sep_splits, (int64_t)p.nyp * p.nxp, p.nxp, p.nx, p.ny,
-                              hologram, s);
+  const EventPair ev = profile_begin(kernel, s, timed);
+  e = launch_contract_fwd(p, c, hologram, target, residual, s);
+  profile_end(kernel, ev, s);
   return hip_status(e);
 }
 
+// Half-precision separable variants: the adjoint's contractions on 16-bit planes
+// (G divided by a power of two recorded in w.hmax).
 int backward_separable_half(const Plan& p, const Workspace& w, const float* z, const float* a,
                             double pitch, double wavelength, const float* g, float* gx, float* gy,
                             float* gz, float* ga, hipStream_t s) {
@@ -594,6 +585,14 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
   const int32_t variant = p.variant;
   const int64_t n = p.n;
   const Workspace w = carve(p, workspace);
+  if (variant == CGH_COMPENSATED || half_mode(variant) >= 0) {
+    ContractFwd c;
+    if (plan_contract_fwd(p, w, c))
+      return forward_contract(p, c,
+                              variant == CGH_COMPENSATED ? CGH_KERNEL_FWD_COMPENSATED
+                                                         : CGH_KERNEL_FWD_SEPARABLE,
+                              x, y, z, a, pitch, wavelength, hologram, target, residual, s, timed);
+  }
   // The compensated forward forms the records with its row-phase table.
   hipError_t e = variant == CGH_COMPENSATED
                      ? launch_prep_ytab(x, y, z, a, pitch, wavelength, p, w, s)
@@ -605,8 +604,6 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
   };
   if (variant == CGH_SEPARABLE)
     return separate_residual(forward_separable(p, w, hologram, s, timed));
-  if (half_mode(variant) >= 0)
-    return separate_residual(forward_separable_half(p, w, hologram, s, timed));
   if (variant == CGH_COMPENSATED) {
     const EventPair ev = profile_begin(CGH_KERNEL_FWD_COMPENSATED, s, timed);
     e = launch_fwd_comp(p, w, hologram, s, target, residual);

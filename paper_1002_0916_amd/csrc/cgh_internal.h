@@ -325,8 +325,6 @@ __device__ __forceinline__ float pow2_scale(unsigned max_bits) {
 // launch_absmax raises *out (cleared beforehand, by the prep kernel) to the
 // float bits of max |v|.
 hipError_t launch_absmax(const float* v, int64_t count, unsigned* out, hipStream_t s);
-// Forward operands: X [nxp][k2] and Y [nyp][k2] (with A_j / 2^e) planes.
-hipError_t launch_sep_tables_half(int mode, const Plan& p, const Workspace& w, hipStream_t s);
 // Adjoint operands: Xt [k2][nxp], Yt [k2][nyp], and G / 2^e as G [nyp][nxp]
 // and Gt [nxp][nyp] planes, in one launch.
 hipError_t launch_sep_adj_operands_half(int mode, const Plan& p, const Workspace& w,

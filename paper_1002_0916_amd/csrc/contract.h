@@ -1,0 +1,162 @@
+// The hologram sum as a contraction on the 16-bit matrix cores,
+// with the operands formed inside the kernel (contract_fwd.hip).
+//
+// The phase of Eq. (1) (Section 1) separates by axis, theta = X_j(x) + Y_j(y)
+// revolutions, each part the compensated axis_phase, and by the addition
+// theorem cos(X + Y) = cX cY - sX sY, so the sum over points is a contraction
+// of per-axis cosines and sines.  A value v enters the matrix cores in one of
+// these formats (FP32 accumulation in all):
+//
+//   kHalfF16x3  v = hi + lo, hi = fp16(v), lo = fp16(v - hi), three products
+//               hi*hi + hi*lo + lo*hi: the two planes hold 22 to 24 bits of v
+//               and what is dropped, lo*lo, is below 2^-22 of the product.
+//   kHalfF16, kHalfBF16   v rounded once to 16 bits, one product.
+//
+// Cosines and sines lie in [-1, 1].  The amplitudes A_j are multiplied by a power
+// of two first (exact), which puts the largest below 2^15 (f16x3) or 1 (the
+// single planes): with fp16's smallest step at 2^-24, a value down to 2^-16 of
+// the largest keeps both planes at full width, and the absolute error of a
+// smaller one is below 2^-39 of the largest.
+#pragma once
+
+#include <algorithm>
+
+#include "cgh_internal.h"
+#include "phase.h"
+
+namespace cgh {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// One lane's share of a 32 x 16 operand block of v_mfma_f32_32x32x16: row (or
+// column) lane % 32, k = (lane / 32) * 8 .. + 7, two 16-bit values a dword.
+struct Frag {
+  uint4 hi, lo;
+};
+
+template <int MODE>
+__device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
+  if constexpr (MODE == kHalfBF16)
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
+                                                  __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
+}
+
+// Two values rounded to the 16-bit format (to nearest even), v0 in the low half.
+template <int MODE>
+__device__ __forceinline__ uint32_t pack16(float v0, float v1) {
+  if constexpr (MODE == kHalfBF16) {
+    const bf16x2 h = {(__bf16)v0, (__bf16)v1};
+    return __builtin_bit_cast(uint32_t, h);
+  } else {
+    const halfx2 h = {(_Float16)v0, (_Float16)v1};
+    return __builtin_bit_cast(uint32_t, h);
+  }
+}
+
+// hi and lo planes of two values: v_cvt_pk_f16_f32, two v_fma_mix_f32 for the
+// differences v - hi (exact) and another pack.  The two empty asm statements
+// keep the compiler from converting each value a second time for the
+// difference and from turning the fma into a conversion and a subtraction.
+__device__ __forceinline__ void split16(float v0, float v1, uint32_t& hi, uint32_t& lo) {
+  uint32_t h = pack16<kHalfF16x3>(v0, v1);
+  float neg = -1.0f;
+  asm("" : "+v"(h));
+  asm("" : "+v"(neg));
+  const halfx2 hh = __builtin_bit_cast(halfx2, h);
+  hi = h;
+  lo = pack16<kHalfF16x3>(__builtin_fmaf((float)hh[0], neg, v0),
+                          __builtin_fmaf((float)hh[1], neg, v1));
+}
+
+// Eight values as one lane's share of a block (k in order).
+template <int MODE>
+__device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
+  Frag f;
+  if constexpr (MODE == kHalfF16x3) {
+    split16(v[0], v[1], f.hi.x, f.lo.x);
+    split16(v[2], v[3], f.hi.y, f.lo.y);
+    split16(v[4], v[5], f.hi.z, f.lo.z);
+    split16(v[6], v[7], f.hi.w, f.lo.w);
+  } else {
+    f.hi = make_uint4(pack16<MODE>(v[0], v[1]), pack16<MODE>(v[2], v[3]),
+                      pack16<MODE>(v[4], v[5]), pack16<MODE>(v[6], v[7]));
+    f.lo = make_uint4(0, 0, 0, 0);
+  }
+  return f;
+}
+
+// The power of two that an operand with the largest magnitude m (float bits of
+// a finite m) is multiplied by, and its inverse.  frexp's exponent e (m < 2^e)
+// is clamped so that both stay normal floats.
+template <int MODE>
+__device__ __forceinline__ void operand_scale(unsigned max_bits, float& mul, float& undo) {
+  int e = 0;
+  const float m = __uint_as_float(max_bits);
+  if (m > 0.0f) (void)frexpf(m, &e);
+  e -= MODE == kHalfF16x3 ? 15 : 0;
+  e = max(-126, min(126, e));
+  undo = ldexpf(1.0f, e);
+  mul = ldexpf(1.0f, -e);
+}
+__device__ __forceinline__ bool finite_bits(unsigned max_bits) { return max_bits < 0x7f800000u; }
+
+// Largest of v over a workgroup of T threads, on every thread; `lds` holds one
+// word per wave.  (Non-negative floats order as their bits.)
+template <int T>
+__device__ __forceinline__ unsigned group_max(unsigned v, unsigned* lds) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, off, 64));
+  if constexpr (T > kWave) {
+    if ((threadIdx.x & (kWave - 1)) == 0) lds[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = lds[0];
+#pragma unroll
+    for (int w = 1; w < T / kWave; ++w) v = max(v, lds[w]);
+    __syncthreads();
+  }
+  return v;
+}
+
+// ----------------------------------------------------------------- forward --
+// Tables of the forward, a quad of points at a time so that a lane's four
+// points of one coordinate are one 16-byte load and 32 lanes of consecutive
+// coordinates read 512 consecutive bytes:
+//   f16x3        float [npad / 4][rows][4]   the axis phase
+//   f16, bf16    uint32 [npad / 4][rows][4]  (cos, sin) as two 16-bit values
+// y rows (with A_j and the scale in the 16-bit values), then x columns.
+struct FwdOperands {
+  const void* yq;     // [npad / 4][rows_y][4]
+  const void* xq;     // [npad / 4][cols_x][4], or null: from the records
+  const float4* rec;  // [npad / 4][5] x records {c, ph, pl, b, d} by quad, when xq is null
+  const float* amp;   // [npad]
+  int rows_y, cols_x;
+};
+
+struct ContractFwd {
+  int mode;           // kHalfF16x3, kHalfF16, kHalfBF16
+  int shape;          // index of the kernel's tile shape
+  int rows_y, cols_x;
+  bool xtab;
+  void* yq;
+  void* xq;
+  float4* rec;
+  float* amp;
+  unsigned* amax;     // largest |A| as float bits, one word (single planes)
+  int slices;         // the points are cut into this many slices,
+  float* planes;      //   with a plane [ny][nx] each when there are several
+};
+bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c);
+hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const float* x,
+                                      const float* y, const float* z, const float* a,
+                                      double pitch, double wavelength, hipStream_t s);
+hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
+                               const float* target, float* residual, hipStream_t s);
+
+}  // namespace cgh

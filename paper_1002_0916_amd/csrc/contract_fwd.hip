@@ -1,0 +1,625 @@
+// Forward hologram as one contraction on the 16-bit matrix cores (contract.h):
+//
+//   I[y][x] = sum_j A_j (cY_j(y) cX_j(x) - sY_j(y) sX_j(x)) = sum_k P[y][k] Q[x][k],
+//   P[y][2j] = A_j cY_j(y), P[y][2j + 1] = -A_j sY_j(y), Q[x][2j] = cX_j(x),
+//   Q[x][2j + 1] = sX_j(x)                                      (Eq. (1), Section 1)
+//
+// A wave computes MI x NJ blocks of 32 x 32 pixels with
+// v_mfma_f32_32x32x16 (lane l: row or column l % 32, k = (l / 32) * 8 .. + 7,
+// i.e. four points; accumulator register r: row (r / 4) * 8 + (l / 32) * 4 +
+// r % 4, column l % 32).  The operands never exist in memory: a lane reads the
+// phases of its four points at its coordinate (16 bytes), takes their cosines
+// and sines and splits them into fp16 planes in registers, already in the
+// matrix cores' layout.  The table is therefore 4 bytes per point and
+// coordinate where both planes of both values would be 8.
+//
+// A workgroup is KS groups of WM waves.  The WM waves of a group are stacked in
+// y and share their columns: each forms a share of the column operand and
+// leaves it in LDS (double buffered), in the layout in which all of them read
+// it back (a wave reads or writes 1 KB of consecutive bytes: no bank
+// conflicts).  The row operand stays in the registers of the wave that forms
+// it.  The KS groups (two or more) split the points of the same pixels; their
+// sums are added in group order through LDS at the end (a fixed order: bitwise
+// reproducible), which also keeps every chain of additions short.
+#include "contract.h"
+#include "records.h"
+
+namespace cgh {
+
+namespace {
+
+constexpr int kBand = 8;       // tile rows per band of the tile order
+constexpr int kTabRows = 256;  // coordinates per table workgroup slice
+
+// (cos, sin) operand block share from four phases, times a factor each for the
+// cosine and the sine.
+template <int MODE>
+__device__ __forceinline__ Frag frag_of_phases(float4 ph) {
+  const float v[8] = {cos_rev(ph.x), sin_rev(ph.x), cos_rev(ph.y), sin_rev(ph.y),
+                      cos_rev(ph.z), sin_rev(ph.z), cos_rev(ph.w), sin_rev(ph.w)};
+  return make_frag<MODE>(v);
+}
+template <int MODE>
+__device__ __forceinline__ Frag frag_of_phases(float4 ph, float4 a) {
+  const float v[8] = {a.x * cos_rev(ph.x), -(a.x * sin_rev(ph.x)), a.y * cos_rev(ph.y),
+                      -(a.y * sin_rev(ph.y)), a.z * cos_rev(ph.z), -(a.z * sin_rev(ph.z)),
+                      a.w * cos_rev(ph.w), -(a.w * sin_rev(ph.w))};
+  return make_frag<MODE>(v);
+}
+
+// One quad's phases at coordinate h from its records {c, ph, pl, b, d}.
+__device__ __forceinline__ float4 quad_phases(const float4* __restrict__ rec, int64_t q, float h) {
+  const float4 c = rec[q * 5], ph = rec[q * 5 + 1], pl = rec[q * 5 + 2], b = rec[q * 5 + 3],
+               d = rec[q * 5 + 4];
+  return make_float4(axis_phase(h, c.x, ph.x, pl.x, b.x, d.x),
+                     axis_phase(h, c.y, ph.y, pl.y, b.y, d.y),
+                     axis_phase(h, c.z, ph.z, pl.z, b.z, d.z),
+                     axis_phase(h, c.w, ph.w, pl.w, b.w, d.w));
+}
+
+template <int MODE, int MI, int NJ, int WM, int KS, bool XTAB, bool RES>
+__global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
+    FwdOperands o, int npad, int nx, int ny, unsigned tiles_x, unsigned tiles, int per_slice,
+    const unsigned* __restrict__ amax, float* __restrict__ out, const float* __restrict__ tgt,
+    float* __restrict__ res) {
+  constexpr bool kSplit = MODE == kHalfF16x3;
+  constexpr int kThreads = kWave * WM * KS;
+  constexpr int kPlanes = kSplit ? 2 : 1;
+  constexpr int kS = 2;                          // steps (of 8 points) per LDS stage
+  constexpr int kShare = WM > 1 ? kS * NJ / WM : 1;  // operand blocks a wave forms per stage
+  constexpr int kAhead = 2;                      // steps whose phases are loaded ahead
+  constexpr int kPx = WM > 1 ? kShare : NJ;
+  static_assert(WM == 1 || kS * NJ % WM == 0, "the waves of a group share a stage evenly");
+  constexpr int kStage = WM > 1 ? 2 * kS * NJ * kPlanes * kWave : 0;  // uint4 per group
+  constexpr int kRegs = MI * NJ * 16;               // accumulators per lane
+  constexpr int kRounds = (KS * WM * kRegs + 255) / 256;  // of the final sums, 64 KB each
+  constexpr int kChunk = kRegs / kRounds;           // registers per wave and round
+  constexpr int kOwn = kChunk / KS;                 // of these, summed by one group
+  constexpr int kVec = kOwn < 4 ? kOwn : 4;
+  static_assert(kOwn >= 1 && kOwn * KS * kRounds == kRegs, "the groups share every round evenly");
+  constexpr int kSum = KS * WM * kChunk * kWave / 4;
+  constexpr int kLds = KS * kStage > kSum ? KS * kStage : kSum;
+  __shared__ uint4 lds[kLds];
+  __shared__ unsigned red[WM * KS];
+
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int grp = wave / WM, w = wave % WM;
+  const int half = lane >> 5, l32 = lane & 31;
+  // Slices of the points in order, each with all tiles; slice s writes (or is)
+  // plane s of the output.
+  const unsigned id = xcd_tile(blockIdx.x, gridDim.x);
+  const unsigned slice = id / tiles, tile = id - slice * tiles;
+  out += (int64_t)slice * nx * ny;
+  // Bands of kBand tile rows, each walked column by column: the tiles that run
+  // together on an XCD are then about square and share both tables' parts.
+  const unsigned band = tile / (kBand * tiles_x), in_band = tile - band * kBand * tiles_x;
+  const unsigned bh = min((unsigned)kBand, tiles / tiles_x - band * kBand);
+  const int tx = (int)(in_band / bh), ty = (int)(band * kBand + in_band % bh);
+  const int y0 = ty * (WM * MI * 32) + w * (MI * 32), x0 = tx * (NJ * 32);
+
+  // Step t: points 8 t .. 8 t + 7, quads 2 t + half.  Rows and columns beyond
+  // the tables repeat the last one (their pixels are not stored).
+  const int first = (int)slice * per_slice;  // points, multiples of 64
+  const int steps = (min(first + per_slice, npad) - first) / 8 / KS;
+  const int t0 = first / 8 + grp * steps;
+  const int last = t0 + steps - 1;
+  const char* __restrict__ yt = static_cast<const char*>(o.yq);
+  const char* __restrict__ xt = static_cast<const char*>(o.xq);
+  const char* __restrict__ at = reinterpret_cast<const char*>(o.amp);
+  // This lane's byte offsets within a step (uniform base + 32-bit offset).
+  unsigned yoff[MI], xoff[NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+    yoff[i] = (unsigned)(half * o.rows_y + min(y0 + i * 32 + l32, o.rows_y - 1)) * 16u;
+#pragma unroll
+  for (int n = 0; n < NJ; ++n)
+    xoff[n] = (unsigned)(half * o.cols_x + min(x0 + n * 32 + l32, o.cols_x - 1)) * 16u;
+  struct RowPhases {
+    uint4 p[MI];
+    float4 a;
+  };
+  auto load_y = [&](int t, RowPhases& r) {
+    const char* base = yt + (int64_t)t * o.rows_y * 32;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) r.p[i] = *reinterpret_cast<const uint4*>(base + yoff[i]);
+    if (kSplit) r.a = *reinterpret_cast<const float4*>(at + (int64_t)t * 32 + (unsigned)half * 16u);
+  };
+  auto load_x = [&](int t, int n) -> uint4 {
+    if constexpr (XTAB)
+      return *reinterpret_cast<const uint4*>(xt + (int64_t)t * o.cols_x * 32 + xoff[n]);
+    else
+      return __builtin_bit_cast(
+          uint4, quad_phases(o.rec, (int64_t)t * 2 + half, (float)(x0 + n * 32 + l32)));
+  };
+  auto form_x = [&](uint4 p) -> Frag {
+    if constexpr (kSplit) return frag_of_phases<MODE>(__builtin_bit_cast(float4, p));
+    return Frag{p, make_uint4(0, 0, 0, 0)};
+  };
+
+  // The first kAhead steps' loads are in flight while the scale is found.
+  RowPhases py[kAhead];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) load_y(min(t0 + u, last), py[u]);
+  uint4 px[kPx];
+  uint4* buf = lds + grp * kStage;
+  constexpr int kBuf = kS * NJ * kPlanes * kWave;
+  // WM > 1: this wave's share of stage s, blocks b = w, w + WM, ... of the
+  // stage's kS * NJ (step b / NJ, column block b % NJ).
+  auto load_block = [&](int s, int k) {
+    const int b = k * WM + w;
+    px[k] = load_x(min(t0 + s * kS + b / NJ, last), b % NJ);
+  };
+  auto store_block = [&](int s, int k) {
+    const Frag f = form_x(px[k]);
+    uint4* d = buf + (s & 1) * kBuf + (k * WM + w) * kPlanes * kWave + lane;
+    d[0] = f.hi;
+    if (kSplit) d[kWave] = f.lo;
+  };
+  auto load_stage = [&](int s) {
+#pragma unroll
+    for (int k = 0; k < kShare; ++k) load_block(s, k);
+  };
+  auto store_stage = [&](int s) {
+#pragma unroll
+    for (int k = 0; k < kShare; ++k) store_block(s, k);
+  };
+  if constexpr (WM == 1) {
+#pragma unroll
+    for (int n = 0; n < NJ; ++n) px[n] = load_x(t0, n);
+  } else {
+    load_stage(0);
+  }
+
+  // Scale of the amplitudes from their largest magnitude.
+  unsigned m = 0;
+  if (kSplit) {
+    for (int j = threadIdx.x * 4; j < npad; j += kThreads * 4) {
+      const float4 v = *reinterpret_cast<const float4*>(o.amp + j);
+      m = max(m, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
+                     max(__float_as_uint(fabsf(v.z)), __float_as_uint(fabsf(v.w)))));
+    }
+    m = group_max<kThreads>(m, red);
+  } else {
+    m = *amax;
+  }
+  float mul, undo;
+  operand_scale<MODE>(m, mul, undo);
+  auto form_y = [&](const RowPhases& r, float mul, Frag (&A)[MI]) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      if constexpr (kSplit)
+        A[i] = frag_of_phases<MODE>(
+            __builtin_bit_cast(float4, r.p[i]),
+            make_float4(r.a.x * mul, r.a.y * mul, r.a.z * mul, r.a.w * mul));
+      else
+        A[i] = Frag{mul != 0.0f ? r.p[i] : make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
+    }
+  };
+
+  floatx16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int n = 0; n < NJ; ++n)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.0f;
+  auto products = [&](const Frag (&A)[MI], const Frag& B, int n) {
+#pragma unroll
+    for (int k = 0; k < (kSplit ? 3 : 1); ++k)
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+        acc[i][n] = mfma16<MODE>(k == 2 ? A[i].lo : A[i].hi, k == 1 ? B.lo : B.hi, acc[i][n]);
+  };
+
+  // The matrix cores run beside the vector ALU only if a wave keeps issuing
+  // vector instructions between its MFMAs, so the operands of the next step are
+  // formed among the products of the current one, in the proportion given here.
+  // (On gfx950 the same instructions as two blocks take 1.5 times as long.)
+  constexpr int kForm = MI + (WM == 1 ? NJ : kShare / kS);  // quads formed per step
+  constexpr int kMfma = MI * NJ * (kSplit ? 3 : 1);         // MFMAs per step
+  auto interleave = [&]() {
+    if constexpr (kSplit) {
+      constexpr int kTrans = (kForm * 8 + kMfma - 1) / kMfma;
+      constexpr int kValu = (kForm * 16 + kMfma - 1) / kMfma;
+#pragma unroll
+      for (int k = 0; k < kMfma; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x400, kTrans, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+      }
+    }
+  };
+  Frag A[2][MI];
+  if constexpr (WM == 1) {
+    // Column block n + 1 (or the next step's first) is formed among block n's
+    // products, and the next step's rows among all of them.  An odd last step
+    // is taken with zero amplitudes.
+    Frag B = form_x(px[0]);
+    px[0] = load_x(min(t0 + 1, last), 0);
+    form_y(py[0], mul, A[0]);
+    load_y(min(t0 + 2, last), py[0]);
+    for (int t = t0; t <= last; t += 2) {
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NJ; ++n) {
+          const int k = (n + 1) % NJ;
+          const Frag next = form_x(px[k]);
+          px[k] = load_x(min(t + u + (k == 0 ? 2 : 1), last), k);
+          products(A[u], B, n);
+          B = next;
+        }
+        const int v = 1 - u;
+        form_y(py[v], t + u + 1 <= last ? mul : 0.0f, A[v]);
+        load_y(min(t + u + 3, last), py[v]);
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  } else {
+    static_assert(kS == 2 && kAhead == 2, "two steps a stage");
+    const int stages = steps / kS;
+    store_stage(0);
+    load_stage(1);
+    form_y(py[0], mul, A[0]);
+    load_y(min(t0 + 2, last), py[0]);
+    __syncthreads();
+    for (int s = 0; s < stages; ++s) {
+      const uint4* src = buf + (s & 1) * kBuf + lane;
+      auto read_x = [&](int b) -> Frag {
+        const uint4* q = src + b * kPlanes * kWave;
+        Frag f;
+        f.hi = q[0];
+        f.lo = kSplit ? q[kWave] : f.hi;
+        return f;
+      };
+      Frag B = read_x(0);
+#pragma unroll
+      for (int u = 0; u < kS; ++u) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < NJ; ++n) {
+          const int b = u * NJ + n + 1;
+          const Frag next = b < kS * NJ ? read_x(b) : B;
+          products(A[u], B, n);
+          B = next;
+        }
+        // the next step's rows, and this wave's share of the next stage's columns
+        const int v = 1 - u;
+        form_y(py[v], mul, A[v]);
+        load_y(min(t0 + s * kS + u + 3, last), py[v]);
+#pragma unroll
+        for (int k = u * kShare / kS; k < (u + 1) * kShare / kS; ++k) {
+          store_block(s + 1, k);
+          load_block(s + 2, k);
+        }
+        interleave();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __syncthreads();
+    }
+  }
+
+  // An infinite or NaN amplitude has no scale: such a call takes the sum term
+  // by term, cos(X + Y) A, so that its infinities and NaNs are the direct sum's.
+  if (kSplit && !finite_bits(m)) {
+    for (int e = grp * kWave + lane; e < MI * 32 * NJ * 32; e += KS * kWave) {
+      const int row = y0 + e / (NJ * 32), col = x0 + e % (NJ * 32);
+      if (row >= ny || col >= nx) continue;
+      float v = 0.0f;
+      for (int64_t q = first / 4; q < min(first + per_slice, npad) / 4; ++q) {
+        const float4 Y = static_cast<const float4*>(o.yq)[q * o.rows_y + row];
+        const float4 X = XTAB ? static_cast<const float4*>(o.xq)[q * o.cols_x + col]
+                              : quad_phases(o.rec, q, (float)col);
+        const float4 a = *reinterpret_cast<const float4*>(o.amp + q * 4);
+        v = __builtin_fmaf(a.x, cos_rev(X.x + Y.x), v);
+        v = __builtin_fmaf(a.y, cos_rev(X.y + Y.y), v);
+        v = __builtin_fmaf(a.z, cos_rev(X.z + Y.z), v);
+        v = __builtin_fmaf(a.w, cos_rev(X.w + Y.w), v);
+      }
+      const int64_t idx = (int64_t)row * nx + col;
+      out[idx] = v;
+      if constexpr (RES) res[idx] = v - tgt[idx];
+    }
+    return;
+  }
+
+  // The groups' sums, kChunk registers of every wave a round through LDS: each
+  // wave of a group then adds the KS copies of its kOwn registers in group order
+  // and stores those pixels, so the sums, the target's loads and the stores are
+  // spread over all waves.  (One wave storing alone took 30 us longer with a
+  // target at 1920x1024.)
+  float* sums = reinterpret_cast<float*>(lds);
+#pragma unroll
+  for (int h = 0; h < kRounds; ++h) {
+    const int mine = h * kChunk + grp * kOwn;  // first owned register, of block mine / 16
+    if (WM > 1 || h > 0) __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kChunk; c += kVec) {
+      float* d = sums + (((grp * WM + w) * kChunk + c) * kWave + lane * kVec);
+#pragma unroll
+      for (int e = 0; e < kVec; ++e) {
+        const int q = h * kChunk + c + e;
+        d[e] = acc[q / 16 / NJ][q / 16 % NJ][q % 16];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kOwn; c += kVec) {
+      const int q = mine + c, r = q % 16;
+      const int row = y0 + q / 16 / NJ * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+      const int col = x0 + q / 16 % NJ * 32 + l32;
+      const int64_t idx = (int64_t)row * nx + col;
+      float t[kVec], v[kVec];
+#pragma unroll
+      for (int e = 0; e < kVec; ++e) {
+        t[e] = RES && row + e < ny && col < nx ? tgt[idx + (int64_t)e * nx] : 0.0f;
+        v[e] = 0.0f;
+      }
+#pragma unroll
+      for (int k = 0; k < KS; ++k) {
+        const float* d = sums + (((k * WM + w) * kChunk + grp * kOwn + c) * kWave + lane * kVec);
+#pragma unroll
+        for (int e = 0; e < kVec; ++e) v[e] = k == 0 ? d[e] : v[e] + d[e];
+      }
+#pragma unroll
+      for (int e = 0; e < kVec; ++e)
+        if (row + e < ny && col < nx) {
+          v[e] *= undo;
+          out[idx + (int64_t)e * nx] = v[e];
+          if constexpr (RES) res[idx + (int64_t)e * nx] = v[e] - t[e];
+        }
+    }
+  }
+}
+
+// Both tables, the amplitudes and (without an x table) the x records in one
+// launch.  A workgroup is 16 points (blockIdx.x) and kTabRows coordinates
+// (blockIdx.y: y slices, then x slices).  Lane l of wave w takes point
+// 4 w + l % 4 of the 16 and coordinates l / 4, l / 4 + 16, ..., so a store is
+// 256 consecutive bytes; each thread forms its point's record once.
+template <int MODE>
+__global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
+    const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
+    const float* __restrict__ a, int64_t n, double pitch, double wavelength, int yslices,
+    int rows_y, int cols_x, uint32_t* __restrict__ yq, uint32_t* __restrict__ xq,
+    float* __restrict__ rec, float* __restrict__ amp, unsigned* __restrict__ amax) {
+  __shared__ unsigned red[4];
+  const int lane = threadIdx.x & 63;
+  const int64_t q = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int e = lane & 3;
+  const int64_t j = q * 4 + e;
+  const bool is_y = (int)blockIdx.y < yslices;
+  const int slice = is_y ? (int)blockIdx.y : (int)blockIdx.y - yslices;
+  float mul = 1.0f;
+  if (MODE != kHalfF16x3 && is_y) {
+    // every y workgroup takes the largest |A| itself: n words from the cache
+    unsigned m = 0;
+    for (int64_t k = threadIdx.x; k < n; k += 256) m = max(m, __float_as_uint(fabsf(a[k])));
+    m = group_max<256>(m, red);
+    float undo;
+    operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *amax = finite_bits(m) ? m : 0u;
+  }
+  const PointRecord r = point_record(x, y, z, a, j, n, pitch, wavelength);
+  if (blockIdx.y == 0 && lane < 4) {
+    amp[j] = r.a;
+    if (rec) {
+      float* d = rec + q * 20 + e;
+      d[0] = r.xc;
+      d[4] = r.ph;
+      d[8] = r.pl;
+      d[12] = r.xb;
+      d[16] = r.xd;
+    }
+  }
+  const float A = r.a * mul;
+  const int rows = is_y ? rows_y : cols_x;
+  const float c = is_y ? r.yc : r.xc, b = is_y ? r.yb : r.xb, d = is_y ? r.yd : r.xd;
+  uint32_t* dst = (is_y ? yq : xq) + (q * rows) * 4 + e;
+#pragma unroll 4
+  for (int i = 0; i < kTabRows / 16; ++i) {
+    const int h = slice * kTabRows + (lane >> 2) + 16 * i;
+    if (h >= rows) break;
+    const float ph = axis_phase((float)h, c, r.ph, r.pl, b, d);
+    if constexpr (MODE == kHalfF16x3) {
+      dst[h * 4] = __float_as_uint(ph);
+    } else {
+      const float cs = cos_rev(ph), sn = sin_rev(ph);
+      dst[h * 4] = is_y ? pack16<MODE>(A * cs, -(A * sn)) : pack16<MODE>(cs, sn);
+    }
+  }
+}
+
+template <int MODE, int MI, int NJ, int WM, int KS>
+hipError_t launch_shape(const Plan& p, const ContractFwd& c, float* out, const float* tgt,
+                        float* res, hipStream_t s) {
+  const int64_t tiles_x = (p.nx + NJ * 32 - 1) / (NJ * 32);
+  const int64_t tiles_y = (p.ny + WM * MI * 32 - 1) / (WM * MI * 32);
+  const int64_t tiles = tiles_x * tiles_y;
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  if (tiles * c.slices > 0x7fffffff) return hipErrorInvalidValue;
+  const FwdOperands o{c.yq, c.xtab ? c.xq : nullptr, c.rec, c.amp, c.rows_y, c.cols_x};
+  const int per_slice = (int)((p.npad / 64 + c.slices - 1) / c.slices * 64);
+  const bool one = c.slices == 1;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * c.slices)), dim3(kWave * WM * KS), 0, s, o,
+                       (int)p.npad, p.nx, p.ny, (unsigned)tiles_x, (unsigned)tiles, per_slice,
+                       c.amax, one ? out : c.planes, tgt, res);
+  };
+  if (c.xtab) {
+    if (res && one)
+      go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, true, true>);
+    else
+      go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, true, false>);
+  } else if constexpr (MODE == kHalfF16x3) {
+    if (res && one)
+      go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, false, true>);
+    else
+      go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, false, false>);
+  } else {
+    return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+// I = the sum of the slices' planes in order, and I - T with a target.
+__global__ __launch_bounds__(256) void contract_fwd_sum_kernel(const float* __restrict__ planes,
+                                                               int slices, int64_t count,
+                                                               float* __restrict__ out,
+                                                               const float* __restrict__ tgt,
+                                                               float* __restrict__ res) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= count) return;
+  float v = planes[i];
+#pragma unroll 8
+  for (int k = 1; k < slices; ++k) v += planes[k * count + i];
+  out[i] = v;
+  if (res) res[i] = v - tgt[i];
+}
+
+// Tile shapes: kernel <MI, NJ, WM, KS>, pixels per workgroup, and the two terms
+// of its time, measured on this GPU: microseconds per launch beside the loop,
+// and per round of 256 workgroups (one a CU) and 1000 points, for the f16x3
+// format and for the single planes.  Larger tiles form fewer operands per
+// product; smaller ones and more point groups put a small hologram on more
+// CUs.  (At 3840x2160, N = 16384 the five take 1.47, 1.77, 1.99, 2.46 and
+// 3.13 ms, at 1920x1080, N = 8192 0.33, 0.23, 0.27, 0.32 and 0.40 ms, at
+// 1024x1024, N = 4096 164, 96, 75, 81 and 100 us, and at 333x197, N = 700 35,
+// 28, 20, 12 and 9.5 us.)
+struct Shape {
+  int rows, cols;
+  float fixed, split, single;
+};
+constexpr Shape kShapes[] = {
+    {128, 128, 9.5f, 44.8f, 17.0f},  // <2, 4, 2, 2>
+    {64, 128, 12.0f, 24.5f, 10.0f},  // <2, 4, 1, 8>
+    {64, 64, 7.5f, 14.7f, 6.2f},     // <2, 2, 1, 4>
+    {32, 64, 7.0f, 9.6f, 4.5f},      // <1, 2, 1, 8>
+    {32, 32, 5.0f, 6.0f, 3.6f},      // <1, 1, 1, 8>
+};
+
+// Shape and slices for plan p.  Fewer than 256 tiles leave CUs idle: where the
+// plan has room for that many planes, the points are cut into as many slices as
+// the tiles leave CUs, of at least kMinSlice points each, which costs one more
+// launch (kSliceCost microseconds; at 128x96, N = 60000 410 us in one slice).
+constexpr int kMinSlice = 512;
+constexpr float kSliceCost = 6.0f;
+int choose_shape(const Plan& p, int mode, int64_t max_slices, int& slices) {
+  slices = 1;
+#ifdef CGH_CONTRACT_SHAPE
+  return CGH_CONTRACT_SHAPE;
+#endif
+  int best = 0;
+  float best_time = 0.0f;
+  for (int k = 0; k < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++k) {
+    const Shape& q = kShapes[k];
+    const int64_t tiles = (((int64_t)p.nx + q.cols - 1) / q.cols) *
+                          (((int64_t)p.ny + q.rows - 1) / q.rows);
+    const float per_point = 1e-3f * (mode == kHalfF16x3 ? q.split : q.single);
+    const float time = q.fixed + (float)((tiles + 255) / 256) * (float)p.npad * per_point;
+    if (k == 0 || time < best_time) {
+      best = k;
+      best_time = time;
+      slices = 1;
+    }
+    int64_t n = std::min(std::min(256 / tiles, max_slices), p.npad / kMinSlice);
+    if (n < 2) continue;
+    const int64_t per = (p.npad / 64 + n - 1) / n;  // in units of 64 points
+    n = (p.npad / 64 + per - 1) / per;               // none empty
+    const float sliced = q.fixed + kSliceCost + (float)(per * 64) * per_point;
+    if (sliced < best_time) {
+      best = k;
+      best_time = sliced;
+      slices = (int)n;
+    }
+  }
+  return best;
+}
+
+template <int MODE>
+hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const float* tgt,
+                       float* res, hipStream_t s) {
+  switch (c.shape) {
+    case 0: return launch_shape<MODE, 2, 4, 2, 2>(p, c, out, tgt, res, s);
+    case 1: return launch_shape<MODE, 2, 4, 1, 8>(p, c, out, tgt, res, s);
+    case 2: return launch_shape<MODE, 2, 2, 1, 4>(p, c, out, tgt, res, s);
+    case 3: return launch_shape<MODE, 1, 2, 1, 8>(p, c, out, tgt, res, s);
+    case 4: return launch_shape<MODE, 1, 1, 1, 8>(p, c, out, tgt, res, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+}  // namespace
+
+bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
+  c = ContractFwd{};
+  if (p.op != 0) return false;
+  if (p.variant == 1) {
+    // Up to 8 points (one step of the contraction) stay with the direct kernel:
+    // both take the time of their launches there (17 us a call at 101x121,
+    // N = 1), and of a single point the direct form keeps the exact eightfold
+    // symmetry, since A multiplies the whole cosine and not the row factor.
+    if (p.n <= 8) return false;
+    c.mode = kHalfF16x3;
+    c.rows_y = p.groups * kCompRows;
+    c.cols_x = p.fwd_gx * kWave;
+    c.xtab = w.xtab != nullptr;
+    c.yq = w.ytab;
+    c.xq = w.xtab;
+  } else {
+    c.mode = p.variant == 3 ? kHalfF16x3 : p.variant == 4 ? kHalfF16 : kHalfBF16;
+    c.rows_y = p.nyp;
+    c.cols_x = p.nxp;
+    c.xtab = true;
+    c.yq = w.hy_hi;
+    c.xq = w.hx_hi;
+  }
+  c.rec = (float4*)w.xrec;
+  c.amp = w.amp;
+  c.amax = w.hmax;
+  c.planes = w.yrec;  // [npad][8] floats, unused by this path
+  const int64_t max_slices = p.npad * kAxisRec / ((int64_t)p.nx * p.ny);
+  c.shape = choose_shape(p, c.mode, max_slices, c.slices);
+  return true;
+}
+
+hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const float* x,
+                                      const float* y, const float* z, const float* a,
+                                      double pitch, double wavelength, hipStream_t s) {
+  const int yslices = (c.rows_y + kTabRows - 1) / kTabRows;
+  const int xslices = c.xtab ? (c.cols_x + kTabRows - 1) / kTabRows : 0;
+  const dim3 grid((unsigned)(p.npad / 16), (unsigned)(yslices + xslices));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, y, z, a, p.n, pitch, wavelength, yslices,
+                       c.rows_y, c.cols_x, (uint32_t*)c.yq, (uint32_t*)c.xq,
+                       c.xtab ? (float*)nullptr : (float*)c.rec, c.amp, c.amax);
+  };
+  if (c.mode == kHalfF16x3)
+    go(contract_fwd_tables_kernel<kHalfF16x3>);
+  else if (c.mode == kHalfF16)
+    go(contract_fwd_tables_kernel<kHalfF16>);
+  else
+    go(contract_fwd_tables_kernel<kHalfBF16>);
+  return hipGetLastError();
+}
+
+hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
+                               const float* target, float* residual, hipStream_t s) {
+  hipError_t e;
+  if (c.mode == kHalfF16x3)
+    e = launch_mode<kHalfF16x3>(p, c, out, target, residual, s);
+  else if (c.mode == kHalfF16)
+    e = launch_mode<kHalfF16>(p, c, out, target, residual, s);
+  else
+    e = launch_mode<kHalfBF16>(p, c, out, target, residual, s);
+  if (e != hipSuccess || c.slices == 1) return e;
+  const int64_t count = (int64_t)p.nx * p.ny;
+  hipLaunchKernelGGL(contract_fwd_sum_kernel, dim3(grid_blocks(count, 256)), dim3(256), 0, s,
+                     c.planes, c.slices, count, out, target, residual);
+  return hipGetLastError();
+}
+
+}  // namespace cgh

@@ -105,49 +105,6 @@ __device__ __forceinline__ void axis_cs(const float* __restrict__ rec, int64_t j
   }
 }
 
-// Forward operands, one launch: table rows r in [0, nxp) are X [nxp][k2],
-// rows [nxp, nxp + nyp) are Y [nyp][k2] with (A_j cY, -A_j sY) / 2^e.  Lane
-// -> point j = blockIdx.x * 256 + threadIdx.x, the workgroups of one x index
-// stride over the rows; each (cos, sin) pair of 16-bit values is one 32-bit
-// store at [h][j].
-template <int MODE>
-__global__ __launch_bounds__(256) void sep_tables_half_kernel(
-    const float* __restrict__ xrec, const float* __restrict__ yrec,
-    const float* __restrict__ amp, const unsigned* __restrict__ amp_max, int64_t npad, int nx,
-    int nxp, int ny, int nyp, uint32_t* __restrict__ xh, uint32_t* __restrict__ xl,
-    uint32_t* __restrict__ yh, uint32_t* __restrict__ yl) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= npad) return;
-  float xr[5], yr[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    xr[i] = xrec[j * kAxisRec + i];
-    yr[i] = yrec[j * kAxisRec + i];
-  }
-  const float A = amp[j] * inv_scale(amp_max);
-  for (int r = blockIdx.y; r < nxp + nyp; r += gridDim.y) {
-    const bool is_x = r < nxp;
-    const int h = is_x ? r : r - nxp;
-    float c = 0.0f, s = 0.0f;
-    if (h < (is_x ? nx : ny)) {
-      const float* q = is_x ? xr : yr;
-      const float phi = axis_phase((float)h, q[0], q[1], q[2], q[3], q[4]);
-      c = cos_rev(phi);
-      s = sin_rev(phi);
-      if (!is_x) {
-        c = A * c;
-        s = -(A * s);
-      }
-    }
-    uint16_t ch, cl, sh, sl;
-    to_half<MODE>(c, ch, cl);
-    to_half<MODE>(s, sh, sl);
-    const int64_t o = (int64_t)h * npad + j;
-    (is_x ? xh : yh)[o] = (uint32_t)ch | ((uint32_t)sh << 16);
-    if (MODE == kHalfF16x3) (is_x ? xl : yl)[o] = (uint32_t)cl | ((uint32_t)sl << 16);
-  }
-}
-
 // Adjoint operands, one launch (1-D grid).  The first tab_blocks * tab_rows
 // workgroups fill the transposed tables Xt [k2][nxp] then Yt [k2][nyp]:
 // workgroup b takes coordinates h = (b % tab_blocks) * 256 + lane of the
@@ -226,22 +183,6 @@ hipError_t launch_absmax(const float* v, int64_t count, unsigned* out, hipStream
   int64_t blocks = (count + 256 * 16 - 1) / (256 * 16);
   if (blocks > 256) blocks = 256;
   hipLaunchKernelGGL(absmax_kernel, dim3((unsigned)blocks), dim3(256), 0, s, v, count, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_sep_tables_half(int mode, const Plan& p, const Workspace& w, hipStream_t s) {
-  const dim3 grid = table_grid(p.npad, p.nxp + p.nyp), block(256);
-  uint32_t *xh = (uint32_t*)w.hx_hi, *xl = (uint32_t*)w.hx_lo;
-  uint32_t *yh = (uint32_t*)w.hy_hi, *yl = (uint32_t*)w.hy_lo;
-  if (mode == kHalfF16x3)
-    hipLaunchKernelGGL(sep_tables_half_kernel<kHalfF16x3>, grid, block, 0, s, w.xrec, w.yrec,
-                       w.amp, w.hmax, p.npad, p.nx, p.nxp, p.ny, p.nyp, xh, xl, yh, yl);
-  else if (mode == kHalfBF16)
-    hipLaunchKernelGGL(sep_tables_half_kernel<kHalfBF16>, grid, block, 0, s, w.xrec, w.yrec,
-                       w.amp, w.hmax, p.npad, p.nx, p.nxp, p.ny, p.nyp, xh, xl, yh, yl);
-  else
-    hipLaunchKernelGGL(sep_tables_half_kernel<kHalfF16>, grid, block, 0, s, w.xrec, w.yrec,
-                       w.amp, w.hmax, p.npad, p.nx, p.nxp, p.ny, p.nyp, xh, xl, yh, yl);
   return hipGetLastError();
 }
 

@@ -1,0 +1,96 @@
+"""The contraction kernels (operands formed in the kernel, 16-bit matrix
+cores): every tile shape and point split of the forward, at the edges of
+tiles, steps and slices, and the inputs the formats treat specially.
+
+Tolerance of the f16x3 format against the FP64 oracle, as a fraction of
+sum |A|.  A table value is off by 2 pi times its phase error (about
+2^-24 (1 + 1.5 Prev |m|) revolutions, Prev = p^2 / (2 lambda z), |m| the largest
+offset), the transcendental's own error (below 2.5e-7) and the planes'
+rounding (2^-23); a term is two products of two such values, so four of these.
+Adding in FP32 costs at most 2^-24 per addition in a wave's chain (three per 8
+points of its share).
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import TOL_FWD, device, max_err_frac, say, to_dev
+from paper_1002_0916_amd import binding as B
+from paper_1002_0916_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+ZLO = 0.3
+
+
+def f16x3_bar(nx, ny, n, margin):
+    prev = W.PITCH ** 2 / (2 * W.WAVELENGTH * ZLO)
+    phase = 2 * np.pi * 2.0 ** -24 * (1 + 1.5 * prev * (max(nx, ny) + margin))
+    return 4 * (phase + 2.5e-7 + 2.0 ** -23) + 2.0 ** -24 * 3 * (n / 8 + 8)
+
+
+# (nx, ny, n): one step and its neighbours; remainders of 32 and 64 in every
+# size; each tile shape (32x32, 32x64, 64x64, 64x128 and 128x128 pixels); the
+# points in several slices (128x96 and 40x20).
+FORWARD = [(32, 32, 9), (33, 31, 64), (65, 129, 65), (333, 197, 700), (600, 500, 1500),
+           (1024, 1024, 1000), (1920, 1080, 1000), (3840, 2160, 100), (128, 96, 5000),
+           (40, 20, 3001)]
+
+
+@pytest.mark.parametrize("variant", ["compensated", "separable_f16x3", "separable_f16",
+                                     "separable_bf16"])
+@pytest.mark.parametrize("shape", FORWARD)
+def test_forward_shapes(oracle_mod, variant, shape):
+    nx, ny, n = shape
+    dev = device()
+    say("contraction forward", shape, variant)
+    c = W.random_cloud(1000 + n, n, nx, ny, zlo=ZLO, zhi=1.0, alo=-1.0, ahi=1.0, margin=20)
+    x, y, z, a = to_dev(c, dev)
+    rng = np.random.default_rng(n)
+    T = torch.from_numpy(rng.standard_normal((ny, nx)).astype(np.float32)).to(dev)
+    I, G = B.forward_residual(x, y, z, a, T, nx, ny, variant=variant)
+    J = B.forward(x, y, z, a, nx, ny, variant=variant)
+    torch.cuda.synchronize()
+    assert torch.equal(I, J) and torch.equal(G, I - T)
+    px, py = W.sample_pixels(1001, nx, ny, 3000)
+    ref = oracle_mod.forward_at(*c.astuple(), nx, ny, px, py, threads=0)
+    err = max_err_frac(I.cpu().numpy()[py, px], ref, c)
+    bar = (f16x3_bar(nx, ny, n, 20) if variant in ("compensated", "separable_f16x3")
+           else TOL_FWD[variant])
+    say("  max|dI|/sum|A| = %.3e, bar %.3e" % (err, bar))
+    assert err <= bar
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+def test_forward_amplitudes_of_any_scale(oracle_mod, scale):
+    """One amplitude 2^20 times the others, at both ends of the FP32 range."""
+    dev = device()
+    nx, ny, n = 150, 110, 200
+    c = W.random_cloud(1101, n, nx, ny, zlo=ZLO, zhi=1.0, alo=-1.0, ahi=1.0, margin=15)
+    a = c.a.astype(np.float64) * scale * 2.0 ** -20
+    a[7] = scale
+    c = W.Cloud(c.x, c.y, c.z, a.astype(np.float32))
+    I = B.forward(*to_dev(c, dev), nx, ny, variant="compensated").cpu().numpy()
+    ref = oracle_mod.forward(*c.astuple(), nx, ny, threads=0)
+    err = max_err_frac(I, ref, c)
+    say("amplitude scale", scale, "max|dI|/sum|A| =", err)
+    assert np.all(np.isfinite(I)) and err <= f16x3_bar(nx, ny, n, 15)
+
+
+@pytest.mark.parametrize("shape", [(70, 50, 20), (128, 96, 2000)])
+def test_forward_non_finite_amplitudes(shape):
+    """An infinite amplitude gives the infinities of its term's cosine, a NaN
+    gives NaN everywhere, as the sum term by term does."""
+    dev = device()
+    nx, ny, n = shape
+    c = W.random_cloud(1102, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
+    x, y, z, a = to_dev(c, dev)
+    a[3] = float("inf")
+    I = B.forward(x, y, z, a, nx, ny, variant="compensated").cpu().numpy()
+    h, v = np.meshgrid(np.arange(nx), np.arange(ny))
+    P = np.pi * W.PITCH ** 2 / (W.WAVELENGTH * float(c.z[3]))
+    cos = np.cos(P * ((h - float(c.x[3])) ** 2 + (v - float(c.y[3])) ** 2))
+    clear = np.abs(cos) > 1e-3
+    assert np.array_equal(I[clear], np.where(cos > 0, np.inf, -np.inf)[clear])
+    a[3] = float("nan")
+    assert torch.isnan(B.forward(x, y, z, a, nx, ny, variant="compensated")).all()
