@@ -203,8 +203,8 @@ int cgh_backward(const float* x, const float* y, const float* z, const float* a,
  * more scratch than the buffer holds: about 84 bytes per point plus the
  * variant's tables (the compensated forward: 4 bytes per point and row, and
  * 4 per point and column unless dropped to fit, since the kernel can form
- * those values itself; the separable forms: their GEMM tables and split-K
- * planes).  At 1920 x 1024 with 1,024 points every variant fits.
+ * those values itself, and partial planes of a small hologram with many points
+ * where they fit; the separable forms: their GEMM tables and split-K planes).  At 1920 x 1024 with 1,024 points every variant fits.
  *   Every call on a GPU shares that GPU's buffer, which keeps the last call's
  * contents (each call rewrites what it reads): calls that overlap on one GPU
  * (on different streams, or from several threads without ordering) race.

@@ -194,6 +194,22 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.off_xtab = (op == CGH_OP_FORWARD && variant == CGH_COMPENSATED && p.comp_xtab)
                    ? take((size_t)p.fwd_gx * kWave * np * sizeof(float))
                    : 0;
+  // Partial planes of the compensated forward's point slices, where the best
+  // number of slices needs more room than the y records give.  That number is a
+  // rule on the sizes alone and the same with and without the column table, so
+  // that every entry point sums in the same order; and a plan that fits the
+  // static scratch without planes keeps fitting it.
+  if (op == CGH_OP_FORWARD && variant == CGH_COMPENSATED) {
+    const size_t pixels = (size_t)nx * ny;
+    const size_t want = (size_t)contract_fwd_slices(p.npad, nx, ny);
+    const size_t base = off - (p.comp_xtab ? align256((size_t)p.fwd_gx * kWave * np * sizeof(float)) : 0);
+    const size_t bytes = align256(want * pixels * sizeof(float));
+    if (n > 8 && want > 1 && want * pixels > np * kAxisRec &&
+        (base + bytes <= CGH_NOALLOC_SCRATCH_BYTES || base > CGH_NOALLOC_SCRATCH_BYTES)) {
+      p.fwd_planes = (int32_t)want;
+      p.off_planes = take(bytes);
+    }
+  }
   const bool direct_adj = op == CGH_OP_BACKWARD && !is_separable(variant);
   p.off_rtab = (direct_adj && p.adj_kind == kAdjCompensated)
                    ? take((size_t)ny * np * sizeof(float2))
@@ -246,6 +262,7 @@ Workspace carve(const Plan& p, void* base) {
   w.xtab = (p.op == CGH_OP_FORWARD && p.variant == CGH_COMPENSATED && p.comp_xtab)
                ? (float*)(b + p.off_xtab)
                : nullptr;
+  w.planes = p.fwd_planes > 0 ? (float*)(b + p.off_planes) : nullptr;
   const bool direct_adj = p.op == CGH_OP_BACKWARD && !is_separable(p.variant);
   w.rtab = (direct_adj && p.adj_kind == kAdjCompensated) ? (float2*)(b + p.off_rtab) : nullptr;
   w.ctab = (direct_adj && p.adj_kind == kAdjCompensated) ? (float*)(b + p.off_ctab) : nullptr;

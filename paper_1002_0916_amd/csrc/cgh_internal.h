@@ -181,6 +181,7 @@ struct Workspace {
   double4* rec64;  // [npad]
   float* ytab;     // forward, compensated: [groups][npad][kCompRows]
   float* xtab;     // forward, compensated (optional): [fwd_gx * 64][npad] x-phases
+  float* planes;   // forward, compensated (optional): [fwd_planes][ny][nx] partial sums
   float2* rtab;    // adjoint, compensated: [ny][npad] {cos, sin of the y-phase}
   float* ctab;     // adjoint, compensated: [nsx * kAdjCols][npad] x-phases
   float* partial;  // adjoint: [regions][npad][4]
@@ -207,6 +208,7 @@ struct Plan {
   // forward
   int32_t fwd_gx, fwd_gy, comp_gy, groups;
   bool comp_xtab;  // the compensated forward has its column table
+  int32_t fwd_planes;  // partial planes of the compensated forward (0: none of its own)
   int32_t rec_k, rec_r, rec_s, rec_gx, rec_gy;  // recurrence forward shape, split, grid
   // adjoint: runs of strip-rows per point group (regions = the most runs the
   // partial buffer holds; the launch may use fewer)
@@ -219,7 +221,7 @@ struct Plan {
   int64_t k2;
   size_t off_sep_x, off_sep_y, off_sep_c, off_sep_g, off_fold_x, off_fold_y;
   size_t off_hx, off_hy, off_hg, off_hgt, off_hmax;  // half variants (hi plane; lo follows)
-  size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_rtab,
+  size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_rtab,
       off_ctab, off_partial, off_gpad, total;
 };
 

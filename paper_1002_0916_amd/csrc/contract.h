@@ -148,11 +148,13 @@ struct ContractFwd {
   void* xq;
   float4* rec;
   float* amp;
-  unsigned* amax;     // largest |A| as float bits, one word (single planes)
+  unsigned* amax;     // [kWave] maxima of |A| as float bits (single planes)
   int slices;         // the points are cut into this many slices,
   float* planes;      //   with a plane [ny][nx] each when there are several
 };
 bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c);
+// The number of point slices of the f16x3 forward given room for any number.
+int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny);
 hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const float* x,
                                       const float* y, const float* z, const float* a,
                                       double pitch, double wavelength, hipStream_t s);

@@ -30,6 +30,7 @@ namespace {
 
 constexpr int kBand = 8;       // tile rows per band of the tile order
 constexpr int kTabRows = 256;  // coordinates per table workgroup slice
+constexpr int kAmaxInline = 8192;  // points up to which the tables find max |A| themselves
 
 // (cos, sin) operand block share from four phases, times a factor each for the
 // cosine and the sine.
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     }
     m = group_max<kThreads>(m, red);
   } else {
-    m = *amax;
+    m = group_max<kWave>(amax[lane], red);
   }
   float mul, undo;
   operand_scale<MODE>(m, mul, undo);
@@ -375,6 +376,17 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
   }
 }
 
+// Largest |A| (0 unless finite) of each of kWave parts of the points.
+__global__ __launch_bounds__(256) void contract_amax_kernel(const float* __restrict__ a, int64_t n,
+                                                            unsigned* __restrict__ amax) {
+  __shared__ unsigned red[4];
+  unsigned m = 0;
+  for (int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x; k < n; k += 256 * kWave)
+    m = max(m, __float_as_uint(fabsf(a[k])));
+  m = group_max<256>(m, red);
+  if (threadIdx.x == 0) amax[blockIdx.x] = m;
+}
+
 // Both tables, the amplitudes and (without an x table) the x records in one
 // launch.  A workgroup is 16 points (blockIdx.x) and kTabRows coordinates
 // (blockIdx.y: y slices, then x slices).  Lane l of wave w takes point
@@ -395,13 +407,19 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
   const int slice = is_y ? (int)blockIdx.y : (int)blockIdx.y - yslices;
   float mul = 1.0f;
   if (MODE != kHalfF16x3 && is_y) {
-    // every y workgroup takes the largest |A| itself: n words from the cache
+    // Few points: every y workgroup takes the largest |A| itself, n words from
+    // the cache; else the maxima of contract_amax_kernel are there.
     unsigned m = 0;
-    for (int64_t k = threadIdx.x; k < n; k += 256) m = max(m, __float_as_uint(fabsf(a[k])));
-    m = group_max<256>(m, red);
+    if (n <= kAmaxInline) {
+      for (int64_t k = threadIdx.x; k < n; k += 256) m = max(m, __float_as_uint(fabsf(a[k])));
+      m = group_max<256>(m, red);
+      m = finite_bits(m) ? m : 0u;
+      if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWave) amax[threadIdx.x] = m;
+    } else {
+      m = group_max<kWave>(amax[lane], red);
+    }
     float undo;
-    operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *amax = finite_bits(m) ? m : 0u;
+    operand_scale<MODE>(m, mul, undo);
   }
   const PointRecord r = point_record(x, y, z, a, j, n, pitch, wavelength);
   if (blockIdx.y == 0 && lane < 4) {
@@ -480,60 +498,53 @@ __global__ __launch_bounds__(256) void contract_fwd_sum_kernel(const float* __re
   if (res) res[i] = v - tgt[i];
 }
 
-// Tile shapes: kernel <MI, NJ, WM, KS>, pixels per workgroup, and the two terms
-// of its time, measured on this GPU: microseconds per launch beside the loop,
-// and per round of 256 workgroups (one a CU) and 1000 points, for the f16x3
-// format and for the single planes.  Larger tiles form fewer operands per
-// product; smaller ones and more point groups put a small hologram on more
-// CUs.  (At 3840x2160, N = 16384 the five take 1.47, 1.77, 1.99, 2.46 and
-// 3.13 ms, at 1920x1080, N = 8192 0.33, 0.23, 0.27, 0.32 and 0.40 ms, at
-// 1024x1024, N = 4096 164, 96, 75, 81 and 100 us, and at 333x197, N = 700 35,
-// 28, 20, 12 and 9.5 us.)
+// Tile shapes <MI, NJ, WM, KS>: pixels per workgroup and the terms of its time
+// on this GPU: microseconds per launch beside the loop, and per 1000 points and
+// round of 256 workgroups (one a CU), for f16x3 and for the single planes, each
+// in a launch of one round and of more.  Larger tiles form fewer operands per
+// product (per pixel <2, 4, 2, 2> takes 0.7 of <2, 2, 1, 4>'s time and 0.4 of
+// <1, 1, 1, 8>'s); smaller ones and more point groups put a small hologram on
+// more CUs.  Measured at 50 random sizes (64 to 3840 by 64 to 2160, 64 to 65,536
+// points), the choice is within 4% of the best shape on average, 21% at most.
 struct Shape {
   int rows, cols;
-  float fixed, split, single;
+  float fixed, split_one, split, single_one, single;
 };
 constexpr Shape kShapes[] = {
-    {128, 128, 9.5f, 44.8f, 17.0f},  // <2, 4, 2, 2>
-    {64, 128, 12.0f, 24.5f, 10.0f},  // <2, 4, 1, 8>
-    {64, 64, 7.5f, 14.7f, 6.2f},     // <2, 2, 1, 4>
-    {32, 64, 7.0f, 9.6f, 4.5f},      // <1, 2, 1, 8>
-    {32, 32, 5.0f, 6.0f, 3.6f},      // <1, 1, 1, 8>
+    {128, 128, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f},  // <2, 4, 2, 2>
+    {64, 128, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f},   // <2, 4, 1, 8>
+    {64, 64, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f},     // <2, 2, 1, 4>
+    {64, 64, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f},      // <2, 2, 1, 8>
+    {32, 64, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f},      // <1, 2, 1, 8>
+    {32, 32, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f},        // <1, 1, 1, 8>
 };
 
-// Shape and slices for plan p.  Fewer than 256 tiles leave CUs idle: where the
-// plan has room for that many planes, the points are cut into as many slices as
-// the tiles leave CUs, of at least kMinSlice points each, which costs one more
-// launch (kSliceCost microseconds; at 128x96, N = 60000 410 us in one slice).
-constexpr int kMinSlice = 512;
-constexpr float kSliceCost = 6.0f;
-int choose_shape(const Plan& p, int mode, int64_t max_slices, int& slices) {
-  slices = 1;
-#ifdef CGH_CONTRACT_SHAPE
-  return CGH_CONTRACT_SHAPE;
-#endif
+// Shape and slices for plan p.  Cutting the points into slices (as far as the
+// plan has room for their planes) puts a small hologram of many points on more
+// CUs, at one more launch (6 us) and the planes' traffic (at 3 TB/s); a slice
+// has at least 512 points.  (128x96, N = 60000: 410 us in one slice, 36 in 21.)
+int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices, int& slices) {
   int best = 0;
   float best_time = 0.0f;
+  slices = 1;
+  const int64_t units = npad / 64;  // points are cut in units of 64
+  const float plane_us = (float)nx * (float)ny * (8.0f / 3e6f);
   for (int k = 0; k < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++k) {
     const Shape& q = kShapes[k];
-    const int64_t tiles = (((int64_t)p.nx + q.cols - 1) / q.cols) *
-                          (((int64_t)p.ny + q.rows - 1) / q.rows);
-    const float per_point = 1e-3f * (mode == kHalfF16x3 ? q.split : q.single);
-    const float time = q.fixed + (float)((tiles + 255) / 256) * (float)p.npad * per_point;
-    if (k == 0 || time < best_time) {
-      best = k;
-      best_time = time;
-      slices = 1;
-    }
-    int64_t n = std::min(std::min(256 / tiles, max_slices), p.npad / kMinSlice);
-    if (n < 2) continue;
-    const int64_t per = (p.npad / 64 + n - 1) / n;  // in units of 64 points
-    n = (p.npad / 64 + per - 1) / per;               // none empty
-    const float sliced = q.fixed + kSliceCost + (float)(per * 64) * per_point;
-    if (sliced < best_time) {
-      best = k;
-      best_time = sliced;
-      slices = (int)n;
+    const int64_t tiles = (((int64_t)nx + q.cols - 1) / q.cols) * (((int64_t)ny + q.rows - 1) / q.rows);
+    for (int64_t want = 1; want <= max_slices || want == 1; want += want < 4 ? 1 : want / 2) {
+      if (want > 1 && (units < 8 * want || tiles * want > 1024)) break;
+      const int64_t per = (units + want - 1) / want, n = (units + per - 1) / per;  // none empty
+      const int64_t rounds = (tiles * n + 255) / 256;
+      const float per_k = mode == kHalfF16x3 ? (rounds == 1 ? q.split_one : q.split)
+                                             : (rounds == 1 ? q.single_one : q.single);
+      const float time = q.fixed + (float)rounds * (float)(per * 64) * 1e-3f * per_k +
+                         (n > 1 ? 6.0f + (float)n * plane_us : 0.0f);
+      if (best_time == 0.0f || time < best_time) {
+        best = k;
+        best_time = time;
+        slices = (int)n;
+      }
     }
   }
   return best;
@@ -546,13 +557,20 @@ hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const fl
     case 0: return launch_shape<MODE, 2, 4, 2, 2>(p, c, out, tgt, res, s);
     case 1: return launch_shape<MODE, 2, 4, 1, 8>(p, c, out, tgt, res, s);
     case 2: return launch_shape<MODE, 2, 2, 1, 4>(p, c, out, tgt, res, s);
-    case 3: return launch_shape<MODE, 1, 2, 1, 8>(p, c, out, tgt, res, s);
-    case 4: return launch_shape<MODE, 1, 1, 1, 8>(p, c, out, tgt, res, s);
+    case 3: return launch_shape<MODE, 2, 2, 1, 8>(p, c, out, tgt, res, s);
+    case 4: return launch_shape<MODE, 1, 2, 1, 8>(p, c, out, tgt, res, s);
+    case 5: return launch_shape<MODE, 1, 1, 1, 8>(p, c, out, tgt, res, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 }  // namespace
+
+int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny) {
+  int slices;
+  (void)choose_shape(npad, nx, ny, kHalfF16x3, INT64_MAX / 2, slices);
+  return slices;
+}
 
 bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   c = ContractFwd{};
@@ -580,9 +598,21 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   c.rec = (float4*)w.xrec;
   c.amp = w.amp;
   c.amax = w.hmax;
-  c.planes = w.yrec;  // [npad][8] floats, unused by this path
-  const int64_t max_slices = p.npad * kAxisRec / ((int64_t)p.nx * p.ny);
-  c.shape = choose_shape(p, c.mode, max_slices, c.slices);
+  // Planes of the point slices: the plan's own, the split planes of the
+  // separable plans, or the y records (which this path does not use).
+  const int64_t pixels = (int64_t)p.nx * p.ny;
+  const int64_t in_rec = p.npad * kAxisRec / pixels;
+  const int64_t in_sep = w.sep_c ? p.sep_splits * ((int64_t)p.nxp * p.nyp) / pixels : 0;
+  int64_t room = in_rec;
+  c.planes = w.yrec;
+  if (p.fwd_planes > 0) {
+    room = p.fwd_planes;
+    c.planes = w.planes;
+  } else if (in_sep > in_rec) {
+    room = in_sep;
+    c.planes = w.sep_c;
+  }
+  c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, c.slices);
   return true;
 }
 
@@ -592,6 +622,8 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
   const int yslices = (c.rows_y + kTabRows - 1) / kTabRows;
   const int xslices = c.xtab ? (c.cols_x + kTabRows - 1) / kTabRows : 0;
   const dim3 grid((unsigned)(p.npad / 16), (unsigned)(yslices + xslices));
+  if (c.mode != kHalfF16x3 && p.n > kAmaxInline)
+    hipLaunchKernelGGL(contract_amax_kernel, dim3(kWave), dim3(256), 0, s, a, p.n, c.amax);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, y, z, a, p.n, pitch, wavelength, yslices,
                        c.rows_y, c.cols_x, (uint32_t*)c.yq, (uint32_t*)c.xq,
