@@ -237,14 +237,13 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
       (sep && bwd) ? take((size_t)p.sep_splits_u * (nxp / 128) * np * sizeof(float4)) : 0;
   p.off_fold_y =
       (sep && bwd) ? take((size_t)p.sep_splits_p * (nyp / 128) * np * sizeof(float4)) : 0;
-  // 16-bit planes: hi, then (f16x3) lo at the next 256-byte boundary.
+  // The contraction's tables hold 4 bytes a point and coordinate; the f16x3 ones
+  // take the room of two 16-bit planes of cosines and sines, so that the problems
+  // the static scratch holds do not depend on how a table is laid out.
   const size_t planes = hm == kHalfF16x3 ? 2 : 1;
-  auto take_planes = [&](size_t elems) { return take(planes * align256(elems * 2)); };
-  p.off_hx = hm >= 0 ? take_planes(nxp * k2) : 0;
-  p.off_hy = hm >= 0 ? take_planes(nyp * k2) : 0;
-  p.off_hg = (hm >= 0 && bwd) ? take_planes(nyp * nxp) : 0;
-  p.off_hgt = (hm >= 0 && bwd) ? take_planes(nyp * nxp) : 0;
-  p.off_hmax = hm >= 0 ? take(sizeof(unsigned)) : 0;
+  p.off_hx = hm >= 0 ? take(planes * align256(nxp * k2 * 2)) : 0;
+  p.off_hy = hm >= 0 ? take(planes * align256(nyp * k2 * 2)) : 0;
+  p.off_hmax = hm >= 0 ? take(kWave * sizeof(unsigned)) : 0;
   p.total = off;
   return p;
 }
@@ -279,18 +278,8 @@ Workspace carve(const Plan& p, void* base) {
   w.fold_x = (sep && bwd) ? (float4*)(b + p.off_fold_x) : nullptr;
   w.fold_y = (sep && bwd) ? (float4*)(b + p.off_fold_y) : nullptr;
   if (hm >= 0) {
-    const size_t k2 = (size_t)p.k2, nxp = (size_t)p.nxp, nyp = (size_t)p.nyp;
-    const bool split = hm == kHalfF16x3;
-    auto planes = [&](size_t off, size_t elems, uint16_t*& hi, uint16_t*& lo) {
-      hi = (uint16_t*)(b + off);
-      lo = split ? (uint16_t*)(b + off + align256(elems * 2)) : nullptr;
-    };
-    planes(p.off_hx, nxp * k2, w.hx_hi, w.hx_lo);
-    planes(p.off_hy, nyp * k2, w.hy_hi, w.hy_lo);
-    if (bwd) {
-      planes(p.off_hg, nyp * nxp, w.hg_hi, w.hg_lo);
-      planes(p.off_hgt, nyp * nxp, w.hgt_hi, w.hgt_lo);
-    }
+    w.htab_x = b + p.off_hx;
+    w.htab_y = b + p.off_hy;
     w.hmax = (unsigned*)(b + p.off_hmax);
   }
   return w;
@@ -447,29 +436,21 @@ int forward_contract(const Plan& p, const ContractFwd& c, int kernel, const floa
   return hip_status(e);
 }
 
-// Half-precision separable variants: the adjoint's contractions on 16-bit planes
-// (G divided by a power of two recorded in w.hmax).
-int backward_separable_half(const Plan& p, const Workspace& w, const float* z, const float* a,
-                            double pitch, double wavelength, const float* g, float* gx, float* gy,
-                            float* gz, float* ga, hipStream_t s) {
-  const int hm = half_mode(p.variant);
-  hipError_t e = launch_absmax(g, (int64_t)p.nx * p.ny, w.hmax, s);  // w.hmax cleared by prep
-  if (e == hipSuccess) e = launch_sep_adj_operands_half(hm, p, w, g, s);
+// The adjoint as two contractions folded in the kernel (contract_adj.hip), then
+// the per-point sums of its planes.
+int backward_contract(const Plan& p, const Workspace& w, const ContractAdj& c, int kernel,
+                      const float* x, const float* y, const float* z, const float* a,
+                      double pitch, double wavelength, const float* g, float* gx, float* gy,
+                      float* gz, float* ga, hipStream_t s) {
+  hipError_t e = launch_contract_adj_tables(p, c, x, y, z, a, pitch, wavelength, g, s);
   if (e != hipSuccess) return CGH_EHIP;
-  const FoldSpec fx{1, w.xrec, w.plain, p.nx, w.fold_x};
-  const FoldSpec fy{2, w.yrec, w.plain, p.ny, w.fold_y};
-  const EventPair ev = profile_begin(CGH_KERNEL_ADJ_SEPARABLE, s);
-  // U[k][x] = sum_y Yt[k][y] Gt[x][y], folded in the epilogue
-  e = launch_gemm_half(hm, w.hy_hi, w.hy_lo, p.nyp, w.hgt_hi, w.hgt_lo, p.nyp, nullptr, 0, 0,
-                       (int)p.k2, p.nxp, p.nyp, p.sep_splits_u, (int)p.k2, p.nxp, w.hmax, &fx, s);
-  // Pm[k][y] = sum_x Xt[k][x] G[y][x], folded in the epilogue
-  if (e == hipSuccess)
-    e = launch_gemm_half(hm, w.hx_hi, w.hx_lo, p.nxp, w.hg_hi, w.hg_lo, p.nxp, nullptr, 0, 0,
-                         (int)p.k2, p.nyp, p.nxp, p.sep_splits_p, (int)p.k2, p.nyp, w.hmax, &fy,
-                         s);
-  profile_end(CGH_KERNEL_ADJ_SEPARABLE, ev, s);
+  const EventPair ev = profile_begin(kernel, s);
+  e = launch_contract_adj(p, c, x, y, z, a, pitch, wavelength, g, s);
+  profile_end(kernel, ev, s);
   if (e != hipSuccess) return CGH_EHIP;
-  e = launch_sep_finalize(p, w, z, a, pitch, wavelength, gx, gy, gz, ga, s);
+  Workspace sums = w;
+  sums.partial = (float*)c.partial;
+  e = launch_adj_finalize(p, sums, z, a, pitch, wavelength, c.planes, gx, gy, gz, ga, s);
   return hip_status(e);
 }
 
@@ -678,14 +659,21 @@ int cgh_backward(const float* x, const float* y, const float* z, const float* a,
   if (rc) return rc;
   const Workspace w = carve(p, workspace);
   hipError_t e;
-  if (is_separable(variant)) {
+  if (variant == CGH_COMPENSATED || half_mode(variant) >= 0) {
+    ContractAdj c;
+    if (plan_contract_adj(p, w, c))
+      return backward_contract(p, w, c,
+                               variant == CGH_COMPENSATED ? CGH_KERNEL_ADJ_COMPENSATED
+                                                          : CGH_KERNEL_ADJ_SEPARABLE,
+                               x, y, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
+                               grad_z, grad_a, s);
+    if (variant != CGH_COMPENSATED) return CGH_EHIP;  // its plan always holds the planes
+  }
+  if (variant == CGH_SEPARABLE) {
     e = launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, false, s);
     if (e != hipSuccess) return CGH_EHIP;
-    if (variant == CGH_SEPARABLE)
-      return backward_separable(p, w, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
-                                grad_z, grad_a, s);
-    return backward_separable_half(p, w, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
-                                   grad_z, grad_a, s);
+    return backward_separable(p, w, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
+                              grad_z, grad_a, s);
   }
   // The direct adjoint forms each point's records itself (one point per
   // lane); the compensated one takes its row phases from a table built here.

@@ -193,12 +193,9 @@ struct Workspace {
   float* sep_g;    // adjoint: G zero-padded to [nyp][nxp]
   float4* fold_x;  // adjoint: x-part fold planes [splits_u][nxp / 128][npad]
   float4* fold_y;  // adjoint: y-part fold planes [splits_p][nyp / 128][npad]
-  // half-precision separable variants: 16-bit planes (hi, lo) and scales
-  uint16_t *hx_hi, *hx_lo;   // forward [nxp][k2]; adjoint transposed [k2][nxp]
-  uint16_t *hy_hi, *hy_lo;   // forward [nyp][k2] (with A); adjoint [k2][nyp]
-  uint16_t *hg_hi, *hg_lo;   // adjoint: G [nyp][nxp]
-  uint16_t *hgt_hi, *hgt_lo; // adjoint: G^T [nxp][nyp]
-  unsigned* hmax;            // largest |A| (forward) or |G| (adjoint), as float bits
+  // half-precision separable variants: the contraction's tables and max |A|
+  void *htab_x, *htab_y;
+  unsigned* hmax;  // [kWave] maxima of |A|, as float bits
 };
 
 struct Plan {
@@ -220,7 +217,7 @@ struct Plan {
   int32_t nxp, nyp, sep_splits, sep_splits_u, sep_splits_p;
   int64_t k2;
   size_t off_sep_x, off_sep_y, off_sep_c, off_sep_g, off_fold_x, off_fold_y;
-  size_t off_hx, off_hy, off_hg, off_hgt, off_hmax;  // half variants (hi plane; lo follows)
+  size_t off_hx, off_hy, off_hmax;  // half variants
   size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_rtab,
       off_ctab, off_partial, off_gpad, total;
 };
@@ -232,8 +229,6 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
 Workspace carve(const Plan& p, void* base);
 
 // Launch wrappers (return the hipError_t of the launch).
-// The prep kernel also clears w.hmax (when the plan has one) for the
-// abs-max reduction that follows it on the stream.
 hipError_t launch_prep(const float* x, const float* y, const float* z, const float* a, int64_t n,
                        int64_t npad, double pitch, double wavelength, const Workspace& w,
                        bool want64, hipStream_t s);
@@ -300,37 +295,11 @@ hipError_t launch_sep_pad(const float* g, int nx, int ny, int rows_pad, int cols
 hipError_t launch_sep_finalize(const Plan& p, const Workspace& w, const float* z, const float* a,
                                double pitch, double wavelength, float* gx, float* gy, float* gz,
                                float* ga, hipStream_t s);
-// Half-precision matrix-core GEMM (gemm_half.hip), K-contiguous 16-bit
-// planes; formats:
+// Formats of the 16-bit matrix-core operands (contract.h):
 constexpr int kHalfF16 = 0;    // one fp16 plane per operand
 constexpr int kHalfBF16 = 1;   // one bf16 plane per operand
 constexpr int kHalfF16x3 = 2;  // fp16 hi + lo planes, hi*hi + hi*lo + lo*hi
-hipError_t launch_gemm_half(int mode, const uint16_t* Ah, const uint16_t* Al, int64_t lda,
-                            const uint16_t* Bh, const uint16_t* Bl, int64_t ldb, float* C,
-                            int64_t ldc, int64_t slice_stride, int M, int N, int K, int splits,
-                            int m_valid, int n_valid, const unsigned* scale_max,
-                            const FoldSpec* fold, hipStream_t s);
 
-// Power-of-two scale 2^e >= m for the largest magnitude m, given as the bits
-// of the non-negative float m (1 when m is 0 or not finite).  Dividing an
-// operand by it maps it into [-1, 1] exactly (only the exponent changes).
-__device__ __forceinline__ float pow2_scale(unsigned max_bits) {
-  const float m = __uint_as_float(max_bits);
-  if (!(m > 0.0f) || !(m < 3.0e38f)) return 1.0f;
-  int e;
-  const float f = frexpf(m, &e);  // m = f 2^e, f in [0.5, 1)
-  (void)f;
-  return ldexpf(1.0f, e);
-}
-
-// Separable variants with half-precision contractions (separable_half.hip).
-// launch_absmax raises *out (cleared beforehand, by the prep kernel) to the
-// float bits of max |v|.
-hipError_t launch_absmax(const float* v, int64_t count, unsigned* out, hipStream_t s);
-// Adjoint operands: Xt [k2][nxp], Yt [k2][nyp], and G / 2^e as G [nyp][nxp]
-// and Gt [nxp][nyp] planes, in one launch.
-hipError_t launch_sep_adj_operands_half(int mode, const Plan& p, const Workspace& w,
-                                        const float* g, hipStream_t s);
 // Runs per point group for this launch (<= p.regions), from the occupancy of
 // the adjoint kernel on the current device.
 int adj_runs(const Plan& p);

@@ -1,5 +1,6 @@
-// The hologram sum as a contraction on the 16-bit matrix cores,
-// with the operands formed inside the kernel (contract_fwd.hip).
+// The hologram sum and its adjoint as contractions on the 16-bit matrix cores,
+// with the operands formed inside the kernels (contract_fwd.hip,
+// contract_adj.hip).
 //
 // The phase of Eq. (1) (Section 1) separates by axis, theta = X_j(x) + Y_j(y)
 // revolutions, each part the compensated axis_phase, and by the addition
@@ -12,9 +13,9 @@
 //               and what is dropped, lo*lo, is below 2^-22 of the product.
 //   kHalfF16, kHalfBF16   v rounded once to 16 bits, one product.
 //
-// Cosines and sines lie in [-1, 1].  The amplitudes A_j are multiplied by a power
-// of two first (exact), which puts the largest below 2^15 (f16x3) or 1 (the
-// single planes): with fp16's smallest step at 2^-24, a value down to 2^-16 of
+// Cosines and sines lie in [-1, 1].  The other operand's values (A_j forward, G
+// in the adjoint) are multiplied by a power of two first (exact), which puts the
+// largest below 2^15 (f16x3) or 1 (the single planes): with fp16's smallest step at 2^-24, a value down to 2^-16 of
 // the largest keeps both planes at full width, and the absolute error of a
 // smaller one is below 2^-39 of the largest.
 #pragma once
@@ -160,5 +161,28 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
                                       double pitch, double wavelength, hipStream_t s);
 hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
                                const float* target, float* residual, hipStream_t s);
+
+// ----------------------------------------------------------------- adjoint --
+// Tables of the adjoint, a quad of coordinates at a time (lane = point):
+//   f16x3        float [ceil(size / 4)][npad][4]   the axis phase
+//   f16, bf16    two planes uint32 [ceil(size / 4)][npad][2]: cosines, sines
+struct ContractAdj {
+  int mode;
+  bool tab;           // the tables exist (else the kernel forms the phases)
+  void *yq, *xq;
+  unsigned* gmax;     // [gblocks] block maxima of |G| (float bits)
+  int gblocks;
+  float4* partial;    // [planes][npad] {Sc, Sx, Sy, Sr}
+  int planes;
+  int groups_u, slices_u, groups_p, slices_p;  // column groups x K slices of each part
+};
+bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c);
+hipError_t launch_contract_adj_tables(const Plan& p, const ContractAdj& c, const float* x,
+                                      const float* y, const float* z, const float* a,
+                                      double pitch, double wavelength, const float* g,
+                                      hipStream_t s);
+hipError_t launch_contract_adj(const Plan& p, const ContractAdj& c, const float* x,
+                               const float* y, const float* z, const float* a, double pitch,
+                               double wavelength, const float* g, hipStream_t s);
 
 }  // namespace cgh

@@ -592,8 +592,8 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
     c.rows_y = p.nyp;
     c.cols_x = p.nxp;
     c.xtab = true;
-    c.yq = w.hy_hi;
-    c.xq = w.hx_hi;
+    c.yq = w.htab_y;
+    c.xq = w.htab_x;
   }
   c.rec = (float4*)w.xrec;
   c.amp = w.amp;

@@ -48,10 +48,8 @@ __global__ __launch_bounds__(256) void prep_kernel(const float* __restrict__ x,
                                                    float* __restrict__ amp,
                                                    float* __restrict__ xrec,
                                                    float* __restrict__ yrec,
-                                                   double4* __restrict__ rec64,
-                                                   unsigned* __restrict__ clear) {
+                                                   double4* __restrict__ rec64) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (clear && j == 0) *clear = 0u;
   if (j >= npad) return;
   store_records(point_record(x, y, z, a, j, n, pitch, wavelength), j, plain, amp, xrec, yrec,
                 rec64);
@@ -154,7 +152,7 @@ hipError_t launch_prep(const float* x, const float* y, const float* z, const flo
                        bool want64, hipStream_t s) {
   hipLaunchKernelGGL(prep_kernel, dim3(grid_blocks(npad, 256)), dim3(256), 0, s, x, y, z, a, n,
                      npad, pitch, wavelength, w.plain, w.amp, w.xrec, w.yrec,
-                     want64 ? w.rec64 : (double4*)nullptr, w.hmax);
+                     want64 ? w.rec64 : (double4*)nullptr);
   return hipGetLastError();
 }
 

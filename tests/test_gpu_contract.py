@@ -1,6 +1,7 @@
 """The contraction kernels (operands formed in the kernel, 16-bit matrix
-cores): every tile shape and point split of the forward, at the edges of
-tiles, steps and slices, and the inputs the formats treat specially.
+cores): every tile shape and point split of the forward and the adjoint's
+tiles, slices and column groups, at their edges, and the inputs the formats
+treat specially.
 
 Tolerance of the f16x3 format against the FP64 oracle, as a fraction of
 sum |A|.  A table value is off by 2 pi times its phase error (about
@@ -14,7 +15,8 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_helpers import TOL_FWD, device, max_err_frac, say, to_dev
+from gpu_helpers import (TOL_ADJ, TOL_FWD, device, max_err_frac, rel_l2, say, to_dev,
+                         upstream_gradient)
 from paper_1002_0916_amd import binding as B
 from paper_1002_0916_amd import workloads as W
 
@@ -94,3 +96,76 @@ def test_forward_non_finite_amplitudes(shape):
     assert np.array_equal(I[clear], np.where(cos > 0, np.inf, -np.inf)[clear])
     a[3] = float("nan")
     assert torch.isnan(B.forward(x, y, z, a, nx, ny, variant="compensated")).all()
+
+
+# (nx, ny, n): tiles of 128 coordinates, stages of 32 and steps of 16 with their
+# remainders on both axes, blocks of 128 points with theirs; several tiles per
+# workgroup (640x100) and a single short one.
+ADJOINT = [(32, 32, 9), (33, 32, 64), (65, 129, 65), (129, 127, 200), (333, 197, 700),
+           (640, 100, 3000), (40, 1500, 129), (1501, 37, 130)]
+
+
+@pytest.mark.parametrize("variant", ["compensated", "separable_f16x3", "separable_f16",
+                                     "separable_bf16"])
+@pytest.mark.parametrize("shape", ADJOINT)
+def test_adjoint_shapes(oracle_mod, variant, shape):
+    """The f16x3 bar is the forward's, with the chain of additions over the
+    longer side (three per 16 coordinates); a sum of many terms of either sign
+    and its error grow alike, so the bar holds for the relative L2 error."""
+    nx, ny, n = shape
+    dev = device()
+    say("contraction adjoint", shape, variant)
+    c = W.random_cloud(1200 + n, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0, margin=20)
+    G = upstream_gradient(oracle_mod, nx, ny, 1201)
+    # G at an address that is a multiple of 4 bytes only
+    flat = torch.empty(nx * ny + 1, device=dev)
+    g = flat[1:].view(ny, nx)
+    g.copy_(torch.from_numpy(G))
+    grads = B.backward(*to_dev(c, dev), g, nx, ny, variant=variant)
+    again = B.backward(*to_dev(c, dev), g, nx, ny, variant=variant)
+    idx = np.arange(0, n, max(1, n // 200))
+    ref = oracle_mod.adjoint(*c.astuple(), nx, ny, G, idx=idx, threads=0)
+    bar = (f16x3_bar(nx, ny, max(nx, ny) / 2, 20)
+           if variant in ("compensated", "separable_f16x3") else TOL_ADJ[variant])
+    for name, t, u, r in zip("xyza", grads, again, ref):
+        assert torch.equal(t, u)
+        e = rel_l2(t.cpu().numpy()[idx], r)
+        say("  d%s rel-L2 = %.3e, bar %.3e" % (name, e, bar))
+        assert e <= bar
+
+
+def test_adjoint_non_finite_gradient():
+    """An infinite G gives each point the infinity of its term, a NaN gives NaN."""
+    dev = device()
+    nx, ny, n = 70, 150, 200
+    c = W.random_cloud(1301, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
+    x, y, z, a = to_dev(c, dev)
+    g = torch.from_numpy(np.random.default_rng(3).standard_normal((ny, nx)).astype(np.float32))
+    g = g.to(dev)
+    px, py = 61, 140
+    g[py, px] = float("inf")
+    ga = B.backward(x, y, z, a, g, nx, ny, variant="compensated")[3].cpu().numpy()
+    P = np.pi * W.PITCH ** 2 / (W.WAVELENGTH * c.z.astype(np.float64))
+    cos = np.cos(P * ((px - c.x.astype(np.float64)) ** 2 + (py - c.y.astype(np.float64)) ** 2))
+    clear = np.abs(cos) > 1e-3
+    assert np.array_equal(ga[clear], np.where(cos > 0, np.inf, -np.inf)[clear])
+    g[py, px] = float("nan")
+    for t in B.backward(x, y, z, a, g, nx, ny, variant="compensated"):
+        assert torch.isnan(t).all()
+
+
+@pytest.mark.parametrize("scale", [1e-30, 1e30])
+def test_adjoint_gradient_of_any_scale(oracle_mod, scale):
+    """One pixel 2^20 times the others, at both ends of the FP32 range."""
+    dev = device()
+    nx, ny, n = 150, 110, 100
+    c = W.random_cloud(1302, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
+    G = np.random.default_rng(5).standard_normal((ny, nx)) * scale * 2.0 ** -20
+    G[40, 77] = scale
+    G = G.astype(np.float32)
+    ga = B.backward(*to_dev(c, dev), torch.from_numpy(G).to(dev), nx, ny,
+                    variant="compensated")[3].cpu().numpy()
+    ref = oracle_mod.adjoint(*c.astuple(), nx, ny, G, threads=0)[3]
+    e = rel_l2(ga.astype(np.float64) / scale, ref / scale)
+    say("gradient scale", scale, "rel-L2 =", e)
+    assert np.all(np.isfinite(ga)) and e <= f16x3_bar(nx, ny, nx / 2, 0)
