@@ -507,23 +507,28 @@ __global__ __launch_bounds__(256) void contract_fwd_sum_kernel(const float* __re
 // more CUs.  Measured at 50 random sizes (64 to 3840 by 64 to 2160, 64 to 65,536
 // points), the choice is within 4% of the best shape on average, 21% at most.
 struct Shape {
-  int rows, cols;
+  int rows, cols, groups;
   float fixed, split_one, split, single_one, single;
 };
 constexpr Shape kShapes[] = {
-    {128, 128, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f},  // <2, 4, 2, 2>
-    {64, 128, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f},   // <2, 4, 1, 8>
-    {64, 64, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f},     // <2, 2, 1, 4>
-    {64, 64, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f},      // <2, 2, 1, 8>
-    {32, 64, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f},      // <1, 2, 1, 8>
-    {32, 32, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f},        // <1, 1, 1, 8>
+    {128, 128, 2, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f},  // <2, 4, 2, 2>
+    {64, 128, 8, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f},   // <2, 4, 1, 8>
+    {64, 64, 4, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f},     // <2, 2, 1, 4>
+    {64, 64, 8, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f},      // <2, 2, 1, 8>
+    {32, 64, 8, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f},      // <1, 2, 1, 8>
+    {32, 32, 8, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f},        // <1, 1, 1, 8>
 };
 
 // Shape and slices for plan p.  Cutting the points into slices (as far as the
 // plan has room for their planes) puts a small hologram of many points on more
 // CUs, at one more launch (6 us) and the planes' traffic (at 3 TB/s); a slice
 // has at least 512 points.  (128x96, N = 60000: 410 us in one slice, 36 in 21.)
-int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices, int& slices) {
+// The sums are cut into at least min_parts parts (slices times point groups),
+// which bounds the error of the FP32 additions: it grows as the square root of
+// a part's length (3332x341, N = 60771: 2.97e-6 of the result in 2 parts,
+// 4.3e-7 in 64).
+int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices,
+                 int64_t min_parts, int& slices) {
   int best = 0;
   float best_time = 0.0f;
   slices = 1;
@@ -533,8 +538,10 @@ int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_sli
     const Shape& q = kShapes[k];
     const int64_t tiles = (((int64_t)nx + q.cols - 1) / q.cols) * (((int64_t)ny + q.rows - 1) / q.rows);
     for (int64_t want = 1; want <= max_slices || want == 1; want += want < 4 ? 1 : want / 2) {
-      if (want > 1 && (units < 8 * want || tiles * want > 1024)) break;
       const int64_t per = (units + want - 1) / want, n = (units + per - 1) / per;  // none empty
+      const bool few = n * q.groups < min_parts && n < max_slices && n < units;
+      if (want > 1 && !few && (units < 8 * want || tiles * want > 1024) && best_time > 0.0f) break;
+      if (few) continue;
       const int64_t rounds = (tiles * n + 255) / 256;
       const float per_k = mode == kHalfF16x3 ? (rounds == 1 ? q.split_one : q.split)
                                              : (rounds == 1 ? q.single_one : q.single);
@@ -568,7 +575,7 @@ hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const fl
 
 int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny) {
   int slices;
-  (void)choose_shape(npad, nx, ny, kHalfF16x3, INT64_MAX / 2, slices);
+  (void)choose_shape(npad, nx, ny, kHalfF16x3, INT64_MAX / 2, 1, slices);
   return slices;
 }
 
@@ -612,7 +619,9 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
     room = in_sep;
     c.planes = w.sep_c;
   }
-  c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, c.slices);
+  // The f16x3 variant sums in at least as many parts as its plan's K splits.
+  const int64_t parts = p.variant == 3 ? p.sep_splits : 1;
+  c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices);
   return true;
 }
 
