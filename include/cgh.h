@@ -168,7 +168,11 @@ int cgh_forward_residual(const float* x, const float* y, const float* z, const f
 
 /*
  * Forward, Eq. (1), with FP64 phase arithmetic and FP64 output: the
- * on-device reference used to measure the FP32 variants at full size.
+ * on-device reference used to measure the FP32 variants at full size.  The
+ * phases are formed and reduced per axis and summed by the addition theorem on
+ * the FP64 matrix cores, a chunk of points at a time (the workspace holds a
+ * chunk's tables, at most 128 MiB); where the tables of 64 points would exceed
+ * that (nx + ny above about 130,000), one cosine per interaction.
  *   hologram     device float64[ny][nx], overwritten.
  */
 int cgh_forward_f64(const float* x, const float* y, const float* z, const float* a, int64_t n,

@@ -188,6 +188,12 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.off_xrec = take(np * kAxisRec * sizeof(float));
   p.off_yrec = take(np * kAxisRec * sizeof(float));
   p.off_rec64 = op == CGH_OP_FORWARD_F64 ? take(np * sizeof(double4)) : 0;
+  if (op == CGH_OP_FORWARD_F64) {
+    plan_contract_f64(p);
+    if (p.f64_slices > 0) p.off_tab64 = take(contract_f64_table_bytes(p));
+    if (p.f64_slices > 1)
+      p.off_planes64 = take((size_t)p.f64_slices * (size_t)nx * (size_t)ny * sizeof(double));
+  }
   p.off_ytab = (op == CGH_OP_FORWARD && variant == CGH_COMPENSATED)
                    ? take((size_t)p.groups * np * kCompRows * sizeof(float))
                    : 0;
@@ -256,6 +262,8 @@ Workspace carve(const Plan& p, void* base) {
   w.xrec = (float*)(b + p.off_xrec);
   w.yrec = (float*)(b + p.off_yrec);
   w.rec64 = p.op == CGH_OP_FORWARD_F64 ? (double4*)(b + p.off_rec64) : nullptr;
+  w.tab64 = p.f64_slices > 0 ? (double*)(b + p.off_tab64) : nullptr;
+  w.planes64 = p.f64_slices > 1 ? (double*)(b + p.off_planes64) : nullptr;
   w.ytab = (p.op == CGH_OP_FORWARD && p.variant == CGH_COMPENSATED) ? (float*)(b + p.off_ytab)
                                                                      : nullptr;
   w.xtab = (p.op == CGH_OP_FORWARD && p.variant == CGH_COMPENSATED && p.comp_xtab)
@@ -635,7 +643,14 @@ int cgh_forward_f64(const float* x, const float* y, const float* z, const float*
   rc = check_workspace(p, workspace, workspace_bytes);
   if (rc) return rc;
   const Workspace w = carve(p, workspace);
-  hipError_t e = launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, true, s);
+  hipError_t e;
+  if (p.f64_slices > 0) {
+    const EventPair ev = profile_begin(CGH_KERNEL_FWD_F64, s);
+    e = launch_contract_f64(p, w, x, y, z, a, pitch, wavelength, hologram, s);
+    profile_end(CGH_KERNEL_FWD_F64, ev, s);
+    return hip_status(e);
+  }
+  e = launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, true, s);
   if (e != hipSuccess) return CGH_EHIP;
   const EventPair ev = profile_begin(CGH_KERNEL_FWD_F64, s);
   e = launch_fwd_f64(p, w, hologram, s);

@@ -179,6 +179,8 @@ struct Workspace {
   float* xrec;     // [npad][8]
   float* yrec;     // [npad][8]
   double4* rec64;  // [npad]
+  double* tab64;   // FP64 forward: y then x tables of a chunk of points
+  double* planes64;  // FP64 forward: partial sums [f64_slices][ny][nx]
   float* ytab;     // forward, compensated: [groups][npad][kCompRows]
   float* xtab;     // forward, compensated (optional): [fwd_gx * 64][npad] x-phases
   float* planes;   // forward, compensated (optional): [fwd_planes][ny][nx] partial sums
@@ -205,6 +207,7 @@ struct Plan {
   // forward
   int32_t fwd_gx, fwd_gy, comp_gy, groups;
   bool comp_xtab;  // the compensated forward has its column table
+  int32_t f64_chunk, f64_slices;  // FP64 forward: points per chunk (0 slices: the direct kernel)
   int32_t fwd_planes;  // partial planes of the compensated forward (0: none of its own)
   int32_t rec_k, rec_r, rec_s, rec_gx, rec_gy;  // recurrence forward shape, split, grid
   // adjoint: runs of strip-rows per point group (regions = the most runs the
@@ -218,7 +221,8 @@ struct Plan {
   int64_t k2;
   size_t off_sep_x, off_sep_y, off_sep_c, off_sep_g, off_fold_x, off_fold_y;
   size_t off_hx, off_hy, off_hmax;  // half variants
-  size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_rtab,
+  size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_tab64,
+      off_planes64, off_rtab,
       off_ctab, off_partial, off_gpad, total;
 };
 

@@ -162,6 +162,17 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
 hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
                                const float* target, float* residual, hipStream_t s);
 
+// -------------------------------------------------------------- FP64 forward --
+// Bytes of tables that a chunk of points may take (16 a point and coordinate):
+// large enough that a chunk's launches and its pass over the hologram are small
+// beside its products (3840x2160: 1344 points a chunk, about 0.6 ms).
+constexpr int64_t kF64TableBytes = int64_t(128) << 20;
+void plan_contract_f64(Plan& p);  // sets f64_chunk and f64_slices
+size_t contract_f64_table_bytes(const Plan& p);
+hipError_t launch_contract_f64(const Plan& p, const Workspace& w, const float* x, const float* y,
+                               const float* z, const float* a, double pitch, double wavelength,
+                               double* out, hipStream_t s);
+
 // ----------------------------------------------------------------- adjoint --
 // Tables of the adjoint, a quad of coordinates at a time (lane = point):
 //   f16x3        float [ceil(size / 4)][npad][4]   the axis phase

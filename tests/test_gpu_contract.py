@@ -169,3 +169,39 @@ def test_adjoint_gradient_of_any_scale(oracle_mod, scale):
     e = rel_l2(ga.astype(np.float64) / scale, ref / scale)
     say("gradient scale", scale, "rel-L2 =", e)
     assert np.all(np.isfinite(ga)) and e <= f16x3_bar(nx, ny, nx / 2, 0)
+
+
+# Tiles of 64 pixels and their remainders; the points in slices (128x96) and in
+# chunks whose tables fit (3840x2160, two chunks).
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 65, 64), (333, 197, 700), (128, 96, 3001),
+                                   (3840, 2160, 1400)])
+def test_f64_shapes(oracle_mod, shape):
+    """A phase is at most about 2600 revolutions here, so its FP64 rounding is
+    below 2 pi 2600 2^-52 = 3.6e-12 of a term; the sum adds less."""
+    nx, ny, n = shape
+    dev = device()
+    say("f64", shape)
+    c = W.random_cloud(1400 + n, n, nx, ny, zlo=ZLO, zhi=1.0, alo=-1.0, ahi=1.0)
+    I = B.forward_f64(*to_dev(c, dev), nx, ny)
+    assert torch.equal(I, B.forward_f64(*to_dev(c, dev), nx, ny))
+    px, py = W.sample_pixels(1401, nx, ny, 2000)
+    ref = oracle_mod.forward_at(*c.astuple(), nx, ny, px, py, threads=0)
+    err = max_err_frac(I.cpu().numpy()[py, px], ref, c)
+    say("  max|dI|/sum|A| = %.3e" % err)
+    assert err <= 1e-11
+
+
+def test_f64_non_finite_amplitudes():
+    dev = device()
+    nx, ny = 70, 50
+    c = W.random_cloud(1402, 20, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
+    x, y, z, a = to_dev(c, dev)
+    a[3] = float("-inf")
+    I = B.forward_f64(x, y, z, a, nx, ny).cpu().numpy()
+    h, v = np.meshgrid(np.arange(nx), np.arange(ny))
+    P = np.pi * W.PITCH ** 2 / (W.WAVELENGTH * float(c.z[3]))
+    cos = np.cos(P * ((h - float(c.x[3])) ** 2 + (v - float(c.y[3])) ** 2))
+    clear = np.abs(cos) > 1e-6
+    assert np.array_equal(I[clear], np.where(cos > 0, -np.inf, np.inf)[clear])
+    a[3] = float("nan")
+    assert torch.isnan(B.forward_f64(x, y, z, a, nx, ny)).all()
