@@ -235,14 +235,12 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   const size_t nxp = (size_t)p.nxp, nyp = (size_t)p.nyp;
   p.off_sep_x = f32 ? take(nxp * k2 * sizeof(float)) : 0;
   p.off_sep_y = f32 ? take(nyp * k2 * sizeof(float)) : 0;
-  p.off_sep_g = (f32 && bwd) ? take(nyp * nxp * sizeof(float)) : 0;
   p.off_sep_c = (sep && fwd && p.sep_splits > 1)
                     ? take((size_t)p.sep_splits * nyp * nxp * sizeof(float))
                     : 0;
-  p.off_fold_x =
-      (sep && bwd) ? take((size_t)p.sep_splits_u * (nxp / 128) * np * sizeof(float4)) : 0;
-  p.off_fold_y =
-      (sep && bwd) ? take((size_t)p.sep_splits_p * (nyp / 128) * np * sizeof(float4)) : 0;
+  p.off_fold = (sep && bwd) ? take(((size_t)p.sep_splits_u * (nxp / 128) +
+                                    (size_t)p.sep_splits_p * (nyp / 128)) * np * sizeof(float4))
+                            : 0;
   // The contraction's tables hold 4 bytes a point and coordinate; the f16x3 ones
   // take the room of two 16-bit planes of cosines and sines, so that the problems
   // the static scratch holds do not depend on how a table is laid out.
@@ -281,10 +279,8 @@ Workspace carve(const Plan& p, void* base) {
   const bool fwd = p.op == CGH_OP_FORWARD, bwd = p.op == CGH_OP_BACKWARD;
   w.sep_x = f32 ? (float*)(b + p.off_sep_x) : nullptr;
   w.sep_y = f32 ? (float*)(b + p.off_sep_y) : nullptr;
-  w.sep_g = (f32 && bwd) ? (float*)(b + p.off_sep_g) : nullptr;
   w.sep_c = (sep && fwd && p.sep_splits > 1) ? (float*)(b + p.off_sep_c) : nullptr;
-  w.fold_x = (sep && bwd) ? (float4*)(b + p.off_fold_x) : nullptr;
-  w.fold_y = (sep && bwd) ? (float4*)(b + p.off_fold_y) : nullptr;
+  w.fold = (sep && bwd) ? (float4*)(b + p.off_fold) : nullptr;
   if (hm >= 0) {
     w.htab_x = b + p.off_hx;
     w.htab_y = b + p.off_hy;
@@ -379,56 +375,7 @@ inline int hip_status(hipError_t e) { return e == hipSuccess ? CGH_OK : CGH_EHIP
 
 }  // namespace
 
-// ------------------------------------------------------------- separable --
-
-// I = P Q^T with P = (A cY, -A sY) [nyp][k2], Q = (cX, sX) [nxp][k2].
-int forward_separable(const Plan& p, const Workspace& w, float* hologram, hipStream_t s,
-                      bool timed) {
-  hipError_t e =
-      launch_sep_tables(w.xrec, w.yrec, w.amp, p.npad, p.nx, p.nxp, p.ny, p.nyp, w.sep_x, w.sep_y, s);
-  if (e != hipSuccess) return CGH_EHIP;
-  const EventPair ev = profile_begin(CGH_KERNEL_FWD_SEPARABLE, s, timed);
-  if (p.sep_splits == 1) {
-    e = launch_gemm_f32(true, true, w.sep_y, p.k2, w.sep_x, p.k2, hologram, p.nx, 0, p.nyp,
-                        p.nxp, (int)p.k2, 1, p.ny, p.nx, nullptr, s);
-  } else {
-    const int64_t plane = (int64_t)p.nyp * p.nxp;
-    e = launch_gemm_f32(true, true, w.sep_y, p.k2, w.sep_x, p.k2, w.sep_c, p.nxp, plane, p.nyp,
-                        p.nxp, (int)p.k2, p.sep_splits, p.nyp, p.nxp, nullptr, s);
-  }
-  profile_end(CGH_KERNEL_FWD_SEPARABLE, ev, s);
-  if (e != hipSuccess) return CGH_EHIP;
-  if (p.sep_splits > 1)
-    e = launch_sep_sum_slices(w.sep_c, p.sep_splits, (int64_t)p.nyp * p.nxp, p.nxp, p.nx, p.ny,
-                              hologram, s);
-  return hip_status(e);
-}
-
-// U = Y^T G (Y = (cY, sY) [nyp][k2]), Pm = X^T G^T (X = (cX, sX) [nxp][k2]),
-// each folded per point in its GEMM epilogue, then the per-point sums.
-int backward_separable(const Plan& p, const Workspace& w, const float* z, const float* a,
-                       double pitch, double wavelength, const float* g, float* gx, float* gy,
-                       float* gz, float* ga, hipStream_t s) {
-  hipError_t e = launch_sep_tables(w.xrec, w.yrec, nullptr, p.npad, p.nx, p.nxp, p.ny, p.nyp,
-                                   w.sep_x, w.sep_y, s);
-  if (e == hipSuccess) e = launch_sep_pad(g, p.nx, p.ny, p.nyp, p.nxp, w.sep_g, s);
-  if (e != hipSuccess) return CGH_EHIP;
-  const FoldSpec fx{1, w.xrec, w.plain, p.nx, w.fold_x};
-  const FoldSpec fy{2, w.yrec, w.plain, p.ny, w.fold_y};
-  const EventPair ev = profile_begin(CGH_KERNEL_ADJ_SEPARABLE, s);
-  // U[k][x] = sum_y Y[y][k] G[y][x]: A = Y stored [y][k], B = G stored [y][x];
-  // folded in the epilogue.
-  e = launch_gemm_f32(false, false, w.sep_y, p.k2, w.sep_g, p.nxp, nullptr, 0, 0, (int)p.k2,
-                      p.nxp, p.nyp, p.sep_splits_u, (int)p.k2, p.nxp, &fx, s);
-  // Pm[k][y] = sum_x X[x][k] G[y][x]: A = X stored [x][k], B = G stored [y][x].
-  if (e == hipSuccess)
-    e = launch_gemm_f32(false, true, w.sep_x, p.k2, w.sep_g, p.nxp, nullptr, 0, 0, (int)p.k2,
-                        p.nyp, p.nxp, p.sep_splits_p, (int)p.k2, p.nyp, &fy, s);
-  profile_end(CGH_KERNEL_ADJ_SEPARABLE, ev, s);
-  if (e != hipSuccess) return CGH_EHIP;
-  e = launch_sep_finalize(p, w, z, a, pitch, wavelength, gx, gy, gz, ga, s);
-  return hip_status(e);
-}
+// ------------------------------------------------------------ contraction --
 
 // The forward as one contraction with its operands formed in the kernel
 // (contract_fwd.hip), with the residual in its store.
@@ -591,7 +538,7 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
   const int32_t variant = p.variant;
   const int64_t n = p.n;
   const Workspace w = carve(p, workspace);
-  if (variant == CGH_COMPENSATED || half_mode(variant) >= 0) {
+  if (variant == CGH_COMPENSATED || is_separable(variant)) {
     ContractFwd c;
     if (plan_contract_fwd(p, w, c))
       return forward_contract(p, c,
@@ -608,8 +555,6 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
     if (rc != CGH_OK || !residual) return rc;
     return hip_status(launch_residual(hologram, target, residual, (int64_t)p.nx * p.ny, s));
   };
-  if (variant == CGH_SEPARABLE)
-    return separate_residual(forward_separable(p, w, hologram, s, timed));
   if (variant == CGH_COMPENSATED) {
     const EventPair ev = profile_begin(CGH_KERNEL_FWD_COMPENSATED, s, timed);
     e = launch_fwd_comp(p, w, hologram, s, target, residual);
@@ -674,7 +619,7 @@ int cgh_backward(const float* x, const float* y, const float* z, const float* a,
   if (rc) return rc;
   const Workspace w = carve(p, workspace);
   hipError_t e;
-  if (variant == CGH_COMPENSATED || half_mode(variant) >= 0) {
+  if (variant == CGH_COMPENSATED || is_separable(variant)) {
     ContractAdj c;
     if (plan_contract_adj(p, w, c))
       return backward_contract(p, w, c,
@@ -683,12 +628,6 @@ int cgh_backward(const float* x, const float* y, const float* z, const float* a,
                                x, y, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
                                grad_z, grad_a, s);
     if (variant != CGH_COMPENSATED) return CGH_EHIP;  // its plan always holds the planes
-  }
-  if (variant == CGH_SEPARABLE) {
-    e = launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, false, s);
-    if (e != hipSuccess) return CGH_EHIP;
-    return backward_separable(p, w, z, a, pitch, wavelength, grad_hologram, grad_x, grad_y,
-                              grad_z, grad_a, s);
   }
   // The direct adjoint forms each point's records itself (one point per
   // lane); the compensated one takes its row phases from a table built here.

@@ -136,11 +136,8 @@ constexpr int kAdjThreads = kWave;
 constexpr int kAdjRounds = CGH_ADJ_ROUNDS;
 constexpr int kAdjMaxWaves = kAdjRounds * 256 * 4 * 8;
 constexpr int kAdjMinRun = 8;
-// Second passes: kFinSlices threads per point add interleaved subsets of the
-// partial planes (the separable finalize), and the direct adjoint's finalize
-// spreads its many run partials over kAdjFinSlices threads for each of
-// kAdjFinPoints points per workgroup.
-constexpr int kFinSlices = 16;
+// The adjoint's finalize spreads its partial planes over kAdjFinSlices threads
+// for each of kAdjFinPoints points per workgroup.
 constexpr int kAdjFinPoints = 16;
 constexpr int kAdjFinSlices = 64;
 
@@ -188,13 +185,11 @@ struct Workspace {
   float* ctab;     // adjoint, compensated: [nsx * kAdjCols][npad] x-phases
   float* partial;  // adjoint: [regions][npad][4]
   float* gpad;     // adjoint: G copied to a [ny][nsx*kAdjCols] zero-padded grid
-  // separable variant (tables of k2 = 2 * npad floats per row / column)
-  float* sep_x;    // [nxp][k2]  (cX, sX) per point
-  float* sep_y;    // [nyp][k2]  forward: (A cY, -A sY); adjoint: (cY, sY)
-  float* sep_c;    // forward split-K planes [splits][nyp][nxp]
-  float* sep_g;    // adjoint: G zero-padded to [nyp][nxp]
-  float4* fold_x;  // adjoint: x-part fold planes [splits_u][nxp / 128][npad]
-  float4* fold_y;  // adjoint: y-part fold planes [splits_p][nyp / 128][npad]
+  // separable variants
+  float* sep_x;    // FP32: the contraction's x and y tables
+  float* sep_y;
+  float* sep_c;    // forward: partial planes [sep_splits][nyp][nxp]
+  float4* fold;    // adjoint: partial sums [planes][npad]
   // half-precision separable variants: the contraction's tables and max |A|
   void *htab_x, *htab_y;
   unsigned* hmax;  // [kWave] maxima of |A|, as float bits
@@ -219,7 +214,7 @@ struct Plan {
   // separable variant
   int32_t nxp, nyp, sep_splits, sep_splits_u, sep_splits_p;
   int64_t k2;
-  size_t off_sep_x, off_sep_y, off_sep_c, off_sep_g, off_fold_x, off_fold_y;
+  size_t off_sep_x, off_sep_y, off_sep_c, off_fold;
   size_t off_hx, off_hy, off_hmax;  // half variants
   size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_tab64,
       off_planes64, off_rtab,
@@ -262,47 +257,11 @@ hipError_t launch_residual(const float* hologram, const float* target, float* re
 hipError_t launch_fwd_rec(const Plan& p, const Workspace& w, float* out, hipStream_t s);
 hipError_t launch_fwd_f64(const Plan& p, const Workspace& w, double* out, hipStream_t s);
 hipError_t launch_pad_g(const Plan& p, const float* g, float* gpad, hipStream_t s);
-// Optional epilogue of the adjoint GEMMs (fold.h): instead of storing its
-// tile, each block folds it into per-point sums, written as float4 planes
-// out[(z * (N / 128) + column tile) * (M / 2) + point] for K slice z.
-struct FoldSpec {
-  int part;             // 1: x part (U), 2: y part (Pm)
-  const float* rec;     // axis records of the folded axis (xrec or yrec)
-  const float4* plain;  // point records {x, y, Prev, A}
-  int n_valid;          // nx or ny
-  float4* out;
-};
-// FP32 matrix-core GEMM (gemm.hip): C[m][n] = sum_k A(m, k) B(n, k), split
-// over `splits` K slices written to C + z * slice_stride (or folded, when
-// fold is given: then A must be M-contiguous, as in the adjoint).  M, N
-// multiples of 128; K a multiple of 32; slices of ceil(K / 32 / splits)
-// chunks of 32, the last one shorter and never empty (else an error).
-hipError_t launch_gemm_f32(bool a_kcontig, bool b_kcontig, const float* A, int64_t lda,
-                           const float* B, int64_t ldb, float* C, int64_t ldc,
-                           int64_t slice_stride, int M, int N, int K, int splits, int m_valid,
-                           int n_valid, const FoldSpec* fold, hipStream_t s);
-// Separable variant (separable.hip).
-// Grid of the per-axis table kernels: x over points (256 per workgroup), y a
-// few workgroup rows that stride over the table rows.
-dim3 table_grid(int64_t npad, int rows);
-// Both axis tables (x: (cX, sX) [nxp][k2]; y: (A cY, -A sY) with amp, else
-// (cY, sY), [nyp][k2]) in one launch.
-hipError_t launch_sep_tables(const float* xrec, const float* yrec, const float* amp, int64_t npad,
-                             int nx, int nxp, int ny, int nyp, float* tab_x, float* tab_y,
-                             hipStream_t s);
-hipError_t launch_sep_sum_slices(const float* C, int splits, int64_t slice_stride, int64_t ldc,
-                                 int nx, int ny, float* out, hipStream_t s);
-hipError_t launch_sep_pad(const float* g, int nx, int ny, int rows_pad, int cols_pad, float* gp,
-                          hipStream_t s);
-// Sums the fold planes of both adjoint GEMMs per point in a fixed order
-// (FP64) and scales them into the gradients.
-hipError_t launch_sep_finalize(const Plan& p, const Workspace& w, const float* z, const float* a,
-                               double pitch, double wavelength, float* gx, float* gy, float* gz,
-                               float* ga, hipStream_t s);
-// Formats of the 16-bit matrix-core operands (contract.h):
+// Operand formats of the matrix-core contractions (contract.h):
 constexpr int kHalfF16 = 0;    // one fp16 plane per operand
 constexpr int kHalfBF16 = 1;   // one bf16 plane per operand
 constexpr int kHalfF16x3 = 2;  // fp16 hi + lo planes, hi*hi + hi*lo + lo*hi
+constexpr int kF32 = 3;        // FP32
 
 // Runs per point group for this launch (<= p.regions), from the occupancy of
 // the adjoint kernel on the current device.

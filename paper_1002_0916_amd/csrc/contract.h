@@ -1,4 +1,4 @@
-// The hologram sum and its adjoint as contractions on the 16-bit matrix cores,
+// The hologram sum and its adjoint as contractions on the matrix cores,
 // with the operands formed inside the kernels (contract_fwd.hip,
 // contract_adj.hip).
 //
@@ -12,6 +12,7 @@
 //               hi*hi + hi*lo + lo*hi: the two planes hold 22 to 24 bits of v
 //               and what is dropped, lo*lo, is below 2^-22 of the product.
 //   kHalfF16, kHalfBF16   v rounded once to 16 bits, one product.
+//   kF32        v itself, on the FP32 matrix cores.
 //
 // Cosines and sines lie in [-1, 1].  The other operand's values (A_j forward, G
 // in the adjoint) are multiplied by a power of two first (exact), which puts the
@@ -21,6 +22,8 @@
 #pragma once
 
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "cgh_internal.h"
 #include "phase.h"
@@ -34,7 +37,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // One lane's share of a 32 x 16 operand block of v_mfma_f32_32x32x16: row (or
-// column) lane % 32, k = (lane / 32) * 8 .. + 7, two 16-bit values a dword.
+// column) lane % 32, k = (lane / 32) * 8 .. + 7, two 16-bit values a dword (kF32:
+// the eight values themselves).
 struct Frag {
   uint4 hi, lo;
 };
@@ -47,6 +51,28 @@ __device__ __forceinline__ floatx16 mfma16(uint4 a, uint4 b, floatx16 c) {
   else
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, a),
                                                   __builtin_bit_cast(halfx8, b), c, 0, 0, 0);
+}
+
+// acc += A B over one step (k = 16): the planes' products, or for kF32 eight
+// v_mfma_f32_32x32x2, the t-th with every lane's t-th value (its k is then (lane
+// / 32) * 8 + t on both sides).
+template <class F, int... K>
+__device__ __forceinline__ void parts(F&& f, std::integer_sequence<int, K...>) {
+  (f(std::integral_constant<int, K>{}), ...);  // for each k of the sequence
+}
+constexpr int mfmas_per_step(int mode) {
+  return mode == kF32 ? 8 : mode == kHalfF16x3 ? 3 : 1;
+}
+template <int MODE, int K>
+__device__ __forceinline__ floatx16 mfma_part(const Frag& a, const Frag& b, floatx16 c) {
+  if constexpr (MODE == kF32) {
+    const uint32_t va[8] = {a.hi.x, a.hi.y, a.hi.z, a.hi.w, a.lo.x, a.lo.y, a.lo.z, a.lo.w};
+    const uint32_t vb[8] = {b.hi.x, b.hi.y, b.hi.z, b.hi.w, b.lo.x, b.lo.y, b.lo.z, b.lo.w};
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(va[K]), __uint_as_float(vb[K]), c,
+                                                0, 0, 0);
+  } else {
+    return mfma16<MODE>(K == 2 ? a.lo : a.hi, K == 1 ? b.lo : b.hi, c);
+  }
 }
 
 // Two values rounded to the 16-bit format (to nearest even), v0 in the low half.
@@ -80,7 +106,12 @@ __device__ __forceinline__ void split16(float v0, float v1, uint32_t& hi, uint32
 template <int MODE>
 __device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
   Frag f;
-  if constexpr (MODE == kHalfF16x3) {
+  if constexpr (MODE == kF32) {
+    f.hi = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
+                      __float_as_uint(v[3]));
+    f.lo = make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]),
+                      __float_as_uint(v[7]));
+  } else if constexpr (MODE == kHalfF16x3) {
     split16(v[0], v[1], f.hi.x, f.lo.x);
     split16(v[2], v[3], f.hi.y, f.lo.y);
     split16(v[4], v[5], f.hi.z, f.lo.z);
@@ -130,6 +161,8 @@ __device__ __forceinline__ unsigned group_max(unsigned v, unsigned* lds) {
 // points of one coordinate are one 16-byte load and 32 lanes of consecutive
 // coordinates read 512 consecutive bytes:
 //   f16x3        float [npad / 4][rows][4]   the axis phase
+//   f32          two planes float [npad / 4][rows][4]: (cos, sin) of the quad's
+//                first two points, of its other two
 //   f16, bf16    uint32 [npad / 4][rows][4]  (cos, sin) as two 16-bit values
 // y rows (with A_j and the scale in the 16-bit values), then x columns.
 struct FwdOperands {
@@ -141,7 +174,7 @@ struct FwdOperands {
 };
 
 struct ContractFwd {
-  int mode;           // kHalfF16x3, kHalfF16, kHalfBF16
+  int mode;           // the operand format
   int shape;          // index of the kernel's tile shape
   int rows_y, cols_x;
   bool xtab;
@@ -175,8 +208,8 @@ hipError_t launch_contract_f64(const Plan& p, const Workspace& w, const float* x
 
 // ----------------------------------------------------------------- adjoint --
 // Tables of the adjoint, a quad of coordinates at a time (lane = point):
-//   f16x3        float [ceil(size / 4)][npad][4]   the axis phase
-//   f16, bf16    two planes uint32 [ceil(size / 4)][npad][2]: cosines, sines
+//   f16x3, f32   float [ceil(size / 4)][npad][4]   the axis phase
+//   f16, bf16    two planes uint32 [ceil(size / 8)][npad][4]: cosines, sines
 struct ContractAdj {
   int mode;
   bool tab;           // the tables exist (else the kernel forms the phases)

@@ -1,4 +1,4 @@
-// Adjoint of Eq. (1) (Section 1) as two contractions on the 16-bit matrix cores
+// Adjoint of Eq. (1) (Section 1) as two contractions on the matrix cores
 // (contract.h), with their operands formed in the kernel and their results
 // folded there:
 //
@@ -26,6 +26,11 @@
 // split and left in LDS by all four waves, 32 v by 128 u per stage, double
 // buffered; slot s of a 1 KB block holds lane s ^ (4 * octet) of each half, so
 // that neither the reads nor the writes of either part meet a bank twice.
+//
+// FP32 (8 flops per interaction on the FP32 matrix cores, which bound it) reads
+// the same tables of phases; its G goes through LDS as it is.  1024x1024, N =
+// 4096: 310 us a call where two tiled products of operand tables with a fold took
+// 358.
 #include "contract.h"
 #include "records.h"
 
@@ -56,12 +61,15 @@ struct AdjArgs {
   int tiles_p, groups_p, slices_p, per_p, st_p;  //   tiles per group, stages per slice
 };
 
+// The operands are formed from phases (two uint4 a share); else they are read.
+constexpr bool forms_operands(int mode) { return mode == kHalfF16x3 || mode == kF32; }
+
 // One part (PY: the y part) of one workgroup: point block pb, plane `plane`.
 template <int MODE, bool TAB, bool PY>
 __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, uint4* lds,
                                          unsigned* red) {
-  constexpr bool kSplit = MODE == kHalfF16x3;
-  constexpr int kPlanes = kSplit ? 2 : 1;
+  constexpr bool kForms = forms_operands(MODE);
+  constexpr int kPlanes = kForms ? 2 : 1;
   constexpr int kBlocks = kAdjTile / 32;
   constexpr int kBuf = 2 * kBlocks * kPlanes * kWave;  // uint4 per buffer
   const int lane = threadIdx.x & (kWave - 1);
@@ -89,10 +97,12 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
 
   // Scale of G from the largest block maximum.
   unsigned m = 0;
-  for (int k = threadIdx.x; k < p.gblocks; k += kAdjCThreads) m = max(m, p.gmax[k]);
-  m = group_max<kAdjCThreads>(m, red);
-  float mul, undo;
-  operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
+  if (MODE != kF32) {
+    for (int k = threadIdx.x; k < p.gblocks; k += kAdjCThreads) m = max(m, p.gmax[k]);
+    m = group_max<kAdjCThreads>(m, red);
+  }
+  float mul = 1.0f, undo = 1.0f;
+  if (MODE != kF32) operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
 
   double d0 = 0.0, d1 = 0.0, d2 = 0.0;  // {Sc, Sx or Sy, Sr} of the blocks so far
 
@@ -103,7 +113,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
     uint4 q0, q1;
   };
   auto load_t = [&](int t, Phases& ph) {
-    if constexpr (TAB && kSplit) {
+    if constexpr (TAB && kForms) {
       const int q = 4 * t + 2 * half;
       const char* base = vt + (int64_t)jc * 16;
       ph.q0 = *reinterpret_cast<const uint4*>(base + (int64_t)min(q, vquads - 1) * p.npad * 16);
@@ -116,7 +126,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
     }
   };
   auto form_t = [&](int t, const Phases& ph, Frag& C, Frag& S) {
-    if constexpr (kSplit) {
+    if constexpr (kForms) {
       float v[8];
       if constexpr (TAB) {
         const float4 a = __builtin_bit_cast(float4, ph.q0), b = __builtin_bit_cast(float4, ph.q1);
@@ -154,7 +164,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
     // G: item k of a thread is eight v of one u.  In the x part a wave reads 64
     // consecutive u of a row, so the row is uniform and its address scalar; in
     // the y part four threads read the 32 v of one row.  Addresses are clamped
-    // to the hologram, and what lies outside is multiplied by zero.
+    // to the hologram, and what lies outside becomes zero.
     float gv[2][8];
     const int g_oct = PY ? (int)(threadIdx.x & 3) : wave >> 1;
     const int g_u = PY ? (int)(threadIdx.x >> 2) : (wave & 1) * kWave + lane;
@@ -192,19 +202,26 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
       const int vv = s * kAdjStage + 8 * oct;
       float v[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = gv[k][e] * (vv + e < nv ? mul_u[k] : 0.0f);
+      for (int e = 0; e < 8; ++e) {
+        // (FP32 has no scale, and a select keeps an infinity or NaN at the edge
+        // out of the padding)
+        if constexpr (MODE == kF32)
+          v[e] = mul_u[k] != 0.0f && vv + e < nv ? gv[k][e] : 0.0f;
+        else
+          v[e] = gv[k][e] * (vv + e < nv ? mul_u[k] : 0.0f);
+      }
       const Frag f = make_frag<MODE>(v);
       uint4* d = lds + (s & 1) * kBuf + ((oct >> 1) * kBlocks + (u >> 5)) * kPlanes * kWave +
                  (oct & 1) * 32 + ((u & 31) ^ (oct * 4));
       d[0] = f.hi;
-      if (kSplit) d[kWave] = f.lo;
+      if (kForms) d[kWave] = f.lo;
     };
     auto read_g = [&](int s, int step, int b) -> Frag {
       const uint4* q = lds + (s & 1) * kBuf + (step * kBlocks + b) * kPlanes * kWave + half * 32 +
                        (l32 ^ ((step * 2 + half) * 4));
       Frag f;
       f.hi = q[0];
-      f.lo = kSplit ? q[kWave] : f.hi;
+      f.lo = kForms ? q[kWave] : f.hi;
       return f;
     };
 
@@ -232,12 +249,20 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
         for (int b = 0; b < kBlocks; ++b) {
           const int nb = step * kBlocks + b + 1;
           const Frag next = nb < 2 * kBlocks ? read_g(s, nb / kBlocks, nb % kBlocks) : A;
+          if constexpr (MODE == kF32) {
+            auto part = [&](auto k) {
+              acc[b][0] = mfma_part<MODE, decltype(k)::value>(A, C[step], acc[b][0]);
+              acc[b][1] = mfma_part<MODE, decltype(k)::value>(A, S[step], acc[b][1]);
+            };
+            parts(part, std::make_integer_sequence<int, mfmas_per_step(MODE)>{});
+          } else {
 #pragma unroll
-          for (int k = 0; k < (kSplit ? 3 : 1); ++k) {
-            acc[b][0] = mfma16<MODE>(k == 2 ? A.lo : A.hi, k == 1 ? C[step].lo : C[step].hi,
-                                     acc[b][0]);
-            acc[b][1] = mfma16<MODE>(k == 2 ? A.lo : A.hi, k == 1 ? S[step].lo : S[step].hi,
-                                     acc[b][1]);
+            for (int k = 0; k < mfmas_per_step(MODE); ++k) {
+              acc[b][0] = mfma16<MODE>(k == 2 ? A.lo : A.hi, k == 1 ? C[step].lo : C[step].hi,
+                                       acc[b][0]);
+              acc[b][1] = mfma16<MODE>(k == 2 ? A.lo : A.hi, k == 1 ? S[step].lo : S[step].hi,
+                                       acc[b][1]);
+            }
           }
           A = next;
         }
@@ -263,7 +288,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
         float s0 = 0.f, s1 = 0.f, s2 = 0.f;
         const int ub0 = u0 + 32 * b + 8 * q + 4 * half;
         float f[4];
-        if constexpr (TAB && kSplit) {
+        if constexpr (TAB && kForms) {
           const float4 t = *reinterpret_cast<const float4*>(
               ut + ((int64_t)min(ub0 / 4, uquads - 1) * p.npad + jc) * 16);
           f[0] = t.x; f[1] = t.y; f[2] = t.z; f[3] = t.w;
@@ -298,7 +323,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
   // An infinite or NaN G has no scale: such a call sums term by term (in the
   // x part's workgroups; the y part's planes are zero), so that its infinities
   // and NaNs are the direct sum's.
-  if (!finite_bits(m) && kSplit) {
+  if (MODE == kHalfF16x3 && !finite_bits(m)) {
     s0 = s1 = s2 = 0.0f;
     float sy = 0.0f;
     if (!PY) {
@@ -330,7 +355,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
 
 template <int MODE, bool TAB>
 __global__ __launch_bounds__(kAdjCThreads, 2) void contract_adj_kernel(AdjArgs p) {
-  constexpr int kPlanes = MODE == kHalfF16x3 ? 2 : 1;
+  constexpr int kPlanes = forms_operands(MODE) ? 2 : 1;
   __shared__ uint4 lds[2 * 2 * (kAdjTile / 32) * kPlanes * kWave];
   __shared__ unsigned red[kAdjCThreads / kWave];
   // Bands of kBandPts point blocks, each walked plane by plane: the workgroups
@@ -404,7 +429,7 @@ __global__ __launch_bounds__(256) void contract_adj_tables_kernel(
   const float c = is_y ? r.yc : r.xc, pb = is_y ? r.yb : r.xb, d = is_y ? r.yd : r.xd;
   uint4* dst = is_y ? yq : xq;
   auto phase = [&](int h) { return axis_phase((float)h, c, r.ph, r.pl, pb, d); };
-  if constexpr (MODE == kHalfF16x3) {
+  if constexpr (MODE == kHalfF16x3 || MODE == kF32) {
     const int quads = (size + 3) / 4;
     for (int q = h0 / 4; q < min((h0 + kTabCoords) / 4, quads); ++q)
       dst[(int64_t)q * npad + j] =
@@ -449,57 +474,63 @@ bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c) {
     c.partial = (float4*)w.partial;
     capacity = p.regions;
   } else {
-    c.mode = p.variant == 3 ? kHalfF16x3 : p.variant == 4 ? kHalfF16 : kHalfBF16;
-    c.yq = w.htab_y;
-    c.xq = w.htab_x;
+    c.mode = p.variant == 2 ? kF32 : p.variant == 3 ? kHalfF16x3 : p.variant == 4 ? kHalfF16 : kHalfBF16;
+    c.yq = p.variant == 2 ? w.sep_y : w.htab_y;
+    c.xq = p.variant == 2 ? w.sep_x : w.htab_x;
     c.tab = true;
-    c.partial = w.fold_x;
+    c.partial = w.fold;
     capacity = (int64_t)p.sep_splits_u * (p.nxp / 128) + (int64_t)p.sep_splits_p * (p.nyp / 128);
   }
   c.gmax = (unsigned*)w.plain;
-  c.gblocks = (int)std::min<int64_t>(512, ceil_div((int64_t)p.nx * p.ny, 256 * 8));
+  // (the FP32 operands take no scale)
+  c.gblocks = c.mode == kF32 ? 0 : (int)std::min<int64_t>(512, ceil_div((int64_t)p.nx * p.ny, 256 * 8));
   // Tiles per workgroup and slices of v.  A workgroup takes, in units of one
   // stage, kStart to begin with and for each of its tiles the slice's stages and
-  // kFold for the fold; 512 run at once, two a CU, and one alone on its CU takes
-  // 0.7 of that.  For every length t a workgroup may take, each part gets as few
+  // fold for the fold; 512 run at once, two a CU, and one alone on its CU takes
+  // `alone` of that.  For every length t a workgroup may take, each part gets as few
   // workgroups as keep within it, and the plan with the least time is taken:
   // one workgroup's where all run at once, else the work over the slots and
-  // half a workgroup's tail.  Workgroups beyond kLongest stages drift apart and
+  // part of a workgroup's tail.  Workgroups beyond kLongest stages drift apart and
   // lose each other's G and tables in L2 (3840x2160, N = 16384: 3.14 to 3.2 ms
   // with 75 to 342 stages, 3.5 with 1139), so they are not made longer than a
   // tile needs.  At 46 random sizes the choice is within 1% of the best on
-  // average, 16% at most.
-  constexpr int64_t kSlots = 512, kFold = 6, kStart = 1, kLongest = 350;
+  // average, 16% at most.  In FP32 a stage takes 2.6 times as long on the matrix
+  // cores, so the fold counts for less and a workgroup alone on its CU gains
+  // more (the terms below: within 1% on average, 7% at most, over 34 sizes;
+  // 1449x1371, N = 1730: 333 us where the f16x3 terms' plan took 401).
+  constexpr int64_t kSlots = 512, kStart = 1, kLongest = 350;
+  const int64_t fold = c.mode == kF32 ? 1 : 6;
+  const double alone = c.mode == kF32 ? 0.55 : 0.7, tail = c.mode == kF32 ? 0.35 : 0.5;
   const int64_t npb = ceil_div(p.npad, kAdjTile);
   const int64_t tiles[2] = {ceil_div(p.nx, kAdjTile), ceil_div(p.ny, kAdjTile)};
   const int64_t stages[2] = {ceil_div(p.ny, kAdjStage), ceil_div(p.nx, kAdjStage)};
   double best = -1.0;
-  const int64_t all = kStart + std::max(tiles[0] * (stages[0] + kFold), tiles[1] * (stages[1] + kFold));
-  const int64_t one_tile = kStart + kFold + std::max(stages[0], stages[1]);
-  for (int64_t t = kStart + kFold + 2;; t = t + 1 + t / 16) {
+  const int64_t all = kStart + std::max(tiles[0] * (stages[0] + fold), tiles[1] * (stages[1] + fold));
+  const int64_t one_tile = kStart + fold + std::max(stages[0], stages[1]);
+  for (int64_t t = kStart + fold + 2;; t = t + 1 + t / 16) {
     if (t > all) t = all;
     int64_t groups[2], slices[2], wgs = 0, work = 0, longest = 0;
     for (int k = 0; k < 2; ++k) {
-      const int64_t one = stages[k] + kFold, room = t - kStart;
+      const int64_t one = stages[k] + fold, room = t - kStart;
       if (room >= one) {
         groups[k] = ceil_div(tiles[k], room / one);
         slices[k] = 1;
       } else {
         groups[k] = tiles[k];
-        slices[k] = ceil_div(stages[k], room - kFold);
+        slices[k] = ceil_div(stages[k], room - fold);
         slices[k] = ceil_div(stages[k], ceil_div(stages[k], slices[k]));  // none empty
       }
       wgs += groups[k] * slices[k];
-      work += groups[k] * slices[k] * kStart + tiles[k] * (stages[k] + kFold * slices[k]);
+      work += groups[k] * slices[k] * kStart + tiles[k] * (stages[k] + fold * slices[k]);
       longest = std::max(longest, kStart + ceil_div(tiles[k], groups[k]) *
-                                               (ceil_div(stages[k], slices[k]) + kFold));
+                                               (ceil_div(stages[k], slices[k]) + fold));
     }
     if (wgs <= capacity) {
       const int64_t n = wgs * npb;
-      const double time = n <= kSlots / 2 ? 0.7 * longest
+      const double time = n <= kSlots / 2 ? alone * longest
                           : n <= kSlots   ? (double)longest
                                           : std::max((double)longest, (double)(work * npb) / kSlots +
-                                                                          0.5 * longest);
+                                                                          tail * longest);
       if (best < 0.0 || time < best) {
         best = time;
         c.groups_u = (int)groups[0];
@@ -529,7 +560,7 @@ hipError_t launch_contract_adj_tables(const Plan& p, const ContractAdj& c, const
                        (int)p.npad, pitch, wavelength, g, (int64_t)p.nx * p.ny, c.gblocks, c.gmax,
                        p.ny, p.nx, pblocks, yslices, (uint4*)c.yq, (uint4*)c.xq);
   };
-  if (c.mode == kHalfF16x3)
+  if (c.mode == kHalfF16x3 || c.mode == kF32)
     go(contract_adj_tables_kernel<kHalfF16x3>);
   else if (c.mode == kHalfF16)
     go(contract_adj_tables_kernel<kHalfF16>);
@@ -575,6 +606,8 @@ hipError_t launch_contract_adj(const Plan& p, const ContractAdj& c, const float*
     go(contract_adj_kernel<kHalfF16x3, true>);
   else if (c.mode == kHalfF16x3)
     go(contract_adj_kernel<kHalfF16x3, false>);
+  else if (c.mode == kF32)
+    go(contract_adj_kernel<kF32, true>);
   else if (c.mode == kHalfF16)
     go(contract_adj_kernel<kHalfF16, true>);
   else

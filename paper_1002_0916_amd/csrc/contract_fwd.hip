@@ -1,4 +1,4 @@
-// Forward hologram as one contraction on the 16-bit matrix cores (contract.h):
+// Forward hologram as one contraction on the matrix cores (contract.h):
 //
 //   I[y][x] = sum_j A_j (cY_j(y) cX_j(x) - sY_j(y) sX_j(x)) = sum_k P[y][k] Q[x][k],
 //   P[y][2j] = A_j cY_j(y), P[y][2j + 1] = -A_j sY_j(y), Q[x][2j] = cX_j(x),
@@ -21,6 +21,12 @@
 // it.  The KS groups (two or more) split the points of the same pixels; their
 // sums are added in group order through LDS at the end (a fixed order: bitwise
 // reproducible), which also keeps every chain of additions short.
+//
+// The FP32 format (v_mfma_f32_32x32x2, 4 flops per interaction) is bound by the
+// FP32 matrix cores, whose instructions occupy the vector unit as well: a cosine
+// or sine beside them costs its full time, so its tables hold the operands
+// themselves (8 bytes).  1920x1024, N = 1024: 88 us a call where a tiled product
+// of operand tables in memory took 99 (333x197, N = 700: 16 and 32).
 #include "contract.h"
 #include "records.h"
 
@@ -63,9 +69,10 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     FwdOperands o, int npad, int nx, int ny, unsigned tiles_x, unsigned tiles, int per_slice,
     const unsigned* __restrict__ amax, float* __restrict__ out, const float* __restrict__ tgt,
     float* __restrict__ res) {
-  constexpr bool kSplit = MODE == kHalfF16x3;
+  constexpr bool kForms = MODE == kHalfF16x3;  // from phases; else the tables hold operands
   constexpr int kThreads = kWave * WM * KS;
-  constexpr int kPlanes = kSplit ? 2 : 1;
+  constexpr int kPlanes = kForms || MODE == kF32 ? 2 : 1;  // uint4 per operand share
+  constexpr int kLoad = MODE == kF32 ? 2 : 1;              // and per table entry
   constexpr int kS = 2;                          // steps (of 8 points) per LDS stage
   constexpr int kShare = WM > 1 ? kS * NJ / WM : 1;  // operand blocks a wave forms per stage
   constexpr int kAhead = 2;                      // steps whose phases are loaded ahead
@@ -116,33 +123,48 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 #pragma unroll
   for (int n = 0; n < NJ; ++n)
     xoff[n] = (unsigned)(half * o.cols_x + min(x0 + n * 32 + l32, o.cols_x - 1)) * 16u;
+  struct Entry {
+    uint4 q[kLoad];
+  };
   struct RowPhases {
-    uint4 p[MI];
+    Entry p[MI];
     float4 a;
   };
+  // kF32: a quad's second pair of points is a plane further.
+  const int64_t yplane = (int64_t)(npad / 4) * o.rows_y * 16;
+  const int64_t xplane = (int64_t)(npad / 4) * o.cols_x * 16;
   auto load_y = [&](int t, RowPhases& r) {
     const char* base = yt + (int64_t)t * o.rows_y * 32;
 #pragma unroll
-    for (int i = 0; i < MI; ++i) r.p[i] = *reinterpret_cast<const uint4*>(base + yoff[i]);
-    if (kSplit) r.a = *reinterpret_cast<const float4*>(at + (int64_t)t * 32 + (unsigned)half * 16u);
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int k = 0; k < kLoad; ++k)
+        r.p[i].q[k] = *reinterpret_cast<const uint4*>(base + k * yplane + yoff[i]);
+    if (kForms) r.a = *reinterpret_cast<const float4*>(at + (int64_t)t * 32 + (unsigned)half * 16u);
   };
-  auto load_x = [&](int t, int n) -> uint4 {
-    if constexpr (XTAB)
-      return *reinterpret_cast<const uint4*>(xt + (int64_t)t * o.cols_x * 32 + xoff[n]);
-    else
-      return __builtin_bit_cast(
+  auto load_x = [&](int t, int n) -> Entry {
+    Entry p;
+    if constexpr (XTAB) {
+      const char* base = xt + (int64_t)t * o.cols_x * 32;
+#pragma unroll
+      for (int k = 0; k < kLoad; ++k)
+        p.q[k] = *reinterpret_cast<const uint4*>(base + k * xplane + xoff[n]);
+    } else {
+      p.q[0] = __builtin_bit_cast(
           uint4, quad_phases(o.rec, (int64_t)t * 2 + half, (float)(x0 + n * 32 + l32)));
+    }
+    return p;
   };
-  auto form_x = [&](uint4 p) -> Frag {
-    if constexpr (kSplit) return frag_of_phases<MODE>(__builtin_bit_cast(float4, p));
-    return Frag{p, make_uint4(0, 0, 0, 0)};
+  auto form_x = [&](const Entry& p) -> Frag {
+    if constexpr (kForms) return frag_of_phases<MODE>(__builtin_bit_cast(float4, p.q[0]));
+    return Frag{p.q[0], p.q[kLoad - 1]};
   };
 
   // The first kAhead steps' loads are in flight while the scale is found.
   RowPhases py[kAhead];
 #pragma unroll
   for (int u = 0; u < kAhead; ++u) load_y(min(t0 + u, last), py[u]);
-  uint4 px[kPx];
+  Entry px[kPx];
   uint4* buf = lds + grp * kStage;
   constexpr int kBuf = kS * NJ * kPlanes * kWave;
   // WM > 1: this wave's share of stage s, blocks b = w, w + WM, ... of the
@@ -155,7 +177,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     const Frag f = form_x(px[k]);
     uint4* d = buf + (s & 1) * kBuf + (k * WM + w) * kPlanes * kWave + lane;
     d[0] = f.hi;
-    if (kSplit) d[kWave] = f.lo;
+    if (kPlanes > 1) d[kWave] = f.lo;
   };
   auto load_stage = [&](int s) {
 #pragma unroll
@@ -174,27 +196,29 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 
   // Scale of the amplitudes from their largest magnitude.
   unsigned m = 0;
-  if (kSplit) {
+  if (MODE == kHalfF16x3) {
     for (int j = threadIdx.x * 4; j < npad; j += kThreads * 4) {
       const float4 v = *reinterpret_cast<const float4*>(o.amp + j);
       m = max(m, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
                      max(__float_as_uint(fabsf(v.z)), __float_as_uint(fabsf(v.w)))));
     }
     m = group_max<kThreads>(m, red);
-  } else {
+  } else if (MODE != kF32) {
     m = group_max<kWave>(amax[lane], red);
   }
-  float mul, undo;
-  operand_scale<MODE>(m, mul, undo);
+  float mul = 1.0f, undo = 1.0f;
+  if (MODE != kF32) operand_scale<MODE>(m, mul, undo);
   auto form_y = [&](const RowPhases& r, float mul, Frag (&A)[MI]) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
-      if constexpr (kSplit)
+      if constexpr (kForms) {
         A[i] = frag_of_phases<MODE>(
-            __builtin_bit_cast(float4, r.p[i]),
+            __builtin_bit_cast(float4, r.p[i].q[0]),
             make_float4(r.a.x * mul, r.a.y * mul, r.a.z * mul, r.a.w * mul));
-      else
-        A[i] = Frag{mul != 0.0f ? r.p[i] : make_uint4(0, 0, 0, 0), make_uint4(0, 0, 0, 0)};
+      } else {
+        const uint4 zero = make_uint4(0, 0, 0, 0);
+        A[i] = mul != 0.0f ? Frag{r.p[i].q[0], r.p[i].q[kLoad - 1]} : Frag{zero, zero};
+      }
     }
   };
 
@@ -206,11 +230,11 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][n][r] = 0.0f;
   auto products = [&](const Frag (&A)[MI], const Frag& B, int n) {
+    auto part = [&](auto k) {
 #pragma unroll
-    for (int k = 0; k < (kSplit ? 3 : 1); ++k)
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-        acc[i][n] = mfma16<MODE>(k == 2 ? A[i].lo : A[i].hi, k == 1 ? B.lo : B.hi, acc[i][n]);
+      for (int i = 0; i < MI; ++i) acc[i][n] = mfma_part<MODE, decltype(k)::value>(A[i], B, acc[i][n]);
+    };
+    parts(part, std::make_integer_sequence<int, mfmas_per_step(MODE)>{});
   };
 
   // The matrix cores run beside the vector ALU only if a wave keeps issuing
@@ -218,9 +242,9 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
   // formed among the products of the current one, in the proportion given here.
   // (On gfx950 the same instructions as two blocks take 1.5 times as long.)
   constexpr int kForm = MI + (WM == 1 ? NJ : kShare / kS);  // quads formed per step
-  constexpr int kMfma = MI * NJ * (kSplit ? 3 : 1);         // MFMAs per step
+  constexpr int kMfma = MI * NJ * mfmas_per_step(MODE);     // MFMAs per step
   auto interleave = [&]() {
-    if constexpr (kSplit) {
+    if constexpr (kForms) {
       constexpr int kTrans = (kForm * 8 + kMfma - 1) / kMfma;
       constexpr int kValu = (kForm * 16 + kMfma - 1) / kMfma;
 #pragma unroll
@@ -273,7 +297,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
         const uint4* q = src + b * kPlanes * kWave;
         Frag f;
         f.hi = q[0];
-        f.lo = kSplit ? q[kWave] : f.hi;
+        f.lo = kPlanes > 1 ? q[kWave] : f.hi;
         return f;
       };
       Frag B = read_x(0);
@@ -305,7 +329,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 
   // An infinite or NaN amplitude has no scale: such a call takes the sum term
   // by term, cos(X + Y) A, so that its infinities and NaNs are the direct sum's.
-  if (kSplit && !finite_bits(m)) {
+  if (MODE == kHalfF16x3 && !finite_bits(m)) {
     for (int e = grp * kWave + lane; e < MI * 32 * NJ * 32; e += KS * kWave) {
       const int row = y0 + e / (NJ * 32), col = x0 + e % (NJ * 32);
       if (row >= ny || col >= nx) continue;
@@ -406,7 +430,7 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
   const bool is_y = (int)blockIdx.y < yslices;
   const int slice = is_y ? (int)blockIdx.y : (int)blockIdx.y - yslices;
   float mul = 1.0f;
-  if (MODE != kHalfF16x3 && is_y) {
+  if ((MODE == kHalfF16 || MODE == kHalfBF16) && is_y) {
     // Few points: every y workgroup takes the largest |A| itself, n words from
     // the cache; else the maxima of contract_amax_kernel are there.
     unsigned m = 0;
@@ -444,6 +468,11 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
     const float ph = axis_phase((float)h, c, r.ph, r.pl, b, d);
     if constexpr (MODE == kHalfF16x3) {
       dst[h * 4] = __float_as_uint(ph);
+    } else if constexpr (MODE == kF32) {
+      const float cs = cos_rev(ph), sn = sin_rev(ph);
+      float* d2 = reinterpret_cast<float*>(is_y ? yq : xq) +
+                  (e >> 1) * ((int64_t)gridDim.x * 16 * rows) + (q * rows + h) * 4 + (e & 1) * 2;
+      *reinterpret_cast<float2*>(d2) = is_y ? make_float2(A * cs, -(A * sn)) : make_float2(cs, sn);
     } else {
       const float cs = cos_rev(ph), sn = sin_rev(ph);
       dst[h * 4] = is_y ? pack16<MODE>(A * cs, -(A * sn)) : pack16<MODE>(cs, sn);
@@ -500,23 +529,23 @@ __global__ __launch_bounds__(256) void contract_fwd_sum_kernel(const float* __re
 
 // Tile shapes <MI, NJ, WM, KS>: pixels per workgroup and the terms of its time
 // on this GPU: microseconds per launch beside the loop, and per 1000 points and
-// round of 256 workgroups (one a CU), for f16x3 and for the single planes, each
-// in a launch of one round and of more.  Larger tiles form fewer operands per
+// round of 256 workgroups (one a CU), for f16x3, for the single planes and for
+// FP32, each in a launch of one round and of more.  Larger tiles form fewer operands per
 // product (per pixel <2, 4, 2, 2> takes 0.7 of <2, 2, 1, 4>'s time and 0.4 of
 // <1, 1, 1, 8>'s); smaller ones and more point groups put a small hologram on
 // more CUs.  Measured at 50 random sizes (64 to 3840 by 64 to 2160, 64 to 65,536
 // points), the choice is within 4% of the best shape on average, 21% at most.
 struct Shape {
   int rows, cols, groups;
-  float fixed, split_one, split, single_one, single;
+  float fixed, split_one, split, single_one, single, f32_one, f32;
 };
 constexpr Shape kShapes[] = {
-    {128, 128, 2, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f},  // <2, 4, 2, 2>
-    {64, 128, 8, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f},   // <2, 4, 1, 8>
-    {64, 64, 4, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f},     // <2, 2, 1, 4>
-    {64, 64, 8, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f},      // <2, 2, 1, 8>
-    {32, 64, 8, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f},      // <1, 2, 1, 8>
-    {32, 32, 8, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f},        // <1, 1, 1, 8>
+    {128, 128, 2, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f, 132.0f, 140.0f},  // <2, 4, 2, 2>
+    {64, 128, 8, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f, 77.0f, 77.0f},   // <2, 4, 1, 8>
+    {64, 64, 4, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f, 40.6f, 38.5f},     // <2, 2, 1, 4>
+    {64, 64, 8, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f, 36.6f, 39.5f},      // <2, 2, 1, 8>
+    {32, 64, 8, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f, 19.6f, 20.5f},      // <1, 2, 1, 8>
+    {32, 32, 8, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f, 11.0f, 10.6f},        // <1, 1, 1, 8>
 };
 
 // Shape and slices for plan p.  Cutting the points into slices (as far as the
@@ -533,6 +562,7 @@ int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_sli
   float best_time = 0.0f;
   slices = 1;
   const int64_t units = npad / 64;  // points are cut in units of 64
+  const int64_t most = mode == kF32 ? 4096 : 1024;  // workgroups of a sliced launch
   const float plane_us = (float)nx * (float)ny * (8.0f / 3e6f);
   for (int k = 0; k < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++k) {
     const Shape& q = kShapes[k];
@@ -540,10 +570,11 @@ int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_sli
     for (int64_t want = 1; want <= max_slices || want == 1; want += want < 4 ? 1 : want / 2) {
       const int64_t per = (units + want - 1) / want, n = (units + per - 1) / per;  // none empty
       const bool few = n * q.groups < min_parts && n < max_slices && n < units;
-      if (want > 1 && !few && (units < 8 * want || tiles * want > 1024) && best_time > 0.0f) break;
+      if (want > 1 && !few && (units < 8 * want || tiles * want > most) && best_time > 0.0f) break;
       if (few) continue;
       const int64_t rounds = (tiles * n + 255) / 256;
       const float per_k = mode == kHalfF16x3 ? (rounds == 1 ? q.split_one : q.split)
+                          : mode == kF32     ? (rounds == 1 ? q.f32_one : q.f32)
                                              : (rounds == 1 ? q.single_one : q.single);
       const float time = q.fixed + (float)rounds * (float)(per * 64) * 1e-3f * per_k +
                          (n > 1 ? 6.0f + (float)n * plane_us : 0.0f);
@@ -595,12 +626,12 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
     c.yq = w.ytab;
     c.xq = w.xtab;
   } else {
-    c.mode = p.variant == 3 ? kHalfF16x3 : p.variant == 4 ? kHalfF16 : kHalfBF16;
+    c.mode = p.variant == 2 ? kF32 : p.variant == 3 ? kHalfF16x3 : p.variant == 4 ? kHalfF16 : kHalfBF16;
     c.rows_y = p.nyp;
     c.cols_x = p.nxp;
     c.xtab = true;
-    c.yq = w.htab_y;
-    c.xq = w.htab_x;
+    c.yq = p.variant == 2 ? w.sep_y : w.htab_y;
+    c.xq = p.variant == 2 ? w.sep_x : w.htab_x;
   }
   c.rec = (float4*)w.xrec;
   c.amp = w.amp;
@@ -619,8 +650,9 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
     room = in_sep;
     c.planes = w.sep_c;
   }
-  // The f16x3 variant sums in at least as many parts as its plan's K splits.
-  const int64_t parts = p.variant == 3 ? p.sep_splits : 1;
+  // The f16x3 and f32 separable variants sum in at least as many parts as their
+  // plan's K splits.
+  const int64_t parts = p.variant == 3 || p.variant == 2 ? p.sep_splits : 1;
   c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices);
   return true;
 }
@@ -631,7 +663,7 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
   const int yslices = (c.rows_y + kTabRows - 1) / kTabRows;
   const int xslices = c.xtab ? (c.cols_x + kTabRows - 1) / kTabRows : 0;
   const dim3 grid((unsigned)(p.npad / 16), (unsigned)(yslices + xslices));
-  if (c.mode != kHalfF16x3 && p.n > kAmaxInline)
+  if ((c.mode == kHalfF16 || c.mode == kHalfBF16) && p.n > kAmaxInline)
     hipLaunchKernelGGL(contract_amax_kernel, dim3(kWave), dim3(256), 0, s, a, p.n, c.amax);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, y, z, a, p.n, pitch, wavelength, yslices,
@@ -640,6 +672,8 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
   };
   if (c.mode == kHalfF16x3)
     go(contract_fwd_tables_kernel<kHalfF16x3>);
+  else if (c.mode == kF32)
+    go(contract_fwd_tables_kernel<kF32>);
   else if (c.mode == kHalfF16)
     go(contract_fwd_tables_kernel<kHalfF16>);
   else
@@ -652,6 +686,8 @@ hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
   hipError_t e;
   if (c.mode == kHalfF16x3)
     e = launch_mode<kHalfF16x3>(p, c, out, target, residual, s);
+  else if (c.mode == kF32)
+    e = launch_mode<kF32>(p, c, out, target, residual, s);
   else if (c.mode == kHalfF16)
     e = launch_mode<kHalfF16>(p, c, out, target, residual, s);
   else

@@ -1,5 +1,4 @@
-"""The contraction kernels (operands formed in the kernel, 16-bit matrix
-cores): every tile shape and point split of the forward and the adjoint's
+"""The contraction kernels (operands formed in the kernel, matrix cores): every tile shape and point split of the forward and the adjoint's
 tiles, slices and column groups, at their edges, and the inputs the formats
 treat specially.
 
@@ -39,8 +38,8 @@ FORWARD = [(32, 32, 9), (33, 31, 64), (65, 129, 65), (333, 197, 700), (600, 500,
            (40, 20, 3001)]
 
 
-@pytest.mark.parametrize("variant", ["compensated", "separable_f16x3", "separable_f16",
-                                     "separable_bf16"])
+@pytest.mark.parametrize("variant", ["compensated", "separable", "separable_f16x3",
+                                     "separable_f16", "separable_bf16"])
 @pytest.mark.parametrize("shape", FORWARD)
 def test_forward_shapes(oracle_mod, variant, shape):
     nx, ny, n = shape
@@ -105,8 +104,8 @@ ADJOINT = [(32, 32, 9), (33, 32, 64), (65, 129, 65), (129, 127, 200), (333, 197,
            (640, 100, 3000), (40, 1500, 129), (1501, 37, 130)]
 
 
-@pytest.mark.parametrize("variant", ["compensated", "separable_f16x3", "separable_f16",
-                                     "separable_bf16"])
+@pytest.mark.parametrize("variant", ["compensated", "separable", "separable_f16x3",
+                                     "separable_f16", "separable_bf16"])
 @pytest.mark.parametrize("shape", ADJOINT)
 def test_adjoint_shapes(oracle_mod, variant, shape):
     """The f16x3 bar is the forward's, with the chain of additions over the
