@@ -383,10 +383,13 @@ int forward_contract(const Plan& p, const ContractFwd& c, int kernel, const floa
                      const float* y, const float* z, const float* a, double pitch,
                      double wavelength, float* hologram, const float* target, float* residual,
                      hipStream_t s, bool timed) {
-  hipError_t e = launch_contract_fwd_tables(p, c, x, y, z, a, pitch, wavelength, s);
+  hipError_t e = c.direct ? hipSuccess
+                          : launch_contract_fwd_tables(p, c, x, y, z, a, pitch, wavelength, s);
   if (e != hipSuccess) return CGH_EHIP;
   const EventPair ev = profile_begin(kernel, s, timed);
-  e = launch_contract_fwd(p, c, hologram, target, residual, s);
+  e = c.direct ? launch_contract_direct(p, c, x, y, z, a, pitch, wavelength, hologram, target,
+                                        residual, s)
+               : launch_contract_fwd(p, c, hologram, target, residual, s);
   profile_end(kernel, ev, s);
   return hip_status(e);
 }

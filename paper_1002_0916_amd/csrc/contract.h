@@ -175,6 +175,7 @@ struct FwdOperands {
 
 struct ContractFwd {
   int mode;           // the operand format
+  bool direct;        // one launch without tables (few points), else:
   int shape;          // index of the kernel's tile shape
   int rows_y, cols_x;
   bool xtab;
@@ -192,6 +193,10 @@ int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny);
 hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const float* x,
                                       const float* y, const float* z, const float* a,
                                       double pitch, double wavelength, hipStream_t s);
+hipError_t launch_contract_direct(const Plan& p, const ContractFwd& c, const float* x,
+                                  const float* y, const float* z, const float* a, double pitch,
+                                  double wavelength, float* out, const float* target,
+                                  float* residual, hipStream_t s);
 hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
                                const float* target, float* residual, hipStream_t s);
 

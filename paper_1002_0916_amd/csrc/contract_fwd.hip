@@ -480,6 +480,124 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
   }
 }
 
+// Few points on a small hologram, in one launch without tables: a call of two
+// launches there is bound by them (256x256, N = 64: 14.3 us a call, 11.3 here).  A workgroup is 32 x 32
+// pixels and eight waves.  It forms the records of up to 512 points at a time in
+// LDS, one a thread; wave w takes steps w, w + 8, ... of eight points, each lane
+// the phases of its four points at its row and its column, from records that all
+// lanes of a half read together (broadcasts).  Tiles of one block form every
+// phase once per 32 pixels, 0.9 instructions an interaction, which is why many
+// points or large holograms take tables and larger tiles.
+constexpr int kDirectPoints = 512;
+template <int MODE, bool RES>
+__global__ __launch_bounds__(512) void contract_fwd_direct_kernel(
+    const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
+    const float* __restrict__ a, int n, double pitch, double wavelength, int nx, int ny,
+    unsigned tiles_x, float* __restrict__ out, const float* __restrict__ tgt,
+    float* __restrict__ res) {
+  constexpr int kWaves = 8;
+  __shared__ float4 lds[kWaves * 16 * kWave / 4];  // the records, later the waves' sums
+  __shared__ unsigned red[kWaves];
+  static_assert(9 * kDirectPoints * sizeof(float) <= sizeof(lds), "the records fit");
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int half = lane >> 5, l32 = lane & 31;
+  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int y0 = (int)(tile / tiles_x) * 32, x0 = (int)(tile % tiles_x) * 32;
+  const float row = (float)(y0 + l32), col = (float)(x0 + l32);
+
+  PointRecord r = point_record(x, y, z, a, threadIdx.x, n, pitch, wavelength);
+  unsigned m = 0;
+  float mul = 1.0f, undo = 1.0f;
+  if (MODE != kF32) {
+    m = __float_as_uint(fabsf(r.a));
+    for (int j = kDirectPoints + threadIdx.x; j < n; j += kDirectPoints)
+      m = max(m, __float_as_uint(fabsf(a[j])));
+    m = group_max<512>(m, red);
+    operand_scale<MODE>(MODE == kHalfF16x3 || finite_bits(m) ? m : 0u, mul, undo);
+  }
+  floatx16 acc;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) acc[k] = 0.0f;
+  float direct[2] = {0.0f, 0.0f};  // this thread's two pixels, of a sum without a scale
+  const int sum_at = (threadIdx.x >> 6) * 2;  // their registers: sum_at and sum_at + 1
+
+  float* recs = reinterpret_cast<float*>(lds);
+  for (int base = 0; base < n; base += kDirectPoints) {
+    if (base > 0) {
+      r = point_record(x, y, z, a, base + threadIdx.x, n, pitch, wavelength);
+      __syncthreads();
+    }
+    float* d = recs + threadIdx.x;
+    d[0 * kDirectPoints] = r.ph;
+    d[1 * kDirectPoints] = r.pl;
+    d[2 * kDirectPoints] = r.yc;
+    d[3 * kDirectPoints] = r.yb;
+    d[4 * kDirectPoints] = r.yd;
+    d[5 * kDirectPoints] = r.xc;
+    d[6 * kDirectPoints] = r.xb;
+    d[7 * kDirectPoints] = r.xd;
+    d[8 * kDirectPoints] = r.a;
+    __syncthreads();
+    const int here = min(kDirectPoints, n - base);
+    if (MODE == kHalfF16x3 && !finite_bits(m)) {
+      for (int j = 0; j < here; ++j) {
+        const float* q = recs + j;
+        const float X = axis_phase(col, q[5 * kDirectPoints], q[0], q[kDirectPoints],
+                                   q[6 * kDirectPoints], q[7 * kDirectPoints]);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int k = sum_at + e;
+          const float h = (float)(y0 + (k >> 2) * 8 + half * 4 + (k & 3));
+          const float Y = axis_phase(h, q[2 * kDirectPoints], q[0], q[kDirectPoints],
+                                     q[3 * kDirectPoints], q[4 * kDirectPoints]);
+          direct[e] = __builtin_fmaf(q[8 * kDirectPoints], cos_rev(X + Y), direct[e]);
+        }
+      }
+      continue;
+    }
+    for (int t = wave; t * 8 < here; t += kWaves) {
+      const float4* q = lds + 2 * t + half;
+      constexpr int kQuads = kDirectPoints / 4;
+      const float4 ph = q[0], pl = q[kQuads];
+      auto phases = [&](float h, const float4& c, const float4& b, const float4& d) {
+        return make_float4(axis_phase(h, c.x, ph.x, pl.x, b.x, d.x),
+                           axis_phase(h, c.y, ph.y, pl.y, b.y, d.y),
+                           axis_phase(h, c.z, ph.z, pl.z, b.z, d.z),
+                           axis_phase(h, c.w, ph.w, pl.w, b.w, d.w));
+      };
+      const float4 Y = phases(row, q[2 * kQuads], q[3 * kQuads], q[4 * kQuads]);
+      const float4 X = phases(col, q[5 * kQuads], q[6 * kQuads], q[7 * kQuads]);
+      const float4 A = q[8 * kQuads];
+      const Frag P = frag_of_phases<MODE>(Y, make_float4(A.x * mul, A.y * mul, A.z * mul, A.w * mul));
+      const Frag Q = frag_of_phases<MODE>(X);
+      auto part = [&](auto k) { acc = mfma_part<MODE, decltype(k)::value>(P, Q, acc); };
+      parts(part, std::make_integer_sequence<int, mfmas_per_step(MODE)>{});
+    }
+  }
+
+  // The waves' sums in wave order; thread t stores two pixels.
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) recs[(wave * 16 + k) * kWave + lane] = acc[k];
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int k = sum_at + e;
+    float v = recs[k * kWave + lane];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) v += recs[(w * 16 + k) * kWave + lane];
+    v *= undo;
+    if (MODE == kHalfF16x3 && !finite_bits(m)) v = direct[e];
+    const int yy = y0 + (k >> 2) * 8 + half * 4 + (k & 3), xx = x0 + l32;
+    if (yy < ny && xx < nx) {
+      const int64_t at = (int64_t)yy * nx + xx;
+      out[at] = v;
+      if constexpr (RES) res[at] = v - tgt[at];
+    }
+  }
+}
+
 template <int MODE, int MI, int NJ, int WM, int KS>
 hipError_t launch_shape(const Plan& p, const ContractFwd& c, float* out, const float* tgt,
                         float* res, hipStream_t s) {
@@ -548,7 +666,7 @@ constexpr Shape kShapes[] = {
     {32, 32, 8, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f, 11.0f, 10.6f},        // <1, 1, 1, 8>
 };
 
-// Shape and slices for plan p.  Cutting the points into slices (as far as the
+// Shape, slices and their time in microseconds for plan p.  Cutting the points into slices (as far as the
 // plan has room for their planes) puts a small hologram of many points on more
 // CUs, at one more launch (6 us) and the planes' traffic (at 3 TB/s); a slice
 // has at least 512 points.  (128x96, N = 60000: 410 us in one slice, 36 in 21.)
@@ -557,9 +675,9 @@ constexpr Shape kShapes[] = {
 // a part's length (3332x341, N = 60771: 2.97e-6 of the result in 2 parts,
 // 4.3e-7 in 64).
 int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices,
-                 int64_t min_parts, int& slices) {
+                 int64_t min_parts, int& slices, float& best_time) {
   int best = 0;
-  float best_time = 0.0f;
+  best_time = 0.0f;
   slices = 1;
   const int64_t units = npad / 64;  // points are cut in units of 64
   const int64_t most = mode == kF32 ? 4096 : 1024;  // workgroups of a sliced launch
@@ -602,11 +720,27 @@ hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const fl
   }
 }
 
+// Whether one launch of contract_fwd_direct_kernel is faster than the tables'
+// launch and the shape that takes `tiled` us.  It takes 4.5 us and, for each
+// round of 256 tiles, 0.45 and the given time per 1000 points; the tables take
+// 3.5 us and more.  (us a call, tables and direct: 256x256, N = 64: 14.3 and 11.3;
+// N = 1024: 15.2 and 14.9; N = 2048: 17.3 and 26.5; 1920x1080, N = 64: 20.0 and
+// 12.7; N = 128: 14.3 and 17.5.)  Beyond two rounds of records it loses to the
+// tables, and its eight partial sums a pixel become longer than theirs.
+bool use_direct(int64_t n, int32_t nx, int32_t ny, int mode, float tiled) {
+  if (n > 2 * kDirectPoints) return false;
+  const int64_t tiles = ((int64_t)nx + 31) / 32 * (((int64_t)ny + 31) / 32);
+  const float rounds = (float)((tiles + 255) / 256);
+  const float per_k = mode == kHalfF16x3 ? 9.2f : mode == kF32 ? 13.2f : 7.0f;
+  return 4.5f + rounds * (0.45f + (float)n * 1e-3f * per_k) < tiled + 3.5f;
+}
+
 }  // namespace
 
 int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny) {
   int slices;
-  (void)choose_shape(npad, nx, ny, kHalfF16x3, INT64_MAX / 2, 1, slices);
+  float time;
+  (void)choose_shape(npad, nx, ny, kHalfF16x3, INT64_MAX / 2, 1, slices, time);
   return slices;
 }
 
@@ -653,7 +787,9 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   // The f16x3 and f32 separable variants sum in at least as many parts as their
   // plan's K splits.
   const int64_t parts = p.variant == 3 || p.variant == 2 ? p.sep_splits : 1;
-  c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices);
+  float time;
+  c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices, time);
+  c.direct = use_direct(p.n, p.nx, p.ny, c.mode, time);
   return true;
 }
 
@@ -678,6 +814,34 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
     go(contract_fwd_tables_kernel<kHalfF16>);
   else
     go(contract_fwd_tables_kernel<kHalfBF16>);
+  return hipGetLastError();
+}
+
+hipError_t launch_contract_direct(const Plan& p, const ContractFwd& c, const float* x,
+                                  const float* y, const float* z, const float* a, double pitch,
+                                  double wavelength, float* out, const float* target,
+                                  float* residual, hipStream_t s) {
+  const int64_t tiles_x = (p.nx + 31) / 32, tiles = tiles_x * ((p.ny + 31) / 32);
+  if (tiles > 0x7fffffff || p.n > 0x7fffffff - kDirectPoints) return hipErrorInvalidValue;
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(512), 0, s, x, y, z, a, (int)p.n, pitch,
+                       wavelength, p.nx, p.ny, (unsigned)tiles_x, out, target, residual);
+  };
+  auto either = [&](auto mode) {
+    constexpr int kMode = decltype(mode)::value;
+    if (residual)
+      go(contract_fwd_direct_kernel<kMode, true>);
+    else
+      go(contract_fwd_direct_kernel<kMode, false>);
+  };
+  if (c.mode == kHalfF16x3)
+    either(std::integral_constant<int, kHalfF16x3>{});
+  else if (c.mode == kF32)
+    either(std::integral_constant<int, kF32>{});
+  else if (c.mode == kHalfF16)
+    either(std::integral_constant<int, kHalfF16>{});
+  else
+    either(std::integral_constant<int, kHalfBF16>{});
   return hipGetLastError();
 }
 

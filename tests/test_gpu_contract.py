@@ -62,6 +62,17 @@ def test_forward_shapes(oracle_mod, variant, shape):
     assert err <= bar
 
 
+# One launch without tables: one point and the records' rounds of 512 with their
+# neighbours, tiles of 32 pixels and remainders (compensated calls of up to 8
+# points take the direct sum).
+@pytest.mark.parametrize("variant", ["compensated", "separable", "separable_f16x3",
+                                     "separable_f16", "separable_bf16"])
+@pytest.mark.parametrize("shape", [(33, 31, 1), (32, 32, 9), (65, 97, 511), (100, 40, 513),
+                                   (256, 256, 1024), (256, 256, 1025), (1920, 1080, 16)])
+def test_forward_few_points(oracle_mod, variant, shape):
+    test_forward_shapes(oracle_mod, variant, shape)
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e30])
 def test_forward_amplitudes_of_any_scale(oracle_mod, scale):
     """One amplitude 2^20 times the others, at both ends of the FP32 range."""
@@ -78,7 +89,7 @@ def test_forward_amplitudes_of_any_scale(oracle_mod, scale):
     assert np.all(np.isfinite(I)) and err <= f16x3_bar(nx, ny, n, 15)
 
 
-@pytest.mark.parametrize("shape", [(70, 50, 20), (128, 96, 2000)])
+@pytest.mark.parametrize("shape", [(70, 50, 20), (70, 50, 600), (128, 96, 2000)])
 def test_forward_non_finite_amplitudes(shape):
     """An infinite amplitude gives the infinities of its term's cosine, a NaN
     gives NaN everywhere, as the sum term by term does."""
