@@ -238,9 +238,12 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.off_sep_c = (sep && fwd && p.sep_splits > 1)
                     ? take((size_t)p.sep_splits * nyp * nxp * sizeof(float))
                     : 0;
-  p.off_fold = (sep && bwd) ? take(((size_t)p.sep_splits_u * (nxp / 128) +
-                                    (size_t)p.sep_splits_p * (nyp / 128)) * np * sizeof(float4))
-                            : 0;
+  // Planes of the adjoint's partial sums: with few points as many as the
+  // contraction can use to fill the chip (12 MB at most), else as many as K
+  // slices of 128-wide tiles of both axes.
+  p.fold_planes = (int64_t)p.sep_splits_u * (p.nxp / 128) + (int64_t)p.sep_splits_p * (p.nyp / 128);
+  if (n <= 4096) p.fold_planes = std::max<int64_t>(p.fold_planes, (nx + 31) / 32 + (ny + 31) / 32);
+  p.off_fold = (sep && bwd) ? take((size_t)p.fold_planes * np * sizeof(float4)) : 0;
   // The contraction's tables hold 4 bytes a point and coordinate; the f16x3 ones
   // take the room of two 16-bit planes of cosines and sines, so that the problems
   // the static scratch holds do not depend on how a table is laid out.
@@ -400,7 +403,8 @@ int backward_contract(const Plan& p, const Workspace& w, const ContractAdj& c, i
                       const float* x, const float* y, const float* z, const float* a,
                       double pitch, double wavelength, const float* g, float* gx, float* gy,
                       float* gz, float* ga, hipStream_t s) {
-  hipError_t e = launch_contract_adj_tables(p, c, x, y, z, a, pitch, wavelength, g, s);
+  hipError_t e = c.direct ? hipSuccess
+                          : launch_contract_adj_tables(p, c, x, y, z, a, pitch, wavelength, g, s);
   if (e != hipSuccess) return CGH_EHIP;
   const EventPair ev = profile_begin(kernel, s);
   e = launch_contract_adj(p, c, x, y, z, a, pitch, wavelength, g, s);

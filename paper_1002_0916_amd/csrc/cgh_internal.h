@@ -213,7 +213,7 @@ struct Plan {
   bool need_gpad;
   // separable variant
   int32_t nxp, nyp, sep_splits, sep_splits_u, sep_splits_p;
-  int64_t k2;
+  int64_t k2, fold_planes;
   size_t off_sep_x, off_sep_y, off_sep_c, off_fold;
   size_t off_hx, off_hy, off_hmax;  // half variants
   size_t off_plain, off_amp, off_xrec, off_yrec, off_rec64, off_ytab, off_xtab, off_planes, off_tab64,

@@ -217,6 +217,7 @@ hipError_t launch_contract_f64(const Plan& p, const Workspace& w, const float* x
 //   f16, bf16    two planes uint32 [ceil(size / 8)][npad][4]: cosines, sines
 struct ContractAdj {
   int mode;
+  bool direct;        // no tables: the points' records and 32-wide tiles
   bool tab;           // the tables exist (else the kernel forms the phases)
   void *yq, *xq;
   unsigned* gmax;     // [gblocks] block maxima of |G| (float bits)

@@ -372,6 +372,191 @@ __global__ __launch_bounds__(kAdjCThreads, 2) void contract_adj_kernel(AdjArgs p
     adj_part<MODE, TAB, false>(p, pb, plane, lds, red);
 }
 
+// Few points or a small hologram, without tables or max |G|: a workgroup is 32
+// points by tiles of 32 coordinates u, over all v.  Its eight waves take the
+// steps of 16 v in turn, each forming its points' operands from their records
+// and G's from memory, and add their U and V through LDS, where every thread
+// then folds two (u, point) of a tile.  G is scaled by the largest |G| of the
+// workgroup's own tile, which a first pass finds (the second meets it in the
+// L1), so no launch before this one is needed, and short chains spread over
+// the chip: 333x197, N = 700, is 22 point blocks by 18 tiles.  An operand formed
+// serves 32 u here and 128 in the tiled kernel, which takes over where that
+// counts.
+constexpr int kDirectTile = 32;
+constexpr int kDirectThreads = 512;
+template <int MODE, bool PY>
+__device__ __forceinline__ void direct_part(const AdjArgs& p, int pb, int plane, float* sums,
+                                            unsigned* red) {
+  constexpr int kWaves = kDirectThreads / kWave;
+  const int lane = threadIdx.x & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int half = lane >> 5, l32 = lane & 31;
+  const int sub = PY ? plane - p.groups_u : plane, per = PY ? p.per_p : p.per_u;
+  const int nu = PY ? p.ny : p.nx, nv = PY ? p.nx : p.ny;
+  const int tile_end = min((sub + 1) * per, PY ? p.tiles_p : p.tiles_u);
+  const int j = pb * kDirectTile + l32;  // < npad, a multiple of 64
+  const PointRecord rec = point_record(p.x, p.y, p.z, p.a, j, p.n, p.pitch, p.wavelength);
+  const float vc = PY ? rec.xc : rec.yc, vb = PY ? rec.xb : rec.yb,
+              vd = PY ? rec.xd : rec.yd;
+  const float uc = PY ? rec.yc : rec.xc, ub = PY ? rec.yb : rec.xb,
+              ud = PY ? rec.yd : rec.xd;
+  const float pu = PY ? rec.y : rec.x;
+  const int steps = (nv + 15) / 16;
+  double d0 = 0.0, d1 = 0.0, d2 = 0.0;  // this thread's part of {Sc, Sx or Sy, Sr}
+
+  for (int tile = sub * per; tile < tile_end; ++tile) {
+    const int u0 = tile * kDirectTile;
+    const bool in_u = u0 + l32 < nu;
+    const int u = min(u0 + l32, nu - 1);
+    // G at this lane's u and the eight v of step t, zero outside the hologram.
+    auto load_g = [&](int t, float (&v)[8]) {
+      const int v0 = 16 * t + 8 * half;
+      if constexpr (PY) {
+        const float* __restrict__ row = p.g + (int64_t)u * p.nx;
+        if (v0 + 8 <= nv) {
+          const f32x4u a = *reinterpret_cast<const f32x4u*>(row + v0);
+          const f32x4u b = *reinterpret_cast<const f32x4u*>(row + v0 + 4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[e] = in_u ? a[e] : 0.0f;
+            v[4 + e] = in_u ? b[e] : 0.0f;
+          }
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float g = row[min(v0 + e, nv - 1)];
+            v[e] = in_u && v0 + e < nv ? g : 0.0f;
+          }
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float g = p.g[(int64_t)min(v0 + e, nv - 1) * p.nx + u];
+          v[e] = in_u && v0 + e < nv ? g : 0.0f;
+        }
+      }
+    };
+    unsigned m = 0;
+    float mul = 1.0f, undo = 1.0f;
+    if (MODE != kF32) {
+      for (int t = wave; t < steps; t += kWaves) {
+        float v[8];
+        load_g(t, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = max(m, __float_as_uint(fabsf(v[e])));
+      }
+      __syncthreads();  // the last tile's readers of red are done
+      m = group_max<kDirectThreads>(m, red);
+      operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
+    }
+    // An infinite or NaN G has no scale: such a tile is summed term by term.
+    if (MODE == kHalfF16x3 && !finite_bits(m)) {
+      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+      for (int k = 0; k < kDirectTile && u0 + k < nu; ++k) {
+        const float U = axis_phase((float)(u0 + k), uc, rec.ph, rec.pl, ub, ud);
+        const float d = (float)(u0 + k) - pu;
+        for (int v = wave * 2 + half; v < nv; v += 2 * kWaves) {
+          const float th = U + axis_phase((float)v, vc, rec.ph, rec.pl, vb, vd);
+          const float G = p.g[PY ? (int64_t)(u0 + k) * p.nx + v : (int64_t)v * p.nx + u0 + k];
+          const float gs = G * sin_rev(th);
+          s0 = __builtin_fmaf(G, cos_rev(th), s0);
+          s1 = __builtin_fmaf(gs, d, s1);
+          s2 = __builtin_fmaf(gs, d * d, s2);
+        }
+      }
+      d0 += (double)s0;
+      d1 += (double)s1;
+      d2 += (double)s2;
+      continue;
+    }
+
+    floatx16 U, V;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) U[r] = V[r] = 0.0f;
+    for (int t = wave; t < steps; t += kWaves) {
+      float g[8], c[8], s[8];
+      load_g(t, g);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float ph = axis_phase((float)(16 * t + 8 * half + e), vc, rec.ph, rec.pl, vb, vd);
+        c[e] = cos_rev(ph);
+        s[e] = sin_rev(ph);
+        g[e] *= mul;
+      }
+      const Frag A = make_frag<MODE>(g), C = make_frag<MODE>(c), S = make_frag<MODE>(s);
+      auto part = [&](auto k) {
+        U = mfma_part<MODE, decltype(k)::value>(A, C, U);
+        V = mfma_part<MODE, decltype(k)::value>(A, S, V);
+      };
+      parts(part, std::make_integer_sequence<int, mfmas_per_step(MODE)>{});
+    }
+    // Eight registers of U and of V a round: thread (w, lane) adds the waves'
+    // register 8 h + w in wave order and folds it.
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        sums[((wave * 2 + 0) * 8 + k) * kWave + lane] = U[h * 8 + k];
+        sums[((wave * 2 + 1) * 8 + k) * kWave + lane] = V[h * 8 + k];
+      }
+      __syncthreads();
+      float su = sums[wave * kWave + lane], sv = sums[(8 + wave) * kWave + lane];
+#pragma unroll
+      for (int w = 1; w < kWaves; ++w) {
+        su += sums[((w * 2 + 0) * 8 + wave) * kWave + lane];
+        sv += sums[((w * 2 + 1) * 8 + wave) * kWave + lane];
+      }
+      const int r = h * 8 + wave;
+      const float uu = (float)(u0 + (r >> 2) * 8 + half * 4 + (r & 3));
+      const float ph = axis_phase(uu, uc, rec.ph, rec.pl, ub, ud);
+      const float c = cos_rev(ph), s = sin_rev(ph), d = uu - pu;
+      const float w0 = __builtin_fmaf(c, su, -(s * sv));
+      const float w1 = __builtin_fmaf(s, su, c * sv);
+      d0 += (double)undo * (double)w0;
+      d1 += (double)undo * (double)(d * w1);
+      d2 += (double)undo * (double)(d * d * w1);
+    }
+  }
+
+  // The sixteen threads of a point, in order.
+  d0 += __shfl_xor(d0, 32, 64);
+  d1 += __shfl_xor(d1, 32, 64);
+  d2 += __shfl_xor(d2, 32, 64);
+  __syncthreads();
+  double* all = reinterpret_cast<double*>(sums);
+  if (half == 0) {
+    all[(wave * 3 + 0) * 32 + l32] = d0;
+    all[(wave * 3 + 1) * 32 + l32] = d1;
+    all[(wave * 3 + 2) * 32 + l32] = d2;
+  }
+  __syncthreads();
+  if (threadIdx.x < 32) {
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      d0 += all[(w * 3 + 0) * 32 + l32];
+      d1 += all[(w * 3 + 1) * 32 + l32];
+      d2 += all[(w * 3 + 2) * 32 + l32];
+    }
+    p.partial[(int64_t)plane * p.npad + j] =
+        PY ? make_float4(0.f, 0.f, (float)d1, (float)d2)
+           : make_float4((float)d0, (float)d1, 0.f, (float)d2);
+  }
+}
+
+template <int MODE>
+__global__ __launch_bounds__(kDirectThreads) void contract_adj_direct_kernel(AdjArgs p) {
+  constexpr int kWaves = kDirectThreads / kWave;
+  __shared__ double sums[kWaves * 16 * kWave / 2];
+  __shared__ unsigned red[kWaves];
+  const unsigned job = xcd_tile(blockIdx.x, gridDim.x);
+  const int plane = (int)(job / (unsigned)p.npb), pb = (int)(job % (unsigned)p.npb);
+  if (plane >= p.groups_u)
+    direct_part<MODE, true>(p, pb, plane, reinterpret_cast<float*>(sums), red);
+  else
+    direct_part<MODE, false>(p, pb, plane, reinterpret_cast<float*>(sums), red);
+}
+
 // Largest |G| per workgroup (blockIdx.x < gblocks) and, in the same launch, the
 // phase tables of both axes: the workgroups after those take 256 points and
 // kTabCoords coordinates each (rows first), a thread its point's quads.
@@ -453,6 +638,31 @@ __global__ __launch_bounds__(256) void contract_adj_tables_kernel(
 
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// Plans the direct kernel where a model of its time is below that of the tiled
+// plan, which takes `best` units (none if negative).  Of the direct kernel's
+// workgroups 512 run at once; each takes 3.2 us and 0.31 a step of its longer
+// axis, and one alone on its CU 0.55 of that.  (us a call, tiled and direct:
+// 333x197, N = 700: 24.6 and 20.6; N = 2048: 28.9 and 29.9; 256x256, N = 1024:
+// 25.3 and 20.5; 1024x1024, N = 256: 29.4 and 33.2; 1920x1080, N = 128: 30.7 and
+// 47.2.  Both include 20 us of the host's that hide shorter kernels.)
+bool plan_direct(const Plan& p, int64_t capacity, double best, ContractAdj& c) {
+  const int64_t tiles_u = ceil_div(p.nx, kDirectTile), tiles_p = ceil_div(p.ny, kDirectTile);
+  const double wgs = (double)(tiles_u + tiles_p) * (double)(p.npad / kDirectTile);
+  const double steps = (double)ceil_div(std::max(p.nx, p.ny), 16);
+  const double direct = 9.5 + std::max(0.55, wgs / 512) * (3.2 + 0.31 * steps);
+  if (best >= 0.0 && direct >= 9.0 + (c.mode == kF32 ? 4.0 : 2.0) * best) return false;
+  int64_t per = 1;
+  while (ceil_div(tiles_u, per) + ceil_div(tiles_p, per) > capacity && per < tiles_u + tiles_p) ++per;
+  const int64_t planes = ceil_div(tiles_u, per) + ceil_div(tiles_p, per);
+  if (planes > capacity || planes * (p.npad / kDirectTile) > 0x7fffffff) return false;
+  c.direct = true;
+  c.groups_u = (int)ceil_div(tiles_u, per);
+  c.groups_p = (int)ceil_div(tiles_p, per);
+  c.slices_u = c.slices_p = 1;
+  c.planes = (int)planes;
+  return true;
+}
+
 }  // namespace
 
 bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c) {
@@ -479,7 +689,7 @@ bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c) {
     c.xq = p.variant == 2 ? w.sep_x : w.htab_x;
     c.tab = true;
     c.partial = w.fold;
-    capacity = (int64_t)p.sep_splits_u * (p.nxp / 128) + (int64_t)p.sep_splits_p * (p.nyp / 128);
+    capacity = p.fold_planes;
   }
   c.gmax = (unsigned*)w.plain;
   // (the FP32 operands take no scale)
@@ -541,6 +751,7 @@ bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c) {
     }
     if (t == all || (best >= 0.0 && t > std::max(one_tile, kLongest))) break;
   }
+  if (plan_direct(p, capacity, best, c)) return true;
   if (best < 0.0) return false;
   c.planes = c.groups_u * c.slices_u + c.groups_p * c.slices_p;
   return c.planes * npb <= 0x7fffffff;
@@ -589,20 +800,29 @@ hipError_t launch_contract_adj(const Plan& p, const ContractAdj& c, const float*
   r.gmax = c.gmax;
   r.gblocks = c.gblocks;
   r.partial = c.partial;
-  r.npb = (int)ceil_div(p.npad, kAdjTile);
-  r.tiles_u = (int)ceil_div(p.nx, kAdjTile);
+  const int tile = c.direct ? kDirectTile : kAdjTile;
+  r.npb = (int)ceil_div(p.npad, tile);
+  r.tiles_u = (int)ceil_div(p.nx, tile);
   r.groups_u = c.groups_u;
   r.slices_u = c.slices_u;
   r.per_u = (int)ceil_div(r.tiles_u, c.groups_u);
   r.st_u = (int)ceil_div(ceil_div(p.ny, kAdjStage), c.slices_u);
-  r.tiles_p = (int)ceil_div(p.ny, kAdjTile);
+  r.tiles_p = (int)ceil_div(p.ny, tile);
   r.groups_p = c.groups_p;
   r.slices_p = c.slices_p;
   r.per_p = (int)ceil_div(r.tiles_p, c.groups_p);
   r.st_p = (int)ceil_div(ceil_div(p.nx, kAdjStage), c.slices_p);
-  const dim3 grid((unsigned)(r.npb * c.planes)), block(kAdjCThreads);
+  const dim3 grid((unsigned)(r.npb * c.planes)), block(c.direct ? kDirectThreads : kAdjCThreads);
   auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, s, r); };
-  if (c.mode == kHalfF16x3 && c.tab)
+  if (c.direct && c.mode == kHalfF16x3)
+    go(contract_adj_direct_kernel<kHalfF16x3>);
+  else if (c.direct && c.mode == kF32)
+    go(contract_adj_direct_kernel<kF32>);
+  else if (c.direct && c.mode == kHalfF16)
+    go(contract_adj_direct_kernel<kHalfF16>);
+  else if (c.direct)
+    go(contract_adj_direct_kernel<kHalfBF16>);
+  else if (c.mode == kHalfF16x3 && c.tab)
     go(contract_adj_kernel<kHalfF16x3, true>);
   else if (c.mode == kHalfF16x3)
     go(contract_adj_kernel<kHalfF16x3, false>);

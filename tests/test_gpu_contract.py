@@ -113,6 +113,9 @@ def test_forward_non_finite_amplitudes(shape):
 # workgroup (640x100) and a single short one.
 ADJOINT = [(32, 32, 9), (33, 32, 64), (65, 129, 65), (129, 127, 200), (333, 197, 700),
            (640, 100, 3000), (40, 1500, 129), (1501, 37, 130)]
+# The direct kernel: tiles of 32, steps of 16 and rounds of eight steps with their
+# remainders; several tiles a workgroup (2000x33 with few planes).
+ADJOINT += [(32, 33, 1), (16, 129, 33), (127, 128, 32), (250, 40, 64), (2000, 33, 9)]
 
 
 @pytest.mark.parametrize("variant", ["compensated", "separable", "separable_f16x3",
@@ -144,10 +147,11 @@ def test_adjoint_shapes(oracle_mod, variant, shape):
         assert e <= bar
 
 
-def test_adjoint_non_finite_gradient():
+@pytest.mark.parametrize("shape", [(70, 150, 200), (700, 450, 400)])
+def test_adjoint_non_finite_gradient(shape):
     """An infinite G gives each point the infinity of its term, a NaN gives NaN."""
     dev = device()
-    nx, ny, n = 70, 150, 200
+    nx, ny, n = shape
     c = W.random_cloud(1301, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
     x, y, z, a = to_dev(c, dev)
     g = torch.from_numpy(np.random.default_rng(3).standard_normal((ny, nx)).astype(np.float32))
@@ -164,11 +168,12 @@ def test_adjoint_non_finite_gradient():
         assert torch.isnan(t).all()
 
 
+@pytest.mark.parametrize("shape", [(150, 110, 100), (700, 450, 400)])
 @pytest.mark.parametrize("scale", [1e-30, 1e30])
-def test_adjoint_gradient_of_any_scale(oracle_mod, scale):
+def test_adjoint_gradient_of_any_scale(oracle_mod, shape, scale):
     """One pixel 2^20 times the others, at both ends of the FP32 range."""
     dev = device()
-    nx, ny, n = 150, 110, 100
+    nx, ny, n = shape
     c = W.random_cloud(1302, n, nx, ny, zlo=ZLO, zhi=1.0, alo=0.5, ahi=1.0)
     G = np.random.default_rng(5).standard_normal((ny, nx)) * scale * 2.0 ** -20
     G[40, 77] = scale
