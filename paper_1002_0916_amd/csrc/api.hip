@@ -114,7 +114,6 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.op = op;
   p.npad = ceil_div(n > 0 ? n : 1, kPointPad) * kPointPad;
   p.fwd_gx = (int32_t)ceil_div(nx, kWave);
-  p.fwd_gy = (int32_t)ceil_div(ny, kFwdRowsPerWG);
   p.comp_gy = (int32_t)ceil_div(ny, kCompRowsPerWG);
   p.groups = p.comp_gy * kCompWaves;
   p.comp_xtab = col_table && (int64_t)p.fwd_gx * kWave * p.npad <=
@@ -553,30 +552,29 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
                                                          : CGH_KERNEL_FWD_SEPARABLE,
                               x, y, z, a, pitch, wavelength, hologram, target, residual, s, timed);
   }
+  if (variant == CGH_PLAIN) {
+    const EventPair ev = profile_begin(CGH_KERNEL_FWD_PLAIN, s, timed);
+    const hipError_t e = launch_fwd_plain(p, x, y, z, a, pitch, wavelength, hologram, target,
+                                          residual, s);
+    profile_end(CGH_KERNEL_FWD_PLAIN, ev, s);
+    return hip_status(e);
+  }
   // The compensated forward forms the records with its row-phase table.
   hipError_t e = variant == CGH_COMPENSATED
                      ? launch_prep_ytab(x, y, z, a, pitch, wavelength, p, w, s)
                      : launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, false, s);
   if (e != hipSuccess) return CGH_EHIP;
-  auto separate_residual = [&](int rc) {
-    if (rc != CGH_OK || !residual) return rc;
-    return hip_status(launch_residual(hologram, target, residual, (int64_t)p.nx * p.ny, s));
-  };
   if (variant == CGH_COMPENSATED) {
     const EventPair ev = profile_begin(CGH_KERNEL_FWD_COMPENSATED, s, timed);
     e = launch_fwd_comp(p, w, hologram, s, target, residual);
     profile_end(CGH_KERNEL_FWD_COMPENSATED, ev, s);
     return hip_status(e);
-  } else if (variant == CGH_RECURRENCE) {
-    const EventPair ev = profile_begin(CGH_KERNEL_FWD_RECURRENCE, s, timed);
-    e = launch_fwd_rec(p, w, hologram, s);
-    profile_end(CGH_KERNEL_FWD_RECURRENCE, ev, s);
-  } else {
-    const EventPair ev = profile_begin(CGH_KERNEL_FWD_PLAIN, s, timed);
-    e = launch_fwd_plain(p, w, hologram, s);
-    profile_end(CGH_KERNEL_FWD_PLAIN, ev, s);
   }
-  return separate_residual(hip_status(e));
+  const EventPair ev = profile_begin(CGH_KERNEL_FWD_RECURRENCE, s, timed);
+  e = launch_fwd_rec(p, w, hologram, s);
+  profile_end(CGH_KERNEL_FWD_RECURRENCE, ev, s);
+  if (e != hipSuccess || !residual) return hip_status(e);
+  return hip_status(launch_residual(hologram, target, residual, (int64_t)p.nx * p.ny, s));
 }
 
 }  // namespace cgh

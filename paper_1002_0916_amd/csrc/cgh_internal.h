@@ -48,19 +48,9 @@ inline unsigned grid_blocks(int64_t count, int threads) {
 }
 
 // ---------------------------------------------------------------- forward --
-// Plain forward: a workgroup is 4 waves.  Lane l of every wave owns hologram
-// column x0 + l; wave w owns kRows consecutive rows, so a workgroup covers 64
-// columns x (4 * kRows) rows and every lane produces kRows pixels of one
-// column.
-constexpr int kFwdWaves = 4;
-constexpr int kRows = 8;
-constexpr int kFwdThreads = kFwdWaves * kWave;
-constexpr int kFwdRowsPerWG = kFwdWaves * kRows;
-// Points are processed in unrolled groups of kUnroll; the compensated
-// forward stages kTile points at a time in LDS.  The point arrays in the
-// workspace are padded to a multiple of kPointPad with zero-amplitude
-// points.
-constexpr int kUnroll = 4;
+// The plain and compensated direct forwards stage kTile points at a time in LDS.
+// The point arrays in the workspace are padded to a multiple of kPointPad with
+// zero-amplitude points.
 constexpr int kTile = 64;
 constexpr int kTilePitch = kWave + 1;
 
@@ -200,7 +190,7 @@ struct Plan {
   int32_t nx, ny;
   int32_t variant, op;
   // forward
-  int32_t fwd_gx, fwd_gy, comp_gy, groups;
+  int32_t fwd_gx, comp_gy, groups;
   bool comp_xtab;  // the compensated forward has its column table
   int32_t f64_chunk, f64_slices;  // FP64 forward: points per chunk (0 slices: the direct kernel)
   int32_t fwd_planes;  // partial planes of the compensated forward (0: none of its own)
@@ -246,7 +236,10 @@ hipError_t launch_prep_ytab(const float* x, const float* y, const float* z, cons
 hipError_t launch_prep_rtab(const float* x, const float* y, const float* z, const float* a,
                             double pitch, double wavelength, const Plan& p, const Workspace& w,
                             hipStream_t s);
-hipError_t launch_fwd_plain(const Plan& p, const Workspace& w, float* out, hipStream_t s);
+// The plain forward (plain.hip), and residual = I - target with a target.
+hipError_t launch_fwd_plain(const Plan& p, const float* x, const float* y, const float* z,
+                            const float* a, double pitch, double wavelength, float* out,
+                            const float* target, float* residual, hipStream_t s);
 // With target and residual (both or neither) the compensated forward also
 // writes residual = out - target in its store.
 hipError_t launch_fwd_comp(const Plan& p, const Workspace& w, float* out, hipStream_t s,

@@ -1,7 +1,8 @@
-// Forward kernels: the direct point-source sum of Eq. (1) (Section 1).
+// Forward kernels: the direct point-source sum of Eq. (1) (Section 1); the plain
+// form is in plain.hip, the contractions in contract_fwd.hip and contract_f64.hip.
 //
-// Work mapping: one hologram column per lane.  The plain and compensated FP32
-// kernels give lane l of a wave column x0 + l and a few consecutive rows, so a
+// Work mapping: one hologram column per lane.  The compensated FP32
+// kernel gives lane l of a wave column x0 + l and a few consecutive rows, so a
 // wave writes fully coalesced 256-byte row segments, and every point record
 // is read once per wave through scalar loads (the loop index is
 // wave-uniform), i.e. broadcast to all 64 lanes from SGPRs.  Points are
@@ -15,47 +16,6 @@
 namespace cgh {
 
 namespace {
-
-// Plain FP32: per interaction the phase Prev ((x_h - x_j)^2 + (y_h - y_j)^2)
-// in revolutions, fract range reduction, native cosine, accumulate.
-__global__ __launch_bounds__(kFwdThreads) void fwd_plain_kernel(const float4* __restrict__ rec,
-                                                                int npad, int nx, int ny,
-                                                                float* __restrict__ out) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const unsigned tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  const int bx = (int)(tile % gridDim.x), by = (int)(tile / gridDim.x);
-  const int col = bx * kWave + lane;
-  const int y0 = (by * kFwdWaves + wave) * kRows;
-  const float xh = (float)col;
-  float yh[kRows];
-  float acc[kRows];
-#pragma unroll
-  for (int i = 0; i < kRows; ++i) {
-    yh[i] = (float)(y0 + i);
-    acc[i] = 0.0f;
-  }
-  for (int j = 0; j < npad; j += kUnroll) {
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const float4 r = rec[j + u];
-      const float dx = xh - r.x;
-      const float dx2 = dx * dx;
-#pragma unroll
-      for (int i = 0; i < kRows; ++i) {
-        const float dy = yh[i] - r.y;
-        const float r2 = __builtin_fmaf(dy, dy, dx2);
-        const float t = fract(r.z * r2);
-        acc[i] = __builtin_fmaf(r.w, cos_rev(t), acc[i]);
-      }
-    }
-  }
-  if (col < nx) {
-#pragma unroll
-    for (int i = 0; i < kRows; ++i)
-      if (y0 + i < ny) out[(int64_t)(y0 + i) * nx + col] = acc[i];
-  }
-}
 
 // Recurrence FP32, Eq. (2) (Section 2.1): along a row the phase of pixel
 // x_h + n follows from two additions, Gamma_n = Gamma_{n-1} + delta_{n-1} and
@@ -363,12 +323,6 @@ __global__ __launch_bounds__(256) void fwd_f64_kernel(const double4* __restrict_
 }
 
 }  // namespace
-
-hipError_t launch_fwd_plain(const Plan& p, const Workspace& w, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(fwd_plain_kernel, dim3(p.fwd_gx, p.fwd_gy), dim3(kFwdThreads), 0, s,
-                     (const float4*)w.plain, (int)p.npad, p.nx, p.ny, out);
-  return hipGetLastError();
-}
 
 namespace {
 

@@ -1,4 +1,5 @@
-"""The contraction kernels (operands formed in the kernel, matrix cores): every tile shape and point split of the forward and the adjoint's
+"""The contraction kernels (operands formed in the kernel, matrix cores) and the
+plain forward: every tile shape and point split of the forward and the adjoint's
 tiles, slices and column groups, at their edges, and the inputs the formats
 treat specially.
 
@@ -220,3 +221,30 @@ def test_f64_non_finite_amplitudes():
     assert np.array_equal(I[clear], np.where(cos > 0, -np.inf, np.inf)[clear])
     a[3] = float("nan")
     assert torch.isnan(B.forward_f64(x, y, z, a, nx, ny)).all()
+
+
+# The plain forward: rows per lane, groups that split the points and tiles of 64
+# points with their remainders (each of the rule's three forms); phases within and
+# beyond the cosine's exact range of 256 revolutions (3840 columns reach 2500).
+@pytest.mark.parametrize("shape", [(1, 1, 1), (63, 7, 63), (65, 9, 65), (640, 490, 300),
+                                   (1024, 603, 129), (3841, 1100, 70)])
+def test_plain_forward_shapes(oracle_mod, shape):
+    """Five roundings of 2^-24 of the phase (dx or dy twice in its square, the
+    sum, Prev, the product) and the cosine's 2.5e-7."""
+    nx, ny, n = shape
+    dev = device()
+    say("plain forward", shape)
+    c = W.random_cloud(1500 + n, n, nx, ny, zlo=ZLO, zhi=1.0, alo=-1.0, ahi=1.0, margin=20)
+    x, y, z, a = to_dev(c, dev)
+    T = torch.from_numpy(np.random.default_rng(n).standard_normal((ny, nx)).astype(np.float32))
+    T = T.to(dev)
+    I, G = B.forward_residual(x, y, z, a, T, nx, ny, variant="plain")
+    J = B.forward(x, y, z, a, nx, ny, variant="plain")
+    assert torch.equal(I, J) and torch.equal(G, I - T)
+    px, py = W.sample_pixels(1501, nx, ny, 3000)
+    ref = oracle_mod.forward_at(*c.astuple(), nx, ny, px, py, threads=0)
+    err = max_err_frac(I.cpu().numpy()[py, px], ref, c)
+    revs = W.PITCH ** 2 / (2 * W.WAVELENGTH * ZLO) * ((nx + 20) ** 2 + (ny + 20) ** 2)
+    bar = 2 * np.pi * 5 * 2.0 ** -24 * revs + 2.5e-7 + 2.0 ** -24 * (n + 8)
+    say("  max|dI|/sum|A| = %.3e, bar %.3e" % (err, bar))
+    assert err <= bar
