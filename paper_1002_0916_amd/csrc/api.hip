@@ -50,38 +50,31 @@ inline int gemm_splits(int64_t tiles, int64_t k) {
   return best;
 }
 
-// Shape of the recurrence forward: K pixels x R rows per lane, from the
-// instantiated set K in {4, 6, 8}, R in {1, 2, 4}.  The choice minimises a
-// time model in issue slots per SIMD: the workgroups each of the 256 CUs runs
-// (ceil(workgroups / 256); a workgroup is one wave per SIMD) times the
-// interactions per lane per point (K R) times the slots per interaction,
+// Consecutive pixels per lane of the recurrence forward, K in {4, 6, 8}.  A lane
+// starts Eq. (2) anew at its first pixel, so K is part of the result.  It is that
+// of the shape of K pixels x R rows, R in {1, 2, 4}, with the least work per CU:
+// the workgroups of four waves that each of the 256 CUs runs, times K R, times the
+// slots per interaction,
 //   4 + 1/R + (4 R + 7) / (K R)
-// (cosine 2, the Gamma add and the accumulate per interaction; delta's add
-// once per column step for R rows; dx, dx^2, delta_0 and Delta once per point
-// and lane; Gamma_0 once per row).  CGH_REC_SHAPE = 10 K + R forces a shape
-// (tuning builds only).
-inline void rec_shape(int32_t nx, int32_t ny, int32_t& k_out, int32_t& r_out) {
-#ifdef CGH_REC_SHAPE
-  (void)nx;
-  (void)ny;
-  k_out = CGH_REC_SHAPE / 10;
-  r_out = CGH_REC_SHAPE % 10;
-#else
+// (cosine 2, the Gamma add and the accumulate; delta's add once per column step
+// for R rows; dx, dx^2, delta_0 and Delta once per point and lane; Gamma_0 once
+// per row).
+inline int32_t rec_pixels(int32_t nx, int32_t ny) {
   static const int kShapes[][2] = {{8, 4}, {8, 2}, {8, 1}, {6, 4}, {6, 2},
                                    {6, 1}, {4, 4}, {4, 2}, {4, 1}};
   double best = 0.0;
+  int32_t k_out = 8;
   for (const auto& sh : kShapes) {
     const int K = sh[0], R = sh[1];
-    const int64_t wgs = ceil_div(nx, (int64_t)kWave * K) * ceil_div(ny, (int64_t)kRecWaves * R);
+    const int64_t wgs = ceil_div(nx, (int64_t)kWave * K) * ceil_div(ny, (int64_t)4 * R);
     const double slots = 4.0 + 1.0 / R + (4.0 * R + 7.0) / (K * R);
     const double t = (double)ceil_div(wgs, 256) * K * R * slots;
     if (best == 0.0 || t < best) {
       best = t;
       k_out = K;
-      r_out = R;
     }
   }
-#endif
+  return k_out;
 }
 
 inline bool valid_variant(int32_t v) { return v >= CGH_PLAIN && v <= CGH_RECURRENCE; }
@@ -118,17 +111,7 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.groups = p.comp_gy * kCompWaves;
   p.comp_xtab = col_table && (int64_t)p.fwd_gx * kWave * p.npad <=
                                  kCompColTabMaxBytes / (int64_t)sizeof(float);
-  rec_shape(nx, ny, p.rec_k, p.rec_r);
-  p.rec_gx = (int32_t)ceil_div(nx, (int64_t)kWave * p.rec_k);
-  p.rec_gy = (int32_t)ceil_div(ny, (int64_t)kRecWaves * p.rec_r);
-  // Points split over two wave groups per workgroup: measured 1-3% faster
-  // (more waves per SIMD) at every workload shape, never slower.
-  // CGH_REC_SPLIT = 1 or 2 forces it (tuning builds only).
-#ifdef CGH_REC_SPLIT
-  p.rec_s = CGH_REC_SPLIT;
-#else
-  p.rec_s = 2;
-#endif
+  p.rec_k = rec_pixels(nx, ny);
   p.ngroups = (int32_t)(p.npad / kWave);
   const bool rtab_fits =
       (int64_t)ny * p.npad <= kAdjRowTabMaxBytes / (int64_t)sizeof(float2) &&
@@ -542,7 +525,6 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
                 const float* a, double pitch, double wavelength, float* hologram,
                 hipStream_t s, bool timed, const float* target, float* residual) {
   const int32_t variant = p.variant;
-  const int64_t n = p.n;
   const Workspace w = carve(p, workspace);
   if (variant == CGH_COMPENSATED || is_separable(variant)) {
     ContractFwd c;
@@ -552,29 +534,22 @@ int forward_run(const Plan& p, void* workspace, const float* x, const float* y, 
                                                          : CGH_KERNEL_FWD_SEPARABLE,
                               x, y, z, a, pitch, wavelength, hologram, target, residual, s, timed);
   }
-  if (variant == CGH_PLAIN) {
-    const EventPair ev = profile_begin(CGH_KERNEL_FWD_PLAIN, s, timed);
-    const hipError_t e = launch_fwd_plain(p, x, y, z, a, pitch, wavelength, hologram, target,
-                                          residual, s);
-    profile_end(CGH_KERNEL_FWD_PLAIN, ev, s);
+  if (variant != CGH_COMPENSATED) {
+    const bool rec = variant == CGH_RECURRENCE;
+    const int kernel = rec ? CGH_KERNEL_FWD_RECURRENCE : CGH_KERNEL_FWD_PLAIN;
+    const EventPair ev = profile_begin(kernel, s, timed);
+    const hipError_t e = (rec ? launch_fwd_rec : launch_fwd_plain)(
+        p, x, y, z, a, pitch, wavelength, hologram, target, residual, s);
+    profile_end(kernel, ev, s);
     return hip_status(e);
   }
-  // The compensated forward forms the records with its row-phase table.
-  hipError_t e = variant == CGH_COMPENSATED
-                     ? launch_prep_ytab(x, y, z, a, pitch, wavelength, p, w, s)
-                     : launch_prep(x, y, z, a, n, p.npad, pitch, wavelength, w, false, s);
+  // The records and the row-phase table in one launch.
+  hipError_t e = launch_prep_ytab(x, y, z, a, pitch, wavelength, p, w, s);
   if (e != hipSuccess) return CGH_EHIP;
-  if (variant == CGH_COMPENSATED) {
-    const EventPair ev = profile_begin(CGH_KERNEL_FWD_COMPENSATED, s, timed);
-    e = launch_fwd_comp(p, w, hologram, s, target, residual);
-    profile_end(CGH_KERNEL_FWD_COMPENSATED, ev, s);
-    return hip_status(e);
-  }
-  const EventPair ev = profile_begin(CGH_KERNEL_FWD_RECURRENCE, s, timed);
-  e = launch_fwd_rec(p, w, hologram, s);
-  profile_end(CGH_KERNEL_FWD_RECURRENCE, ev, s);
-  if (e != hipSuccess || !residual) return hip_status(e);
-  return hip_status(launch_residual(hologram, target, residual, (int64_t)p.nx * p.ny, s));
+  const EventPair ev = profile_begin(CGH_KERNEL_FWD_COMPENSATED, s, timed);
+  e = launch_fwd_comp(p, w, hologram, s, target, residual);
+  profile_end(CGH_KERNEL_FWD_COMPENSATED, ev, s);
+  return hip_status(e);
 }
 
 }  // namespace cgh

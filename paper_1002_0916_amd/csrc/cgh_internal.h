@@ -81,16 +81,6 @@ static_assert(kTile % 16 == 0, "the inner loop takes 16 points per iteration");
 constexpr int64_t kCompColTabMaxBytes = int64_t(256) << 20;
 constexpr int kPointPad = 64;
 
-// Recurrence forward (Eq. (2)): lane l of a wave covers K consecutive pixels
-// of R rows, a group of kRecWaves waves is stacked in y, and a workgroup holds
-// S such groups that split the points between them; points are taken
-// kRecUnroll at a time (scalar loads one group ahead).  (K, R) comes from a
-// small set of instantiations chosen per shape by rec_shape().
-constexpr int kRecWaves = 4;
-constexpr int kRecThreads = kRecWaves * kWave;
-constexpr int kRecUnroll = 4;
-static_assert(kPointPad % (2 * kRecUnroll) == 0, "point padding holds whole group pairs");
-
 // ---------------------------------------------------------------- adjoint --
 // An adjoint wave holds 64 points (one per lane) and sweeps a run of
 // strip-rows: the hologram is cut into strips of kAdjCols columns, and the
@@ -194,7 +184,7 @@ struct Plan {
   bool comp_xtab;  // the compensated forward has its column table
   int32_t f64_chunk, f64_slices;  // FP64 forward: points per chunk (0 slices: the direct kernel)
   int32_t fwd_planes;  // partial planes of the compensated forward (0: none of its own)
-  int32_t rec_k, rec_r, rec_s, rec_gx, rec_gy;  // recurrence forward shape, split, grid
+  int32_t rec_k;  // recurrence forward: consecutive pixels per lane
   // adjoint: runs of strip-rows per point group (regions = the most runs the
   // partial buffer holds; the launch may use fewer)
   int32_t nsx, regions, ngroups, adj_kind;
@@ -236,7 +226,9 @@ hipError_t launch_prep_ytab(const float* x, const float* y, const float* z, cons
 hipError_t launch_prep_rtab(const float* x, const float* y, const float* z, const float* a,
                             double pitch, double wavelength, const Plan& p, const Workspace& w,
                             hipStream_t s);
-// The plain forward (plain.hip), and residual = I - target with a target.
+hipError_t launch_residual(const float* hologram, const float* target, float* residual,
+                           int64_t count, hipStream_t s);
+// The plain and recurrence forwards, and residual = I - target with a target.
 hipError_t launch_fwd_plain(const Plan& p, const float* x, const float* y, const float* z,
                             const float* a, double pitch, double wavelength, float* out,
                             const float* target, float* residual, hipStream_t s);
@@ -244,10 +236,9 @@ hipError_t launch_fwd_plain(const Plan& p, const float* x, const float* y, const
 // writes residual = out - target in its store.
 hipError_t launch_fwd_comp(const Plan& p, const Workspace& w, float* out, hipStream_t s,
                            const float* target = nullptr, float* residual = nullptr);
-// residual = hologram - target over count elements (the other forwards).
-hipError_t launch_residual(const float* hologram, const float* target, float* residual,
-                           int64_t count, hipStream_t s);
-hipError_t launch_fwd_rec(const Plan& p, const Workspace& w, float* out, hipStream_t s);
+hipError_t launch_fwd_rec(const Plan& p, const float* x, const float* y, const float* z,
+                          const float* a, double pitch, double wavelength, float* out,
+                          const float* target, float* residual, hipStream_t s);
 hipError_t launch_fwd_f64(const Plan& p, const Workspace& w, double* out, hipStream_t s);
 hipError_t launch_pad_g(const Plan& p, const float* g, float* gpad, hipStream_t s);
 // Operand formats of the matrix-core contractions (contract.h):

@@ -1,142 +1,18 @@
-// Forward kernels: the direct point-source sum of Eq. (1) (Section 1); the plain
-// form is in plain.hip, the contractions in contract_fwd.hip and contract_f64.hip.
+// Direct forward kernels: the compensated sum of Eq. (1) (Section 1) of a few
+// points, and the FP64 one where the contraction's tables have no room.  The plain
+// form is in plain.hip, Eq. (2) in recurrence.hip, the contractions in
+// contract_fwd.hip and contract_f64.hip.
 //
-// Work mapping: one hologram column per lane.  The compensated FP32
-// kernel gives lane l of a wave column x0 + l and a few consecutive rows, so a
-// wave writes fully coalesced 256-byte row segments, and every point record
-// is read once per wave through scalar loads (the loop index is
-// wave-uniform), i.e. broadcast to all 64 lanes from SGPRs.  Points are
-// unrolled a group at a time so the scalar loads of the next points are in
-// flight while the current ones are used.  The recurrence kernel gives a lane
-// K consecutive columns of R rows instead (Eq. (2) steps along x), and the
-// FP64 reference one pixel per lane.
+// Work mapping: one hologram column per lane.  The compensated kernel gives lane l
+// of a wave column x0 + l and a few consecutive rows, so a wave writes fully
+// coalesced 256-byte row segments; the FP64 one has one pixel per lane and reads
+// the points through scalar loads.
 #include "cgh_internal.h"
 #include "phase.h"
 
 namespace cgh {
 
 namespace {
-
-// Recurrence FP32, Eq. (2) (Section 2.1): along a row the phase of pixel
-// x_h + n follows from two additions, Gamma_n = Gamma_{n-1} + delta_{n-1} and
-// delta_n = delta_{n-1} + Delta, from Gamma_0 = P r^2 at x_h,
-// delta_0 = P (2 (x_h - x_j) + 1) and Delta = 2 P (here in revolutions, P ->
-// Prev).  Lane l covers the K consecutive pixels x0 + K l ... x0 + K l + K - 1
-// of R rows (the paper's work-item covers eight consecutive pixels of one
-// row).  delta and Delta depend on the column only, so the lane's R rows
-// share them: per point the lane forms dx, delta_0 and Delta once and
-// Gamma_0 = fract(Prev r^2) (the plain phase) once per row, and per
-// interaction the recurrence costs one add for Gamma (plus 1/R of an add for
-// delta) before the native cosine and the accumulate.  Gamma_0 is in [0, 1)
-// and delta_0, Delta are reduced mod 1 (exactly; cos is 1-periodic in
-// revolutions), so |Gamma_n| < 1 + n (1 + n) stays well inside the cosine's
-// exact-reduction range without a fract per step.  Points are read four at a
-// time through scalar loads (the paper unrolls four points per iteration),
-// one group ahead of their use.
-//
-// S > 1 splits the points of a workgroup's pixels over S groups of kRecWaves
-// waves (point subset s = [s npad / S, (s + 1) npad / S)): more waves per SIMD
-// for the same pixels, when the hologram is too small to give every SIMD
-// several.  Groups 1 .. S-1 leave their sums in LDS and group 0 adds them in
-// group order and stores (deterministic).
-template <int K, int R, int S>
-__global__ __launch_bounds__(kRecThreads * S) void fwd_rec_kernel(const float4* __restrict__ rec,
-                                                                  int npad, int nx, int ny,
-                                                                  float* __restrict__ out) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int wave = wave_all % kRecWaves;  // rows
-  const int part = wave_all / kRecWaves;  // point subset
-  // Row blocks run along the grid's x dimension (up to 2^20 / 4 of them),
-  // column blocks along y.
-  const unsigned tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
-  const int by = (int)(tile % gridDim.x), bx = (int)(tile / gridDim.x);
-  const int x0 = (bx * kWave + lane) * K;
-  const int y0 = (by * kRecWaves + wave) * R;
-  const float xh = (float)x0;
-  float acc[R][K];
-#pragma unroll
-  for (int i = 0; i < R; ++i)
-#pragma unroll
-    for (int n = 0; n < K; ++n) acc[i][n] = 0.0f;
-
-  auto point = [&](const float4& r) {
-    const float dx = xh - r.x;
-    const float dx2 = dx * dx;
-    float d = fract(r.z * __builtin_fmaf(2.0f, dx, 1.0f));
-    const float D = fract(r.z + r.z);
-    float g[R];
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const float dy = (float)(y0 + i) - r.y;
-      g[i] = fract(r.z * __builtin_fmaf(dy, dy, dx2));
-    }
-#pragma unroll
-    for (int n = 0; n < K; ++n) {
-#pragma unroll
-      for (int i = 0; i < R; ++i) acc[i][n] = __builtin_fmaf(r.w, cos_rev(g[i]), acc[i][n]);
-      if (n + 1 < K) {
-#pragma unroll
-        for (int i = 0; i < R; ++i) g[i] += d;
-        d += D;
-      }
-    }
-  };
-  // Two ping-pong groups of records in SGPRs; the next group's loads are
-  // issued after the first point of the current one (whose use waits for
-  // every outstanding scalar load), so the other points cover their latency.
-  // The last group of the subset re-reads itself (in bounds).
-  auto load = [&](int j, float4* dst) {
-#pragma unroll
-    for (int u = 0; u < kRecUnroll; ++u) dst[u] = rec[j + u];
-  };
-  auto group = [&](int j, const float4* cur, float4* nxt, int jend) {
-    point(cur[0]);
-    __builtin_amdgcn_sched_barrier(0);
-    load(min(j + kRecUnroll, jend - kRecUnroll), nxt);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 1; u < kRecUnroll; ++u) point(cur[u]);
-  };
-  const int jbeg = part * (npad / S), jend = jbeg + npad / S;
-  float4 A[kRecUnroll], B[kRecUnroll];
-  load(jbeg, A);
-  for (int j = jbeg; j < jend; j += 2 * kRecUnroll) {
-    group(j, A, B, jend);
-    group(j + kRecUnroll, B, A, jend);
-  }
-  if constexpr (S > 1) {
-    // [subset - 1][element][thread of the group]: consecutive lanes hit
-    // consecutive words.
-    constexpr int kGroupThreads = kRecThreads;
-    __shared__ float part_sums[(S - 1) * R * K * kGroupThreads];
-    const int t = wave * kWave + lane;
-    if (part > 0) {
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int n = 0; n < K; ++n)
-          part_sums[((part - 1) * R * K + i * K + n) * kGroupThreads + t] = acc[i][n];
-    }
-    __syncthreads();
-    if (part > 0) return;
-#pragma unroll
-    for (int q = 1; q < S; ++q)
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int n = 0; n < K; ++n)
-          acc[i][n] += part_sums[((q - 1) * R * K + i * K + n) * kGroupThreads + t];
-  }
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    if (y0 + i >= ny) continue;
-    float* row = out + (int64_t)(y0 + i) * nx;
-#pragma unroll
-    for (int n = 0; n < K; ++n)
-      if (x0 + n < nx) row[x0 + n] = acc[i][n];
-  }
-}
 
 // Compensated FP32: the phase separates exactly as X_j(x_h) + Y_j(y_h) with
 // X_j(x_h) = Prev (x_h - x_j)^2 and Y_j(y_h) = Prev (y_h - y_j)^2.  Each part
@@ -292,8 +168,7 @@ __global__ __launch_bounds__(kCompThreads) void fwd_comp_inline_residual_kernel(
   fwd_comp_body<false, true>(xrec, nullptr, amp, ytab, npad, nx, ny, out, tgt, res);
 }
 
-// The residual G = I - T of a finished hologram, for the forwards without a
-// fused one.
+// The residual G = I - T of an empty sum.
 __global__ __launch_bounds__(256) void residual_kernel(const float* __restrict__ I,
                                                        const float* __restrict__ T,
                                                        float* __restrict__ G, int64_t count) {
@@ -323,36 +198,6 @@ __global__ __launch_bounds__(256) void fwd_f64_kernel(const double4* __restrict_
 }
 
 }  // namespace
-
-namespace {
-
-template <int K, int R>
-hipError_t launch_rec(const Plan& p, const Workspace& w, float* out, hipStream_t s) {
-  if (p.rec_s == 2)
-    hipLaunchKernelGGL((fwd_rec_kernel<K, R, 2>), dim3(p.rec_gy, p.rec_gx), dim3(kRecThreads * 2),
-                       0, s, (const float4*)w.plain, (int)p.npad, p.nx, p.ny, out);
-  else
-    hipLaunchKernelGGL((fwd_rec_kernel<K, R, 1>), dim3(p.rec_gy, p.rec_gx), dim3(kRecThreads), 0,
-                       s, (const float4*)w.plain, (int)p.npad, p.nx, p.ny, out);
-  return hipGetLastError();
-}
-
-}  // namespace
-
-hipError_t launch_fwd_rec(const Plan& p, const Workspace& w, float* out, hipStream_t s) {
-  switch (p.rec_k * 10 + p.rec_r) {
-    case 41: return launch_rec<4, 1>(p, w, out, s);
-    case 42: return launch_rec<4, 2>(p, w, out, s);
-    case 44: return launch_rec<4, 4>(p, w, out, s);
-    case 61: return launch_rec<6, 1>(p, w, out, s);
-    case 62: return launch_rec<6, 2>(p, w, out, s);
-    case 64: return launch_rec<6, 4>(p, w, out, s);
-    case 81: return launch_rec<8, 1>(p, w, out, s);
-    case 82: return launch_rec<8, 2>(p, w, out, s);
-    case 84: return launch_rec<8, 4>(p, w, out, s);
-    default: return hipErrorInvalidValue;
-  }
-}
 
 hipError_t launch_fwd_comp(const Plan& p, const Workspace& w, float* out, hipStream_t s,
                            const float* target, float* residual) {

@@ -1,0 +1,187 @@
+// Forward by the recurrence of Eq. (2) (Section 2.1): along a row the phase of
+// pixel x_h + n follows from two additions, Gamma_n = Gamma_{n-1} + delta_{n-1}
+// and delta_n = delta_{n-1} + Delta, from Gamma_0 = P r^2 at x_h, delta_0 = P (2
+// (x_h - x_j) + 1) and Delta = 2 P (here in revolutions, P -> Prev).  Lane l
+// covers the K consecutive pixels x0 + K l ... x0 + K l + K - 1 of kRecRows rows
+// (the paper's work-item covers eight consecutive pixels of one row).  delta and
+// Delta depend on the column only, so the lane's rows share them: per point the
+// lane forms dx and delta_0 once and Gamma_0 = fract(Prev r^2) (the plain phase)
+// once per row, and per interaction the recurrence costs one add for Gamma (and a
+// quarter of one for delta) before the native cosine and the accumulate.
+// Gamma_0 is in [0, 1) and delta_0, Delta are reduced mod 1 (exactly; cos is
+// 1-periodic in revolutions), so |Gamma_n| < 1 + n (1 + n) stays well inside the
+// cosine's exact-reduction range without a fract per step.
+//
+// The vector ALU bounds it: an add, the cosine and an fma are 3.7 clocks of a CU
+// for 64 interactions when all operands are VGPRs and 4.0 when the amplitude is
+// an SGPR, and the seeds add 0.6 at K = 8.  So the points {x, Prev, A, Delta} and the
+// rows' y_h - y_j are staged in LDS per tile of kTile points and reach the lanes
+// as broadcasts.  The eight waves of a workgroup share the pixels and take eight
+// points of every tile each, since a lane's K x R pixels leave few waves (1024 of
+// 64 K x 4 at 1920x1024, for 8192 places); their sums are added in a fixed order.
+// 1920x1080, N = 8192: 2345 us a call, where records in SGPRs and two groups of
+// waves took 2671; 3840x2160, N = 1024: 1046 and 1166; 333x197, N = 700: 18 and 45.
+#include <type_traits>
+
+#include "cgh_internal.h"
+#include "phase.h"
+
+namespace cgh {
+
+namespace {
+
+constexpr int kParts = 8;  // waves of a workgroup, each with its part of the points
+
+// A point's y_h - y_j at a lane's rows.
+template <int R>
+struct alignas(4 * R) Dy {
+  float v[R];
+};
+
+template <int K, int R>
+__global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
+    const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
+    const float* __restrict__ a, int64_t n, int npad, double pitch, double wavelength, int nx,
+    int ny, unsigned tiles_x, float* __restrict__ out, const float* __restrict__ tgt,
+    float* __restrict__ res) {
+  constexpr int kMine = kTile / kParts;
+  __shared__ float4 recs[2][kTile];  // {x, Prev, A, Delta}
+  __shared__ Dy<R> dys[2][kTile];
+  // The upper half of the parts leaves its sums for the lower half, and so on.
+  __shared__ float sums[kParts / 2 * R * K * kWave];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int x0 = ((int)(tile % tiles_x) * kWave + lane) * K;
+  const int y0 = (int)(tile / tiles_x) * R;
+  const float xh = (float)x0;
+
+  // The tile's stage, by the first wave: lane l has point l.
+  float px = 0.0f, py = 0.0f, pz = 1.0f, pa = 0.0f;
+  auto load = [&](int t) {
+    const int64_t j = (int64_t)t * kTile + lane;
+    const bool in = part == 0 && j < n;
+    px = in ? x[j] : 0.0f;
+    py = in ? y[j] : 0.0f;
+    pz = in ? z[j] : 1.0f;
+    pa = in ? a[j] : 0.0f;
+  };
+  auto store = [&](int b) {
+    if (part != 0) return;
+    const float prev = (float)((pitch * pitch) / (2.0 * wavelength * (double)pz));
+    recs[b][lane] = make_float4(px, prev, pa, fract(prev + prev));
+    Dy<R> dy;
+#pragma unroll
+    for (int i = 0; i < R; ++i) dy.v[i] = (float)(y0 + i) - py;
+    dys[b][lane] = dy;
+  };
+
+  float acc[R][K];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int k = 0; k < K; ++k) acc[i][k] = 0.0f;
+  const int ntiles = npad / kTile;
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int t = 0; t < ntiles; ++t) {
+    const int b = t & 1;
+    if (t + 1 < ntiles) load(t + 1);
+#pragma unroll 2
+    for (int q = 0; q < kMine; ++q) {
+      const int p = part * kMine + q;
+      const float4 r = recs[b][p];
+      const Dy<R> dy = dys[b][p];
+      const float dx = xh - r.x;
+      const float dx2 = dx * dx;
+      float d = fract(r.y * __builtin_fmaf(2.0f, dx, 1.0f));
+      float g[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+        g[i] = fract(r.y * __builtin_fmaf(dy.v[i], dy.v[i], dx2));
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) acc[i][k] = __builtin_fmaf(r.z, cos_rev(g[i]), acc[i][k]);
+        if (k + 1 < K) {
+#pragma unroll
+          for (int i = 0; i < R; ++i) g[i] += d;
+          d += r.w;
+        }
+      }
+    }
+    if (t + 1 < ntiles) store(b ^ 1);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int left = kParts / 2; left >= 1; left /= 2) {
+    float* at = sums + (part % left) * R * K * kWave + lane;
+    if (part >= left && part < 2 * left) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < K; ++k) at[(i * K + k) * kWave] = acc[i][k];
+    }
+    __syncthreads();
+    if (part < left) {
+#pragma unroll
+      for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int k = 0; k < K; ++k) acc[i][k] += at[(i * K + k) * kWave];
+    }
+    __syncthreads();
+  }
+  if (part > 0) return;
+#pragma unroll
+  for (int i = 0; i < R; ++i) {
+    if (y0 + i >= ny) continue;
+    const int64_t row = (int64_t)(y0 + i) * nx;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (x0 + k >= nx) continue;
+      out[row + x0 + k] = acc[i][k];
+      if (res) res[row + x0 + k] = acc[i][k] - tgt[row + x0 + k];
+    }
+  }
+}
+
+template <int K, int R>
+hipError_t launch(const Plan& p, const float* x, const float* y, const float* z, const float* a,
+                  double pitch, double wavelength, float* out, const float* target,
+                  float* residual, hipStream_t s) {
+  constexpr int kRows = R;
+  const int64_t tiles_x = ((int64_t)p.nx + kWave * K - 1) / (kWave * K);
+  const int64_t tiles = tiles_x * (((int64_t)p.ny + kRows - 1) / kRows);
+  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((fwd_rec_kernel<K, R>), dim3((unsigned)tiles), dim3(kParts * kWave), 0, s,
+                     x, y, z, a, p.n, (int)p.npad, pitch, wavelength, p.nx, p.ny, (unsigned)tiles_x,
+                     out, target, residual);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_fwd_rec(const Plan& p, const float* x, const float* y, const float* z,
+                          const float* a, double pitch, double wavelength, float* out,
+                          const float* target, float* residual, hipStream_t s) {
+  auto go = [&](auto f) { return f(p, x, y, z, a, pitch, wavelength, out, target, residual, s); };
+  auto shape = [&](auto k) {
+    constexpr int K = decltype(k)::value;
+    // Waves of 64 K x 4 pixels: few of them take fewer rows per lane, so that there
+    // are more waves, at more seeds per pixel.  (us at 4, 2 and 1 rows: 160x245, N =
+    // 2612: 107, 59, 40; 640x480, N = 512: 34, 33, 35; 1865x300, N = 2246: 238, 193,
+    // 211; 1024x1024, N = 4096: 524, 570, 595.)
+    const int64_t waves = ((int64_t)p.nx + kWave * K - 1) / (kWave * K) * (((int64_t)p.ny + 3) / 4);
+    // (with so few K is 4)
+    if constexpr (K == 4)
+      if (waves <= 80) return go(launch<K, 1>);
+    if (waves <= 430) return go(launch<K, 2>);
+    return go(launch<K, 4>);
+  };
+  if (p.rec_k == 4) return shape(std::integral_constant<int, 4>{});
+  if (p.rec_k == 6) return shape(std::integral_constant<int, 6>{});
+  return shape(std::integral_constant<int, 8>{});
+}
+
+}  // namespace cgh

@@ -223,6 +223,36 @@ def test_f64_non_finite_amplitudes():
     assert torch.isnan(B.forward_f64(x, y, z, a, nx, ny)).all()
 
 
+# The recurrence forward: each K (4, 6 and 8 pixels) with each of 1, 2 and 4 rows
+# per lane, tiles of 64 points and parts of 8 with their remainders.
+@pytest.mark.parametrize("shape", [(1, 1, 1), (70, 50, 9), (333, 197, 65), (3840, 2160, 7),
+                                   (3520, 13, 63), (640, 480, 129), (1640, 1333, 33),
+                                   (2368, 16, 64), (2480, 184, 100), (1920, 1024, 70)])
+def test_recurrence_forward_shapes(oracle_mod, shape):
+    """The plain phase's five roundings at the first pixel of a lane, and those of
+    seven steps of Gamma and delta (each below 64 revolutions)."""
+    nx, ny, n = shape
+    dev = device()
+    say("recurrence forward", shape)
+    c = W.random_cloud(1600 + n, n, nx, ny, zlo=ZLO, zhi=1.0, alo=-1.0, ahi=1.0, margin=20)
+    x, y, z, a = to_dev(c, dev)
+    T = torch.from_numpy(np.random.default_rng(n).standard_normal((ny, nx)).astype(np.float32))
+    T = T.to(dev)
+    I, G = B.forward_residual(x, y, z, a, T, nx, ny, variant="recurrence")
+    J = B.forward(x, y, z, a, nx, ny, variant="recurrence")
+    assert torch.equal(I, J) and torch.equal(G, I - T)
+    px, py = W.sample_pixels(1601, nx, ny, 3000)
+    ref = oracle_mod.forward_at(*c.astuple(), nx, ny, px, py, threads=0)
+    err = max_err_frac(I.cpu().numpy()[py, px], ref, c)
+    prev = W.PITCH ** 2 / (2 * W.WAVELENGTH * ZLO)
+    revs = 5 * prev * ((nx + 20) ** 2 + (ny + 20) ** 2)        # Gamma_0
+    revs += 7 * 3 * prev * 2 * (nx + 20)                       # delta_0, seven times
+    revs += 2 * 7 * 64                                         # the steps' additions
+    bar = 2 * np.pi * 2.0 ** -24 * revs + 2.5e-7 + 2.0 ** -24 * (n + 8)
+    say("  max|dI|/sum|A| = %.3e, bar %.3e" % (err, bar))
+    assert err <= bar
+
+
 # The plain forward: rows per lane, groups that split the points and tiles of 64
 # points with their remainders (each of the rule's three forms); phases within and
 # beyond the cosine's exact range of 256 revolutions (3840 columns reach 2500).
