@@ -8,8 +8,8 @@ yields dL/dx, dL/dy, dL/dz, dL/dA of L = 0.5 ||I - T||^2.  Inputs are seeded
 synthetic clouds already resident in HBM.
 
 Prints ONE JSON line: throughput in G point-pixel interactions per second
-(N * Nx * Ny / step time) of the compensated variant (the paper's method:
-one native cosine per interaction), the roofline record of the dominant
+(N * Nx * Ny / step time) of the compensated variant (the paper's sum at full
+FP32 accuracy), the roofline record of the dominant
 kernel (the adjoint) from HIP events recorded around it, accuracy against the
 FP64 GPU forward, and the FP64 CPU oracle's rate on a bounded sample of the
 same workload (the cpu_baseline leg, the only part that touches the oracle).
@@ -43,7 +43,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# Roofline of the direct kernels, which are bound by the vector ALU.  MI355X's
+# Roofline of the direct kernels (plain, recurrence, and compensated where it
+# takes them), which are bound by the vector ALU.  MI355X's
 # FP32 vector peak, 157.3 TFLOP/s, is 256 CUs x 2.4 GHz x 128 FP32 lanes per
 # clock (x 2 flops per FMA): 7.86e13 FP32 lane-operations per second.  Every
 # FP32 operation of an interaction takes one slot of that rate and every
@@ -72,7 +73,9 @@ TRANS_OPS = {"fwd_plain": 1, "fwd_compensated": 1, "fwd_recurrence": 1,
 SLOTS = {k: FP32_OPS[k] + TRANS_SLOTS * TRANS_OPS[k] for k in FP32_OPS}
 # The practical ceiling: each kernel's per-interaction instruction mix run
 # alone by the probe (issue-bound, 8 resident waves per SIMD, operands where
-# the kernel holds them), in CU clocks per 64 interactions.  The recurrence
+# the probe holds them), in CU clocks per 64 interactions.  The plain and
+# recurrence forwards' mixes read the point from SGPRs, which their kernels no
+# longer do (the fastest issue a few per cent above these mixes).  The recurrence
 # forward issues Gamma += delta, the cosine and an FMA with A from an SGPR,
 # plus one add per 4 interactions (delta += Delta, shared by 4 rows).  The recurrence
 # adjoint issues an add of two VGPRs, sine, cosine and three FMAs with G from
@@ -81,16 +84,16 @@ SLOTS = {k: FP32_OPS[k] + TRANS_SLOTS * TRANS_OPS[k] for k in FP32_OPS}
 MIX_CLOCKS = {"fwd_plain": 6.116, "fwd_compensated": 3.685, "fwd_recurrence": 3.966,
               "adj_plain": 9.331, "adj_compensated": 4.033, "adj_recurrence": 7.839}
 CU_CLOCKS_PER_S = 256 * 2.4e9
-# The separable variant is a different algorithm, bound by the FP32 matrix
-# cores (dense MFMA FP32 peak 157.3 TFLOP/s): the forward is one GEMM of
-# 2 x (2N) flops per pixel (4 flops per interaction), the adjoint two
-# (8 flops per interaction).
-# The half-precision separable variants run the same GEMMs on the fp16/bf16
-# matrix cores (dense peak 2.5 PFLOP/s); f16x3 issues three MFMAs per product
-# (hi*hi, hi*lo, lo*hi), so its matrix-core work is three times the flops.
+# The compensated and separable variants are contractions, bound by the matrix
+# cores: the forward is one of 2 x (2N) flops per pixel (4 flops per
+# interaction), the adjoint two (8 flops per interaction).  The FP32 form runs on
+# the FP32 matrix cores (dense peak 157.3 TFLOP/s), the others on the fp16/bf16
+# ones (dense peak 2.5 PFLOP/s); the compensated variant and f16x3 issue three
+# MFMAs per product (hi*hi, hi*lo, lo*hi), so their matrix-core work is three
+# times the flops.
 PEAK_MFMA_F32 = 157.3e12
 PEAK_MFMA_F16 = 2.5e15
-MFMA_FLOPS = {"separable": (4, 8, PEAK_MFMA_F32), "separable_f16x3": (12, 24, PEAK_MFMA_F16),
+MFMA_FLOPS = {"compensated": (12, 24, PEAK_MFMA_F16), "separable": (4, 8, PEAK_MFMA_F32), "separable_f16x3": (12, 24, PEAK_MFMA_F16),
               "separable_f16": (4, 8, PEAK_MFMA_F16), "separable_bf16": (4, 8, PEAK_MFMA_F16)}
 ALL_VARIANTS = ("compensated", "plain", "recurrence", "separable", "separable_f16x3",
                 "separable_f16", "separable_bf16")
@@ -98,13 +101,19 @@ ALL_VARIANTS = ("compensated", "plain", "recurrence", "separable", "separable_f1
 
 def peak_interactions(key):
     """Roofline peak (interactions/s) of a kernel ("fwd_<variant>" or
-    "adj_<variant>"): VALU issue for the direct variants, the matrix cores of
-    the GEMM operand type for the separable ones."""
+    "adj_<variant>"): VALU issue for the plain and recurrence variants, the matrix
+    cores of the operand type for the contractions."""
     op, variant = key.split("_", 1)
     if variant in MFMA_FLOPS:
         f_fwd, f_adj, peak = MFMA_FLOPS[variant]
         return peak / (f_fwd if op == "fwd" else f_adj)
     return PEAK_FP32_LANE_OPS / SLOTS[key]
+
+
+def mix_of(key):
+    """mix_interactions() of a kernel that a step of its variant launches: None
+    for the contractions."""
+    return None if key.split("_", 1)[1] in MFMA_FLOPS else mix_interactions(key)
 
 
 def mix_interactions(key):
@@ -182,13 +191,18 @@ def measured_traffic(kernel, path=None, key="traffic_bytes"):
     return rec.get(key)
 
 
-# Device-code names of the direct adjoint kernels (the roofline kernel).
-ADJ_KERNEL_NAME = {"plain": "adj_partial_kernel<0>", "compensated": "adj_partial_kernel<1>",
-                   "recurrence": "adj_partial_kernel<2>"}
+# Device-code names of the adjoint kernels (the roofline kernel).
+ADJ_KERNEL_NAME = {"plain": "adj_partial_kernel<0>", "recurrence": "adj_partial_kernel<2>",
+                   "compensated": "contract_adj_kernel<2, true>",
+                   "separable": "contract_adj_kernel<3, true>",
+                   "separable_f16x3": "contract_adj_kernel<2, true>",
+                   "separable_f16": "contract_adj_kernel<0, true>",
+                   "separable_bf16": "contract_adj_kernel<1, true>"}
 FWD_KERNEL = {"plain": 0, "compensated": 1, "recurrence": 7}
 ADJ_KERNEL = {"plain": 3, "compensated": 4, "recurrence": 8}
 for _v in MFMA_FLOPS:
-    FWD_KERNEL[_v], ADJ_KERNEL[_v] = 5, 6
+    if _v != "compensated":
+        FWD_KERNEL[_v], ADJ_KERNEL[_v] = 5, 6
 
 
 def _launch_stats(prefix, each):
@@ -239,11 +253,11 @@ def timed_steps(step, steps, torch):
     return e0.elapsed_time(e1) / steps, wall
 
 
-# The separable variants' contractions at the headline workload (1920x1024,
-# N = 1024: 2N = 2048 table columns), as (name, M, N, K) of C[M][N] =
-# sum_k A(m, k) B(n, k), and the library kernel each one is compared with:
-# this library's GEMM instantiation per operand format (fp16 hi/lo as one
-# plain fp16 GEMM of three times the depth: [Ah Ah Al] . [Bh Bl Bh]).
+# The contractions of the headline workload (1920x1024, N = 1024: 2N = 2048
+# table columns) as library products, (name, M, N, K) of C[M][N] = sum_k A(m, k)
+# B(n, k), and the names of the tiled kernels that they were compared with when
+# the separable variants were products of operand tables (fp16 hi/lo as one plain
+# fp16 GEMM of three times the depth: [Ah Ah Al] . [Bh Bl Bh]).
 SEP_GEMMS = (("forward I = Y X^T", 1024, 1920, 2048, 0),
              ("adjoint U, K = rows", 2048, 1920, 1024, 1),
              ("adjoint P, K = columns", 2048, 1024, 1920, 2))
@@ -419,11 +433,9 @@ def main():
             "adj_roofline_frac": (inter / (r["adj_kernel_ms"] * 1e-3)) /
                                  peak_interactions("adj_" + variant),
             "fwd_frac_of_mix": ((inter / (r["fwd_kernel_ms"] * 1e-3)) /
-                                mix_interactions("fwd_" + variant)
-                                if mix_interactions("fwd_" + variant) else None),
+                                mix_of("fwd_" + variant) if mix_of("fwd_" + variant) else None),
             "adj_frac_of_mix": ((inter / (r["adj_kernel_ms"] * 1e-3)) /
-                                mix_interactions("adj_" + variant)
-                                if mix_interactions("adj_" + variant) else None),
+                                mix_of("adj_" + variant) if mix_of("adj_" + variant) else None),
             "max_err_vs_fp64_over_sum_abs_a": errs[variant],
             "adj_rel_l2_vs_compensated": adj_errs[variant],
         }
@@ -452,7 +464,7 @@ def main():
         },
         "roofline": {
             "kernel": adj_key,
-            "bound": "mfma" if args.variant.startswith("separable") else "alu",
+            "bound": "mfma" if args.variant in MFMA_FLOPS else "alu",
             "achieved": achieved,
             "peak": peak,
             "unit": "Ginteraction/s",
@@ -471,17 +483,20 @@ def main():
                 "128 lanes); per interaction %d FP32 ops + %d transcendentals x %d slots "
                 "(quarter rate) = %d slots" % (FP32_OPS[adj_key], TRANS_OPS[adj_key],
                                                 TRANS_SLOTS, SLOTS[adj_key])
-                if adj_key in SLOTS else "matrix-core peak of the GEMM operand type"),
-            "slots_per_interaction": SLOTS.get(adj_key),
-            "trans_slots": TRANS_SLOTS if adj_key in SLOTS else None,
+                if args.variant not in MFMA_FLOPS else
+                "dense matrix-core peak of the operand type (%.4g FLOP/s), %d flops per "
+                "interaction issued" % (MFMA_FLOPS[args.variant][2],
+                                        MFMA_FLOPS[args.variant][1])),
+            "slots_per_interaction": (SLOTS[adj_key] if args.variant not in MFMA_FLOPS
+                                      else None),
+            "trans_slots": TRANS_SLOTS if args.variant not in MFMA_FLOPS else None,
             # the same instruction mix run alone on this chip (machine probe)
-            "mix_peak": (mix_interactions(adj_key) / 1e9 if mix_interactions(adj_key)
-                         else None),
-            "frac_of_mix": (achieved * 1e9 / mix_interactions(adj_key)
-                            if mix_interactions(adj_key) else None),
+            "mix_peak": mix_of(adj_key) / 1e9 if mix_of(adj_key) else None,
+            "frac_of_mix": achieved * 1e9 / mix_of(adj_key) if mix_of(adj_key) else None,
             "flops_per_interaction": (MFMA_FLOPS[args.variant][1]
                                       if args.variant in MFMA_FLOPS else None),
-            "peak_lane_ops_per_s": PEAK_FP32_LANE_OPS if adj_key in SLOTS else None,
+            "peak_lane_ops_per_s": (PEAK_FP32_LANE_OPS if args.variant not in MFMA_FLOPS
+                                    else None),
             "kernel_ms": adj_ms,
         },
         "variants": {v: kernel_summary(v) for v in [args.variant] + others},
@@ -805,10 +820,11 @@ def report_workload(args):
             "fwd_roofline_frac": inter / (fms * 1e-3) / peak_interactions("fwd_" + variant),
             "adj_kernel_ms": ams, "adj_gpps": inter / (ams * 1e-3) / 1e9,
             "adj_roofline_frac": inter / (ams * 1e-3) / peak_interactions("adj_" + variant),
-            "fwd_frac_of_mix": (inter / (fms * 1e-3) / mix_interactions("fwd_" + variant)
-                                if mix_interactions("fwd_" + variant) else None),
-            "adj_frac_of_mix": (inter / (ams * 1e-3) / mix_interactions("adj_" + variant)
-                                if mix_interactions("adj_" + variant) else None),
+            "fwd_frac_of_mix": (inter / (fms * 1e-3) / mix_of("fwd_" + variant)
+                                if mix_of("fwd_" + variant) else None),
+            "adj_frac_of_mix": (inter / (ams * 1e-3) / mix_of("adj_" + variant)
+                                if mix_of("adj_" + variant) else None),
+            "contraction": variant in MFMA_FLOPS,
             "max_err_vs_fp64_over_sum_abs_a": err,
         }
     if args.workload == "fit4k" and args.fit_iters > 0:
@@ -936,12 +952,11 @@ def summarize_stats(root):
              "The run times every variant of the step (50 timed + 5 warm-up steps each, one "
              "graph capture and 50 replays per variant, the accuracy checks and the CPU "
              "baseline).  Kernel "
-             "names: fwd_comp_residual_kernel (the step's forward, which also writes G = I - T) "
-             "/ adj_partial_kernel<1> (compensated), fwd_plain_kernel / "
-             "adj_partial_kernel<0> (plain), fwd_rec_kernel<K, R> / adj_partial_kernel<2> "
-             "(recurrence), gemm_f32_kernel (separable FP32), gemm_half_kernel<format, fold> "
-             "(format 2 = fp16 hi/lo, 0 = fp16, 1 = bf16; fold 0 = forward, 1 and 2 = the "
-             "adjoint contractions).", "", "Durations in microseconds.", "",
+             "names: contract_fwd_kernel<format, shape, ...> (the forward, which also writes G = "
+             "I - T) and contract_adj_kernel<format, tables> with their tables kernels (format "
+             "2 = fp16 hi/lo: compensated and separable_f16x3, 0 = fp16, 1 = bf16, 3 = FP32: "
+             "separable), fwd_plain_kernel<R, S> / adj_partial_kernel<0> (plain), "
+             "fwd_rec_kernel<K, R> / adj_partial_kernel<2> (recurrence).", "", "Durations in microseconds.", "",
              "| kernel | calls | avg us | min us | max us | share |", "|---|---|---|---|---|---|"]
     for r in sorted(rows, key=lambda r: -float(r["Percentage"])):
         lines.append("| %s | %s | %.1f | %.1f | %.1f | %.1f%% |" % (
@@ -969,9 +984,13 @@ def summarize_stats(root):
         traced = {_kernel_short(r["Name"]): float(r["AverageNs"]) / 1e3 for r in rows}
         pairs = [("fwd_comp_residual_kernel", "compensated", "fwd"),
                  ("adj_partial_kernel<1>", "compensated", "adj"),
-                 ("fwd_plain_kernel", "plain", "fwd"), ("adj_partial_kernel<0>", "plain", "adj"),
-                 ("fwd_rec_kernel<8, 4, 2>", "recurrence", "fwd"),
-                 ("adj_partial_kernel<2>", "recurrence", "adj")]
+                 ("fwd_plain_kernel<4, 4>", "plain", "fwd"),
+                 ("adj_partial_kernel<0>", "plain", "adj"),
+                 ("fwd_rec_kernel<8, 4>", "recurrence", "fwd"),
+                 ("adj_partial_kernel<2>", "recurrence", "adj"),
+                 ("contract_adj_kernel<3, true>", "separable", "adj"),
+                 ("contract_adj_kernel<0, true>", "separable_f16", "adj"),
+                 ("contract_adj_kernel<1, true>", "separable_bf16", "adj")]
         lines += ["", "Agreement with the HIP events that bench.py records around the same kernels "
                   "in the same profiled run (mean of the timed steps' launches; the trace "
                   "average also covers warm-up, graph-replay and accuracy-check launches)"
@@ -1012,30 +1031,26 @@ TRAFFIC_KERNELS = {
     "fwd_comp_residual_kernel": (["forward.hip", "phase.h", "cgh_internal.h"],
                                  "row table 4.19 MB + column table 7.86 MB + amplitudes + "
                                  "hologram 7.86 MB + target 7.86 MB + residual 7.86 MB = 35.6 MB"),
-    "fwd_plain_kernel": (["forward.hip", "phase.h", "cgh_internal.h"],
-                         "records 0.02 MB + hologram 7.86 MB"),
-    "fwd_rec_kernel<8, 4, 2>": (["forward.hip", "phase.h", "cgh_internal.h"],
-                             "records 0.02 MB + hologram 7.86 MB"),
+    "fwd_plain_kernel<4, 4>": (["plain.hip", "phase.h", "cgh_internal.h"],
+                               "inputs 0.02 MB + hologram 7.86 MB + target 7.86 MB + residual "
+                               "7.86 MB"),
+    "fwd_rec_kernel<8, 4>": (["recurrence.hip", "phase.h", "cgh_internal.h"],
+                             "inputs 0.02 MB + hologram 7.86 MB + target 7.86 MB + residual "
+                             "7.86 MB"),
     "prep_kernel": (["prep.hip", "phase.h", "records.h", "cgh_internal.h"],
                     "inputs 0.02 MB + records 0.2 MB (+ f64 records)"),
-    "gemm_f32_kernel<true, true, 0>": (["gemm.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                                       "tables 8.4 + 15.7 MB + split planes (forward)"),
-    "gemm_f32_kernel<false, false, 1>": (["gemm.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                                         "tables 8.4 MB + G 7.86 MB + fold planes 0.5 MB"),
-    "gemm_f32_kernel<false, true, 2>": (["gemm.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                                        "tables 15.7 MB + G 7.86 MB + fold planes 0.5 MB"),
-    "gemm_half_kernel<2, 0>": (["gemm_half.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                               "hi+lo tables 12 MB + split planes (forward)"),
-    "gemm_half_kernel<2, 1>": (["gemm_half.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                               "hi+lo tables 4.2 MB + hi+lo G 7.9 MB + fold planes 0.5 MB"),
-    "gemm_half_kernel<2, 2>": (["gemm_half.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                               "hi+lo tables 7.9 MB + hi+lo G 7.9 MB + fold planes 0.5 MB"),
-    "gemm_half_kernel<0, 0>": (["gemm_half.hip", "fold.h", "phase.h", "cgh_internal.h"],
-                               "fp16 tables 6 MB + split planes (forward)"),
-    "sep_sum_slices_kernel": (["separable.hip", "phase.h", "cgh_internal.h"],
-                              "split planes + hologram 7.86 MB"),
-    "sep_adj_operands_half_kernel<2>": (["separable_half.hip", "phase.h", "cgh_internal.h"],
-                                        "G 7.86 MB in; G, Gt, Xt, Yt hi+lo planes 41 MB out"),
+    "contract_fwd_kernel<2, 2, 4, 1, 8, true, true>": (
+        ["contract_fwd.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
+        "phase tables 4.2 + 7.9 MB + hologram, target and residual 23.6 MB = 35.7 MB"),
+    "contract_fwd_tables_kernel<2>": (
+        ["contract_fwd.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
+        "inputs 0.02 MB + phase tables 4.2 + 7.9 MB = 12.1 MB"),
+    "contract_adj_kernel<2, true>": (
+        ["contract_adj.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
+        "phase tables 4.2 + 7.9 MB + G 7.86 MB + partial planes = 20 MB"),
+    "contract_adj_tables_kernel<2>": (
+        ["contract_adj.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
+        "inputs 0.02 MB + G 7.86 MB + phase tables 4.2 + 7.9 MB = 20 MB"),
 }
 
 
@@ -1104,6 +1119,15 @@ def summarize_traffic(root):
                                   "128B": c["TCC_EA0_RDREQ_128B_sum"]},
                 "read_bytes_sized": sized(c),
                 "traffic_bytes_sized": sized(c) + w_raw * 1024 / wf})
+    # Kernels that this step no longer launches keep the record they have while
+    # their sources are the same.
+    path = os.path.join(PROFILES, "traffic_paper_1920x1024_n1024.json")
+    if os.path.exists(path):
+        with open(path) as f:
+            for k, v in json.load(f)["kernels"].items():
+                if (k in TRAFFIC_KERNELS and k not in kernels
+                        and _sources_hash(v["sources"]) == v["source_sha256_16"]):
+                    kernels[k] = v
     rec = {"workload": "1920x1024 hologram, N=1024 points (bench.py step)",
            "copy_reference_bytes": copy_bytes, "fetch_factor": ff, "write_factor": wf,
            "copy_read_bytes_sized": copy_sized, "kernels": kernels}
@@ -1130,7 +1154,8 @@ def summarize_traffic(root):
               "Counter values are averages over the kernel's dispatches in the run (every "
               "variant of the step).  `traffic_paper_1920x1024_n1024.json` holds the same "
               "figures with a hash of each kernel's sources; bench.py reports the traffic of "
-              "the roofline kernel only while that hash matches.", "",
+              "the roofline kernel only while that hash matches.  A kernel that this step no longer "
+              "launches keeps the record of an earlier run.", "",
               "| kernel | FETCH_SIZE KiB (raw) | WRITE_SIZE KiB (raw) | fetch | write | total | "
               "algorithmic bytes |", "|---|---|---|---|---|---|---|"]
     for k, v in kernels.items():
@@ -1221,8 +1246,8 @@ COUNTER_PASSES = (
 COUNTER_KERNELS = {
     "compensated": {"fwd_comp_residual_kernel": "fwd_compensated",
                     "adj_partial_kernel<1>": "adj_compensated"},
-    "plain": {"fwd_plain_kernel": "fwd_plain", "adj_partial_kernel<0>": "adj_plain"},
-    "recurrence": {"fwd_rec_kernel<8, 4, 2>": "fwd_recurrence",
+    "plain": {"fwd_plain_kernel<4, 4>": "fwd_plain", "adj_partial_kernel<0>": "adj_plain"},
+    "recurrence": {"fwd_rec_kernel<8, 4>": "fwd_recurrence",
                    "adj_partial_kernel<2>": "adj_recurrence"},
 }
 
@@ -1230,19 +1255,17 @@ COUNTER_KERNELS = {
 def summarize_counters(root):
     """Per-interaction VALU, transcendental, SALU, SMEM and LDS instruction
     counts and VALU issue rate of the direct kernels, and matrix-core use of the
-    fp16 hi/lo GEMM, from two counter passes per variant (DIR/<variant>.<pass>)."""
+    contractions, from two counter passes per variant (DIR/<variant>.<pass>)."""
     variants = list(COUNTER_KERNELS) + ["separable_f16x3"]
     data = {}
     for v in variants:
         files = [f for p in (1, 2)
                  for f in _csv_files(os.path.join(root, "%s.%d" % (v, p)), "*counter_collection.csv")]
         data[v] = _counter_means(files)
-    # The fp16 hi/lo GEMM runs as three instantiations per step (forward and
-    # the two adjoint contractions, one dispatch each): average them.
-    half = [c for k, c in data["separable_f16x3"].items() if k.startswith("gemm_half_kernel<2,")]
-    if half:
-        data["separable_f16x3"]["gemm_half_kernel<2>"] = {
-            name: sum(c[name] for c in half) / len(half) for name in half[0]}
+    # Kernels of the f16x3 variant (the compensated variant launches the same) that
+    # issue matrix instructions.
+    matrix = {k: c for k, c in sorted(data["separable_f16x3"].items())
+              if c.get("SQ_INSTS_MFMA", 0) > 0 and "SQ_INSTS_VALU" in c}
     n = HEADLINE_INTERACTIONS
     lines = ["# Hardware counters of the hot kernels, 1920x1024 hologram, N = 1024", "",
              "Two counter passes per variant (rocprofv3 does not split counters over passes), "
@@ -1282,21 +1305,20 @@ def summarize_counters(root):
                 100 * busy,
                 c["SQ_INSTS_SALU"] / c["SQ_INSTS_VALU"], c["SQ_INSTS_SMEM"] / c["SQ_INSTS_VALU"],
                 c["SQ_INSTS_LDS"] / c["SQ_INSTS_VALU"]))
-    g = data["separable_f16x3"].get("gemm_half_kernel<2>")
-    if g is not None:
+    if matrix:
+        lines += ["", "Matrix-core kernels of the separable_f16x3 variant (the compensated variant "
+                  "launches the same), per dispatch:", "",
+                  "| kernel | MFMA instr / dispatch | MFMA busy cycles / MFMA | MFMA busy | LDS "
+                  "instr / MFMA | VALU instr / MFMA |", "|---|---|---|---|---|---|"]
+    for k, g in matrix.items():
         mf = g["SQ_VALU_MFMA_BUSY_CYCLES"] / (1024 * g["GRBM_GUI_ACTIVE"] / 8)
-        lines += ["", "Matrix-core kernel (`gemm_half_kernel<2>`, the fp16 hi/lo GEMM of the "
-                  "separable_f16x3 variant; average over its forward and two adjoint dispatches "
-                  "per step):", "",
-                  "| MFMA instr / dispatch | MFMA busy cycles / MFMA | MFMA busy | LDS instr / MFMA "
-                  "| VALU instr / MFMA |", "|---|---|---|---|---|",
-                  "| %.0f | %.1f | %.0f%% | %.2f | %.2f |" % (
-                      g["SQ_INSTS_MFMA"], g["SQ_VALU_MFMA_BUSY_CYCLES"] / g["SQ_INSTS_MFMA"],
-                      100 * mf, g["SQ_INSTS_LDS"] / g["SQ_INSTS_MFMA"],
-                      g["SQ_INSTS_VALU"] / g["SQ_INSTS_MFMA"])]
+        lines.append("| `%s` | %.0f | %.1f | %.0f%% | %.2f | %.2f |" % (
+            k, g["SQ_INSTS_MFMA"], g["SQ_VALU_MFMA_BUSY_CYCLES"] / g["SQ_INSTS_MFMA"],
+            100 * mf, g["SQ_INSTS_LDS"] / g["SQ_INSTS_MFMA"],
+            g["SQ_INSTS_VALU"] / g["SQ_INSTS_MFMA"]))
     lines += ["", "Raw averages per dispatch:", "", "| kernel | counter | value |", "|---|---|---|"]
     for v in variants:
-        ks = list(COUNTER_KERNELS.get(v, {})) or ["gemm_half_kernel<2>"]
+        ks = list(COUNTER_KERNELS.get(v, {})) or list(matrix)
         for k in ks:
             for name, val in sorted(data[v].get(k, {}).items()):
                 lines.append("| `%s` | %s | %.6g |" % (k, name, val))
@@ -1388,9 +1410,9 @@ def summarize_workloads(root):
                  "--summarize workloads <out>`:", "", "```", cmd, "```", "",
                  "Kernel times are the mean of %d launches (HIP events around the kernel).  "
                  "Errors are max |dI| / sum |A| against the FP64 GPU forward on the full grid.  "
-                 "Roofline fractions: of the FP32 vector peak for the direct variants (slots per "
-                 "interaction as in bench.py), of the matrix-core peak of the GEMM operand type "
-                 "for the separable ones; 'of mix' is the fraction of the same instruction mix run "
+                 "Roofline fractions: of the FP32 vector peak for plain and recurrence (slots per "
+                 "interaction as in bench.py), of the dense matrix-core peak of the operand type "
+                 "for the others; 'of mix' is the fraction of the same instruction mix run "
                  "alone by the machine probe." % d["reps"], "",
                  "FP64 GPU forward: %.2f ms (%.0f G interactions/s)." % (d["fwd_f64_ms"],
                                                                         d["fwd_f64_gpps"]), "",
@@ -1402,9 +1424,10 @@ def summarize_workloads(root):
             if not r:
                 continue
             fm, am = r.get("fwd_frac_of_mix"), r.get("adj_frac_of_mix")
-            if fm is None and mix_interactions("fwd_" + v):
+            direct = not r.get("contraction", False)
+            if fm is None and direct and mix_interactions("fwd_" + v):
                 fm = r["fwd_gpps"] * 1e9 / mix_interactions("fwd_" + v)
-            if am is None and mix_interactions("adj_" + v):
+            if am is None and direct and mix_interactions("adj_" + v):
                 am = r["adj_gpps"] * 1e9 / mix_interactions("adj_" + v)
             lines.append("| %s | %.4g | %.0f | %.2f | %s | %.4g | %.0f | %.2f | %s | %.2e |" % (
                 v, r["fwd_kernel_ms"], r["fwd_gpps"], r["fwd_roofline_frac"],
