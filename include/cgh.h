@@ -52,19 +52,21 @@
  *                       two axis phases' sum by the addition theorem and sums over the
  *                       points on the fp16 matrix cores with hi + lo operands, as
  *                       CGH_SEPARABLE_F16X3 (whose error is the smaller of the two forms);
- *                       up to 8 points it takes one cosine per interaction.
+ *                       up to 8 points it takes one cosine per interaction.  The backward
+ *                       is two such contractions of G, folded per point; below 32 rows it
+ *                       sums each interaction's sine and cosine instead.
  *      CGH_SEPARABLE    not the per-interaction cosine: the phase separates
  *                       exactly into x and y parts (each formed as in
  *                       CGH_COMPENSATED), cos(X + Y) = cXcY - sXsY turns the sum
- *                       into a dense real contraction of per-axis tables, and
- *                       the forward and adjoint run as FP32 matrix-core GEMMs.
+ *                       into a dense real contraction, and the forward and
+ *                       adjoint run on the FP32 matrix cores.
  *                       Needs a larger workspace (tables of 2N floats per row
- *                       and per column, plus split-K partial planes).
+ *                       and per column, plus partial planes).
  *      CGH_SEPARABLE_F16X3, CGH_SEPARABLE_F16, CGH_SEPARABLE_BF16
  *                       CGH_SEPARABLE with the contractions on the fp16 / bf16
- *                       matrix cores (FP32 accumulation).  The tables and G are
- *                       rounded to 16 bits after dividing A_j (forward) or G
- *                       (adjoint) by a power of two >= their largest
+ *                       matrix cores (FP32 accumulation).  The cosines, sines and
+ *                       G are rounded to 16 bits, A_j (forward) and G (adjoint) after
+ *                       scaling by a power of two from their largest
  *                       magnitude (undone exactly on the FP32 result).  F16X3
  *                       splits each operand into fp16 hi + lo and forms
  *                       hi*hi + hi*lo + lo*hi (near-FP32 accuracy); F16 and
@@ -118,8 +120,8 @@ extern "C" {
 #define CGH_KERNEL_FWD_F64 2
 #define CGH_KERNEL_ADJ_PLAIN 3
 #define CGH_KERNEL_ADJ_COMPENSATED 4
-#define CGH_KERNEL_FWD_SEPARABLE 5 /* the forward GEMM (every separable variant) */
-#define CGH_KERNEL_ADJ_SEPARABLE 6 /* both adjoint GEMMs, one event pair */
+#define CGH_KERNEL_FWD_SEPARABLE 5 /* the forward contraction (every separable variant) */
+#define CGH_KERNEL_ADJ_SEPARABLE 6 /* both adjoint contractions */
 #define CGH_KERNEL_FWD_RECURRENCE 7
 #define CGH_KERNEL_ADJ_RECURRENCE 8
 #define CGH_KERNEL_COUNT 9
@@ -208,7 +210,8 @@ int cgh_backward(const float* x, const float* y, const float* z, const float* a,
  * variant's tables (the compensated forward: 4 bytes per point and row, and
  * 4 per point and column unless dropped to fit, since the kernel can form
  * those values itself, and partial planes of a small hologram with many points
- * where they fit; the separable forms: their GEMM tables and split-K planes).  At 1920 x 1024 with 1,024 points every variant fits.
+ * where they fit; the separable forms: their tables and partial planes).  At 1920
+ * x 1024 with 1,024 points every variant fits.
  *   Every call on a GPU shares that GPU's buffer, which keeps the last call's
  * contents (each call rewrites what it reads): calls that overlap on one GPU
  * (on different streams, or from several threads without ordering) race.

@@ -25,14 +25,14 @@ constexpr int32_t kMaxSide = 1 << 20;
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Split-K count for a GEMM of `tiles` 128 x 128 output tiles and contraction
-// length k (a multiple of 32).  A slice holds ceil(k / 32 / splits) stages of
-// 32 (the last slice fewer, never none) and at least 8 stages.  The count
-// minimises a simple time model in units of one workgroup stage: rounds of
-// 512 resident GEMM workgroups (two per CU on 256 CUs) times the stages per
-// slice, plus the partial planes (each tile of each slice costs about six
-// stages of traffic, spread over the 512 slots).
-inline int gemm_splits(int64_t tiles, int64_t k) {
+// Parts in which a contraction of `tiles` 128 x 128 output tiles and length k (a
+// multiple of 32) of the separable variants has room for partial planes, and in
+// at least as many of which the forward sums (f16x3, FP32).  A part holds ceil(k /
+// 32 / splits) stages of 32 (the last one fewer, never none) and at least 8
+// stages.  The count minimises rounds of 512 resident workgroups (two per CU on
+// 256 CUs) times the stages per part, plus the planes (each tile of each part costs
+// about six stages of traffic, spread over the 512 slots).
+inline int split_count(int64_t tiles, int64_t k) {
   const int64_t chunks = k / 32;
   int best = 1;
   double best_time = 0.0;
@@ -79,7 +79,7 @@ inline int32_t rec_pixels(int32_t nx, int32_t ny) {
 
 inline bool valid_variant(int32_t v) { return v >= CGH_PLAIN && v <= CGH_RECURRENCE; }
 
-// The 16-bit GEMM format of a half-precision separable variant, or -1.
+// The 16-bit format of a half-precision separable variant, or -1.
 inline int half_mode(int32_t v) {
   switch (v) {
     case CGH_SEPARABLE_F16X3:
@@ -150,13 +150,13 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.regions = (int32_t)runs;
   p.need_gpad = (nx % kAdjCols) != 0;
 
-  // Separable variant: padded GEMM shapes and split-K counts.
+  // Separable variants: padded sides and partial planes.
   p.nxp = (int32_t)ceil_div(nx, 128) * 128;
   p.nyp = (int32_t)ceil_div(ny, 128) * 128;
   p.k2 = 2 * p.npad;
-  p.sep_splits = gemm_splits((int64_t)(p.nyp / 128) * (p.nxp / 128), p.k2);
-  p.sep_splits_u = gemm_splits((p.k2 / 128) * (p.nxp / 128), p.nyp);
-  p.sep_splits_p = gemm_splits((p.k2 / 128) * (p.nyp / 128), p.nxp);
+  p.sep_splits = split_count((int64_t)(p.nyp / 128) * (p.nxp / 128), p.k2);
+  p.sep_splits_u = split_count((p.k2 / 128) * (p.nxp / 128), p.nyp);
+  p.sep_splits_p = split_count((p.k2 / 128) * (p.nyp / 128), p.nxp);
 
   size_t off = 0;
   auto take = [&](size_t bytes) {
