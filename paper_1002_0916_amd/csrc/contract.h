@@ -91,9 +91,13 @@ __device__ __forceinline__ uint32_t pack16(float v0, float v1) {
 // differences v - hi (exact) and another pack.  The two empty asm statements
 // keep the compiler from converting each value a second time for the
 // difference and from turning the fma into a conversion and a subtraction.
+// With RAISE the planes hold v (1 + 2^-24) instead: the native cosine and sine are
+// 3.3e-8 too small on average (measured as the scale of a hologram), so a product
+// of two is 6.6e-8 too small, which one raised operand takes back.
+template <bool RAISE>
 __device__ __forceinline__ void split16(float v0, float v1, uint32_t& hi, uint32_t& lo) {
   uint32_t h = pack16<kHalfF16x3>(v0, v1);
-  float neg = -1.0f;
+  float neg = RAISE ? -0x1.fffffep-1f : -1.0f;
   asm("" : "+v"(h));
   asm("" : "+v"(neg));
   const halfx2 hh = __builtin_bit_cast(halfx2, h);
@@ -103,7 +107,7 @@ __device__ __forceinline__ void split16(float v0, float v1, uint32_t& hi, uint32
 }
 
 // Eight values as one lane's share of a block (k in order).
-template <int MODE>
+template <int MODE, bool RAISE = false>
 __device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
   Frag f;
   if constexpr (MODE == kF32) {
@@ -112,10 +116,10 @@ __device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
     f.lo = make_uint4(__float_as_uint(v[4]), __float_as_uint(v[5]), __float_as_uint(v[6]),
                       __float_as_uint(v[7]));
   } else if constexpr (MODE == kHalfF16x3) {
-    split16(v[0], v[1], f.hi.x, f.lo.x);
-    split16(v[2], v[3], f.hi.y, f.lo.y);
-    split16(v[4], v[5], f.hi.z, f.lo.z);
-    split16(v[6], v[7], f.hi.w, f.lo.w);
+    split16<RAISE>(v[0], v[1], f.hi.x, f.lo.x);
+    split16<RAISE>(v[2], v[3], f.hi.y, f.lo.y);
+    split16<RAISE>(v[4], v[5], f.hi.z, f.lo.z);
+    split16<RAISE>(v[6], v[7], f.hi.w, f.lo.w);
   } else {
     f.hi = make_uint4(pack16<MODE>(v[0], v[1]), pack16<MODE>(v[2], v[3]),
                       pack16<MODE>(v[4], v[5]), pack16<MODE>(v[6], v[7]));

@@ -143,8 +143,8 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
         c[e] = cos_rev(v[e]);
         s[e] = sin_rev(v[e]);
       }
-      C = make_frag<MODE>(c);
-      S = make_frag<MODE>(s);
+      C = make_frag<MODE, true>(c);
+      S = make_frag<MODE, true>(s);
     } else {
       C = Frag{ph.q0, ph.q0};
       S = Frag{ph.q1, ph.q1};
@@ -483,7 +483,7 @@ __device__ __forceinline__ void direct_part(const AdjArgs& p, int pb, int plane,
         s[e] = sin_rev(ph);
         g[e] *= mul;
       }
-      const Frag A = make_frag<MODE>(g), C = make_frag<MODE>(c), S = make_frag<MODE>(s);
+      const Frag A = make_frag<MODE>(g), C = make_frag<MODE, true>(c), S = make_frag<MODE, true>(s);
       auto part = [&](auto k) {
         U = mfma_part<MODE, decltype(k)::value>(A, C, U);
         V = mfma_part<MODE, decltype(k)::value>(A, S, V);

@@ -51,7 +51,7 @@ __device__ __forceinline__ Frag frag_of_phases(float4 ph, float4 a) {
   const float v[8] = {a.x * cos_rev(ph.x), -(a.x * sin_rev(ph.x)), a.y * cos_rev(ph.y),
                       -(a.y * sin_rev(ph.y)), a.z * cos_rev(ph.z), -(a.z * sin_rev(ph.z)),
                       a.w * cos_rev(ph.w), -(a.w * sin_rev(ph.w))};
-  return make_frag<MODE>(v);
+  return make_frag<MODE, true>(v);
 }
 
 // One quad's phases at coordinate h from its records {c, ph, pl, b, d}.
