@@ -109,8 +109,8 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.fwd_gx = (int32_t)ceil_div(nx, kWave);
   p.comp_gy = (int32_t)ceil_div(ny, kCompRowsPerWG);
   p.groups = p.comp_gy * kCompWaves;
-  p.comp_xtab = col_table && (int64_t)p.fwd_gx * kWave * p.npad <=
-                                 kCompColTabMaxBytes / (int64_t)sizeof(float);
+  p.comp_wide = (int64_t)p.fwd_gx * kWave * p.npad > kCompColTabMaxBytes / (int64_t)sizeof(float);
+  p.comp_xtab = col_table && !p.comp_wide;
   p.rec_k = rec_pixels(nx, ny);
   p.ngroups = (int32_t)(p.npad / kWave);
   const bool rtab_fits =
@@ -368,13 +368,16 @@ int forward_contract(const Plan& p, const ContractFwd& c, int kernel, const floa
                      const float* y, const float* z, const float* a, double pitch,
                      double wavelength, float* hologram, const float* target, float* residual,
                      hipStream_t s, bool timed) {
-  hipError_t e = c.direct ? hipSuccess
-                          : launch_contract_fwd_tables(p, c, x, y, z, a, pitch, wavelength, s);
+  hipError_t e = c.direct || c.chunk
+                     ? hipSuccess
+                     : launch_contract_fwd_tables(p, c, x, y, z, a, pitch, wavelength, s);
   if (e != hipSuccess) return CGH_EHIP;
   const EventPair ev = profile_begin(kernel, s, timed);
   e = c.direct ? launch_contract_direct(p, c, x, y, z, a, pitch, wavelength, hologram, target,
                                         residual, s)
-               : launch_contract_fwd(p, c, hologram, target, residual, s);
+      : c.chunk ? launch_contract_chunks(p, c, x, y, z, a, pitch, wavelength, hologram, target,
+                                         residual, s)
+                : launch_contract_fwd(p, c, hologram, target, residual, s);
   profile_end(kernel, ev, s);
   return hip_status(e);
 }

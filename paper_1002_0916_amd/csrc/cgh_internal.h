@@ -182,6 +182,7 @@ struct Plan {
   // forward
   int32_t fwd_gx, comp_gy, groups;
   bool comp_xtab;  // the compensated forward has its column table
+  bool comp_wide;  // that table would exceed kCompColTabMaxBytes
   int32_t f64_chunk, f64_slices;  // FP64 forward: points per chunk (0 slices: the direct kernel)
   int32_t fwd_planes;  // partial planes of the compensated forward (0: none of its own)
   int32_t rec_k;  // recurrence forward: consecutive pixels per lane

@@ -188,6 +188,7 @@ struct ContractFwd {
   float4* rec;
   float* amp;
   unsigned* amax;     // [kWave] maxima of |A| as float bits (single planes)
+  int64_t chunk;      // points per pass where the tables of all have no room (else 0)
   int slices;         // the points are cut into this many slices,
   float* planes;      //   with a plane [ny][nx] each when there are several
 };
@@ -197,6 +198,12 @@ int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny);
 hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const float* x,
                                       const float* y, const float* z, const float* a,
                                       double pitch, double wavelength, hipStream_t s);
+// The chunks of points one after the other, each with its tables and its sum, which
+// is added to the ones before.
+hipError_t launch_contract_chunks(const Plan& p, const ContractFwd& c, const float* x,
+                                  const float* y, const float* z, const float* a, double pitch,
+                                  double wavelength, float* out, const float* target,
+                                  float* residual, hipStream_t s);
 hipError_t launch_contract_direct(const Plan& p, const ContractFwd& c, const float* x,
                                   const float* y, const float* z, const float* a, double pitch,
                                   double wavelength, float* out, const float* target,

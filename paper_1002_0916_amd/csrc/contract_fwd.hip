@@ -661,6 +661,19 @@ __global__ __launch_bounds__(256) void contract_fwd_sum_kernel(const float* __re
   if (res) res[i] = v - tgt[i];
 }
 
+// I += plane, and I - T with a target.
+__global__ __launch_bounds__(256) void contract_fwd_add_kernel(const float* __restrict__ plane,
+                                                               int64_t count,
+                                                               float* __restrict__ out,
+                                                               const float* __restrict__ tgt,
+                                                               float* __restrict__ res) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= count) return;
+  const float v = out[i] + plane[i];
+  out[i] = v;
+  if (res) res[i] = v - tgt[i];
+}
+
 // Tile shapes <MI, NJ, WM, KS>: pixels per workgroup and the terms of its time
 // on this GPU: microseconds per launch beside the loop, and per 1000 points and
 // round of 256 workgroups (one a CU), for f16x3, for the single planes and for
@@ -751,6 +764,38 @@ bool use_direct(int64_t n, int32_t nx, int32_t ny, int mode, float tiled) {
   return 4.5f + rounds * (0.45f + (float)n * 1e-3f * per_k) < tiled + 3.5f;
 }
 
+// Without room for the column table of all points, the row table's region holds
+// both tables of a part of them and a plane for that part's sum, and the points can
+// be taken in chunks.  A pass takes its shape's time, 12 us for its launches and
+// the planes' traffic; forming the x-phases in the kernel takes about 1.3 times
+// `inline_us`, the shape's time with tables.  (us a call, formed in the kernel and
+// in chunks: 1920x1080, N = 65536: 2357 and 1871; 3840x800, N = 40000: 3002 and
+// 1934; 2011x81, N = 96630: 517 and, in 23 chunks, 1184.)  A rule on the plan alone,
+// so every entry point takes the same way.
+constexpr int64_t kMinChunk = 4096;
+void plan_chunks(const Plan& p, const Workspace& w, float inline_us, ContractFwd& c) {
+  const int64_t room = (int64_t)c.rows_y * p.npad;  // words
+  const int64_t pixels = (int64_t)p.nx * p.ny, units = p.npad / 64;
+  for (int64_t k = 1 + (c.cols_x + c.rows_y - 1) / c.rows_y;; ++k) {
+    const int64_t chunk = (units + k - 1) / k * 64;
+    if (chunk < kMinChunk) return;
+    const int64_t left = room - chunk * ((int64_t)c.rows_y + c.cols_x) - pixels;
+    if (left < 0) continue;
+    int slices;
+    float time;
+    const int shape = choose_shape(chunk, p.nx, p.ny, c.mode, left / pixels, 1, slices, time);
+    const float passes = (float)((p.npad + chunk - 1) / chunk);
+    if (passes * (time + 12.0f + (float)pixels * (12.0f / 4e6f)) > 1.3f * inline_us) return;
+    c.shape = shape;
+    c.slices = slices;
+    c.chunk = chunk;
+    c.xtab = true;
+    c.xq = w.ytab + chunk * c.rows_y;
+    c.planes = w.ytab + chunk * ((int64_t)c.rows_y + c.cols_x);  // a pass's sum, its slices
+    return;
+  }
+}
+
 }  // namespace
 
 int contract_fwd_slices(int64_t npad, int32_t nx, int32_t ny) {
@@ -806,6 +851,7 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   float time;
   c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices, time);
   c.direct = use_direct(p.n, p.nx, p.ny, c.mode, time);
+  if (p.variant == 1 && p.comp_wide && !c.direct) plan_chunks(p, w, time, c);
   return true;
 }
 
@@ -876,6 +922,32 @@ hipError_t launch_contract_fwd(const Plan& p, const ContractFwd& c, float* out,
   const int64_t count = (int64_t)p.nx * p.ny;
   hipLaunchKernelGGL(contract_fwd_sum_kernel, dim3(grid_blocks(count, 256)), dim3(256), 0, s,
                      c.planes, c.slices, count, out, target, residual);
+  return hipGetLastError();
+}
+
+hipError_t launch_contract_chunks(const Plan& p, const ContractFwd& c, const float* x,
+                                  const float* y, const float* z, const float* a, double pitch,
+                                  double wavelength, float* out, const float* target,
+                                  float* residual, hipStream_t s) {
+  const int64_t pixels = (int64_t)p.nx * p.ny;
+  ContractFwd part = c;
+  part.planes = c.planes + pixels;
+  for (int64_t first = 0; first < p.npad; first += c.chunk) {
+    Plan q = p;
+    q.npad = std::min(c.chunk, p.npad - first);
+    q.n = std::min(q.npad, p.n - first);
+    const int64_t units = q.npad / 64, per = (units + c.slices - 1) / c.slices;
+    part.slices = (int)((units + per - 1) / per);  // none empty in a shorter last pass
+    hipError_t e = launch_contract_fwd_tables(q, part, x + first, y + first, z + first, a + first,
+                                              pitch, wavelength, s);
+    if (e == hipSuccess)
+      e = launch_contract_fwd(q, part, first == 0 ? out : c.planes, nullptr, nullptr, s);
+    if (e != hipSuccess) return e;
+    if (first > 0)
+      hipLaunchKernelGGL(contract_fwd_add_kernel, dim3(grid_blocks(pixels, 256)), dim3(256), 0, s,
+                         c.planes, pixels, out, first + c.chunk < p.npad ? nullptr : target,
+                         first + c.chunk < p.npad ? nullptr : residual);
+  }
   return hipGetLastError();
 }
 

@@ -74,6 +74,14 @@ def test_forward_few_points(oracle_mod, variant, shape):
     test_forward_shapes(oracle_mod, variant, shape)
 
 
+# The column table of all points has no room (above 256 MiB): chunks of points, the
+# last one shorter, without and with slices in a chunk.
+@pytest.mark.parametrize("shape", [(1024, 700, 65601), (1273, 331, 91466)])
+def test_forward_chunks(oracle_mod, shape):
+    assert shape[0] * shape[2] * 4 > 256 << 20
+    test_forward_shapes(oracle_mod, "compensated", shape)
+
+
 @pytest.mark.parametrize("scale", [1e-30, 1e30])
 def test_forward_amplitudes_of_any_scale(oracle_mod, scale):
     """One amplitude 2^20 times the others, at both ends of the FP32 range."""
