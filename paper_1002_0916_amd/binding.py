@@ -129,14 +129,21 @@ def workspace_bytes(n: int, nx: int, ny: int, variant=COMPENSATED, op: int = OP_
 _workspaces: dict = {}
 
 
-def _workspace(device: torch.device, stream, nbytes: int):
+def _stream(device: torch.device) -> int:
+    """The handle of the current stream on ``device``: as
+    torch.cuda.current_stream(device).cuda_stream, without a Stream object
+    (1 us of a call)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+def _workspace(device: torch.device, stream: int, nbytes: int):
     if nbytes == 0:
         return None, 0
-    key = (device.index, stream.cuda_stream)
+    key = (device.index, stream)
     buf = _workspaces.get(key)
     if buf is None or buf.numel() < nbytes:
-        with torch.cuda.stream(stream):
-            buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
+        # allocated on the current stream, which is `stream`
+        buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
         _workspaces[key] = buf
     return buf.data_ptr(), buf.numel()
 
@@ -147,6 +154,16 @@ def release_workspaces():
 
 def _points(x, y, z, a):
     ts = (x, y, z, a)
+    # The checks below in one pass of cheap queries; what fails them is named there.
+    if isinstance(x, torch.Tensor):
+        n, index = x.numel(), x.get_device()
+        for t in ts:
+            if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype is torch.float32
+                    and t.dim() == 1 and t.numel() == n and t.get_device() == index
+                    and t.is_contiguous()):
+                break
+        else:
+            return n, x.device
     for name, t in zip("xyza", ts):
         if not isinstance(t, torch.Tensor):
             raise ValueError("%s must be a torch tensor" % name)
@@ -181,11 +198,11 @@ def forward(x, y, z, a, nx: int, ny: int, pitch: float = 8e-6, wavelength: float
     elif (out.dtype != torch.float32 or out.device != dev or not out.is_contiguous()
           or out.numel() != nx * ny):
         raise ValueError("out must be a contiguous float32 tensor of ny*nx on x's device")
-    stream = torch.cuda.current_stream(dev)
+    stream = _stream(dev)
     ws, wsb = _workspace(dev, stream, workspace_bytes(n, nx, ny, v, OP_FORWARD))
     _check(lib.cgh_forward(x.data_ptr(), y.data_ptr(), z.data_ptr(), a.data_ptr(), n, nx, ny,
                            float(pitch), float(wavelength), v, out.data_ptr(), ws, wsb,
-                           stream.cuda_stream))
+                           stream))
     return out
 
 
@@ -214,12 +231,12 @@ def forward_residual(x, y, z, a, target: torch.Tensor, nx: int, ny: int, pitch: 
     target = grid(target, "target")
     out = grid(out, "out")
     residual = grid(residual, "residual")
-    stream = torch.cuda.current_stream(dev)
+    stream = _stream(dev)
     ws, wsb = _workspace(dev, stream, workspace_bytes(n, nx, ny, v, OP_FORWARD))
     _check(lib.cgh_forward_residual(x.data_ptr(), y.data_ptr(), z.data_ptr(), a.data_ptr(), n,
                                     nx, ny, float(pitch), float(wavelength), v,
                                     target.data_ptr(), out.data_ptr(), residual.data_ptr(), ws,
-                                    wsb, stream.cuda_stream))
+                                    wsb, stream))
     return out, residual
 
 
@@ -239,10 +256,10 @@ def forward_noalloc(x, y, z, a, nx: int, ny: int, pitch: float = 8e-6,
     elif (out.dtype != torch.float32 or out.device != dev or not out.is_contiguous()
           or out.numel() != nx * ny):
         raise ValueError("out must be a contiguous float32 tensor of ny*nx on x's device")
-    stream = torch.cuda.current_stream(dev)
+    stream = _stream(dev)
     _check(lib.cgh_forward_noalloc(x.data_ptr(), y.data_ptr(), z.data_ptr(), a.data_ptr(), n,
                                    nx, ny, float(pitch), float(wavelength), v, out.data_ptr(),
-                                   stream.cuda_stream))
+                                   stream))
     return out
 
 
@@ -253,11 +270,11 @@ def forward_f64(x, y, z, a, nx: int, ny: int, pitch: float = 8e-6,
     n, dev = _points(x, y, z, a)
     nx, ny = _sizes(nx, ny)
     out = torch.empty((ny, nx), dtype=torch.float64, device=dev)
-    stream = torch.cuda.current_stream(dev)
+    stream = _stream(dev)
     ws, wsb = _workspace(dev, stream, workspace_bytes(n, nx, ny, PLAIN, OP_FORWARD_F64))
     _check(lib.cgh_forward_f64(x.data_ptr(), y.data_ptr(), z.data_ptr(), a.data_ptr(), n, nx,
                                ny, float(pitch), float(wavelength), out.data_ptr(), ws, wsb,
-                               stream.cuda_stream))
+                               stream))
     return out
 
 
@@ -273,12 +290,12 @@ def backward(x, y, z, a, grad, nx: int, ny: int, pitch: float = 8e-6,
         raise ValueError("grad must be a float32 tensor of shape (ny, nx) on x's device")
     grad = grad.contiguous()
     gx, gy, gz, ga = (torch.empty(n, dtype=torch.float32, device=dev) for _ in range(4))
-    stream = torch.cuda.current_stream(dev)
+    stream = _stream(dev)
     ws, wsb = _workspace(dev, stream, workspace_bytes(n, nx, ny, v, OP_BACKWARD))
     _check(lib.cgh_backward(x.data_ptr(), y.data_ptr(), z.data_ptr(), a.data_ptr(), n, nx, ny,
                             float(pitch), float(wavelength), v, grad.data_ptr(), gx.data_ptr(),
                             gy.data_ptr(), gz.data_ptr(), ga.data_ptr(), ws, wsb,
-                            stream.cuda_stream))
+                            stream))
     return gx, gy, gz, ga
 
 

@@ -154,9 +154,11 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.nxp = (int32_t)ceil_div(nx, 128) * 128;
   p.nyp = (int32_t)ceil_div(ny, 128) * 128;
   p.k2 = 2 * p.npad;
-  p.sep_splits = split_count((int64_t)(p.nyp / 128) * (p.nxp / 128), p.k2);
-  p.sep_splits_u = split_count((p.k2 / 128) * (p.nxp / 128), p.nyp);
-  p.sep_splits_p = split_count((p.k2 / 128) * (p.nyp / 128), p.nxp);
+  if (is_separable(variant)) {
+    p.sep_splits = split_count((int64_t)(p.nyp / 128) * (p.nxp / 128), p.k2);
+    p.sep_splits_u = split_count((p.k2 / 128) * (p.nxp / 128), p.nyp);
+    p.sep_splits_p = split_count((p.k2 / 128) * (p.nyp / 128), p.nxp);
+  }
 
   size_t off = 0;
   auto take = [&](size_t bytes) {
