@@ -852,6 +852,22 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   c.shape = choose_shape(p.npad, p.nx, p.ny, c.mode, room, parts, c.slices, time);
   c.direct = use_direct(p.n, p.nx, p.ny, c.mode, time);
   if (p.variant == 1 && p.comp_wide && !c.direct) plan_chunks(p, w, time, c);
+  // The single planes are bound by their operand loads: tables that exceed the 256
+  // MB Infinity Cache are formed and read in passes that fit it, where there is
+  // room for a pass's plane.  (us a call in f16, in one pass, of 96 MB and of 192 MB:
+  // 1673x658, N = 51542: 601, 525, 443; 1920x1080, N = 65536: 915, 848, 806;
+  // 1382x471, N = 36660: 271, 259, 239.  f16x3 and FP32, with more work an operand,
+  // gain nothing or lose.)
+  constexpr int64_t kCached = int64_t(256) << 20, kPassBytes = int64_t(192) << 20;
+  const int64_t point_bytes = ((int64_t)c.rows_y + c.cols_x) * 4;  // tables, a point
+  if ((c.mode == kHalfF16 || c.mode == kHalfBF16) && point_bytes * p.npad > kCached && room >= 2) {
+    const int64_t passes = (point_bytes * p.npad + kPassBytes - 1) / kPassBytes;
+    const int64_t chunk = (p.npad / 64 + passes - 1) / passes * 64;
+    if (chunk >= kMinChunk) {
+      c.chunk = chunk;
+      c.shape = choose_shape(chunk, p.nx, p.ny, c.mode, room - 1, 1, c.slices, time);
+    }
+  }
   return true;
 }
 

@@ -74,12 +74,17 @@ def test_forward_few_points(oracle_mod, variant, shape):
     test_forward_shapes(oracle_mod, variant, shape)
 
 
-# The column table of all points has no room (above 256 MiB): chunks of points, the
-# last one shorter, without and with slices in a chunk.
-@pytest.mark.parametrize("shape", [(1024, 700, 65601), (1273, 331, 91466)])
-def test_forward_chunks(oracle_mod, shape):
-    assert shape[0] * shape[2] * 4 > 256 << 20
-    test_forward_shapes(oracle_mod, "compensated", shape)
+# Tables in chunks of points, the last one shorter, without and with slices in a
+# chunk: the compensated variant's where the column table of all points has no room,
+# the single planes' where both tables exceed 256 MiB.
+@pytest.mark.parametrize("variant,shape", [("compensated", (1024, 700, 65601)),
+                                           ("compensated", (1273, 331, 91466)),
+                                           ("separable_f16", (1920, 1080, 24001)),
+                                           ("separable_bf16", (1382, 471, 36660))])
+def test_forward_chunks(oracle_mod, variant, shape):
+    nx, ny, n = shape
+    assert (nx if variant == "compensated" else nx + ny) * n * 4 > 256 << 20
+    test_forward_shapes(oracle_mod, variant, shape)
 
 
 @pytest.mark.parametrize("scale", [1e-30, 1e30])
