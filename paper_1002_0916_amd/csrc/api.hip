@@ -224,9 +224,16 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
                     : 0;
   // Planes of the adjoint's partial sums: with few points as many as the
   // contraction can use to fill the chip (12 MB at most), else as many as K
-  // slices of 128-wide tiles of both axes.
+  // slices of 128-wide tiles of both axes.  In FP32, whose workgroups run longest,
+  // at least four a tile, so that slices can fill the last round (2104x1335, N =
+  // 5414: 1277 us a call with one a tile, 1122 with four; 182x382, N = 13668: 137
+  // and 110).
+  const int64_t tiles = p.nxp / 128 + p.nyp / 128;
   p.fold_planes = (int64_t)p.sep_splits_u * (p.nxp / 128) + (int64_t)p.sep_splits_p * (p.nyp / 128);
-  if (n <= 4096) p.fold_planes = std::max<int64_t>(p.fold_planes, (nx + 31) / 32 + (ny + 31) / 32);
+  if (n <= 4096)
+    p.fold_planes = std::max<int64_t>(p.fold_planes, (nx + 31) / 32 + (ny + 31) / 32);
+  else if (f32)
+    p.fold_planes = std::max<int64_t>(p.fold_planes, 4 * tiles);
   p.off_fold = (sep && bwd) ? take((size_t)p.fold_planes * np * sizeof(float4)) : 0;
   // The contraction's tables hold 4 bytes a point and coordinate; the f16x3 ones
   // take the room of two 16-bit planes of cosines and sines, so that the problems
