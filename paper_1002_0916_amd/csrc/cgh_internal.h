@@ -73,11 +73,10 @@ constexpr int kCompRowsPerWG = kCompWaves * kCompRows;
 static_assert(kWave % kCompWaves == 0, "x-phase fill splits the 64 columns over the waves");
 static_assert(kTile % 16 == 0, "the inner loop takes 16 points per iteration");
 // The compensated forward reads its x-phases from a column table
-// [fwd_gx * 64][npad] while that takes at most kCompColTabMaxBytes, else it
-// forms them per workgroup (the same values).  Every row block of
-// workgroups reads the whole table again, so it pays only while the table
-// stays in the 256 MB Infinity Cache (measured: 252 MB faster, 503 MB 10%
-// slower than forming the values).
+// [fwd_gx * 64][npad] while that takes at most kCompColTabMaxBytes; else it
+// takes the points in chunks whose tables fit the row table's region, or forms
+// the x-phases in the kernel (the same values).  Every row block of workgroups
+// reads the table again, from the 256 MB Infinity Cache while it fits.
 constexpr int64_t kCompColTabMaxBytes = int64_t(256) << 20;
 constexpr int kPointPad = 64;
 

@@ -16,9 +16,9 @@
 //
 // Cosines and sines lie in [-1, 1].  The other operand's values (A_j forward, G
 // in the adjoint) are multiplied by a power of two first (exact), which puts the
-// largest below 2^15 (f16x3) or 1 (the single planes): with fp16's smallest step at 2^-24, a value down to 2^-16 of
-// the largest keeps both planes at full width, and the absolute error of a
-// smaller one is below 2^-39 of the largest.
+// largest below 2^15 (f16x3) or 1 (the single planes): with fp16's smallest step
+// at 2^-24, a value down to 2^-16 of the largest keeps both planes at full width,
+// and the absolute error of a smaller one is below 2^-39 of the largest.
 #pragma once
 
 #include <algorithm>

@@ -497,11 +497,11 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
 }
 
 // Few points on a small hologram, in one launch without tables: a call of two
-// launches there is bound by them (256x256, N = 64: 14.3 us a call, 11.3 here).  A workgroup is 32 x 32
-// pixels and eight waves.  It forms the records of up to 512 points at a time in
-// LDS, one a thread; wave w takes steps w, w + 8, ... of eight points, each lane
-// the phases of its four points at its row and its column, from records that all
-// lanes of a half read together (broadcasts).  Tiles of one block form every
+// launches there is bound by them (256x256, N = 64: 14.3 us a call, 11.3 here).
+// A workgroup is 32 x 32 pixels and eight waves.  It forms the records of up to
+// 512 points at a time in LDS, one a thread; wave w takes steps w, w + 8, ... of
+// eight points, each lane the phases of its four points at its row and its
+// column, from records that all lanes of a half read together (broadcasts).  Tiles of one block form every
 // phase once per 32 pixels, 0.9 instructions an interaction, which is why many
 // points or large holograms take tables and larger tiles.
 constexpr int kDirectPoints = 512;
