@@ -759,6 +759,7 @@ hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const fl
 bool use_direct(int64_t n, int32_t nx, int32_t ny, int mode, float tiled) {
   if (n > 2 * kDirectPoints) return false;
   const int64_t tiles = ((int64_t)nx + 31) / 32 * (((int64_t)ny + 31) / 32);
+  if (tiles > 1 << 20) return false;  // (a grid of 2^32 threads at most)
   const float rounds = (float)((tiles + 255) / 256);
   const float per_k = mode == kHalfF16x3 ? 9.2f : mode == kF32 ? 13.2f : 7.0f;
   return 4.5f + rounds * (0.45f + (float)n * 1e-3f * per_k) < tiled + 3.5f;
@@ -776,6 +777,7 @@ constexpr int64_t kMinChunk = 4096;
 void plan_chunks(const Plan& p, const Workspace& w, float inline_us, ContractFwd& c) {
   const int64_t room = (int64_t)c.rows_y * p.npad;  // words
   const int64_t pixels = (int64_t)p.nx * p.ny, units = p.npad / 64;
+  if (pixels > 0x7fffffff) return;  // (the planes' kernels take a thread a pixel)
   for (int64_t k = 1 + (c.cols_x + c.rows_y - 1) / c.rows_y;; ++k) {
     const int64_t chunk = (units + k - 1) / k * 64;
     if (chunk < kMinChunk) return;
@@ -860,7 +862,8 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   // gain nothing or lose.)
   constexpr int64_t kCached = int64_t(256) << 20, kPassBytes = int64_t(192) << 20;
   const int64_t point_bytes = ((int64_t)c.rows_y + c.cols_x) * 4;  // tables, a point
-  if ((c.mode == kHalfF16 || c.mode == kHalfBF16) && point_bytes * p.npad > kCached && room >= 2) {
+  if ((c.mode == kHalfF16 || c.mode == kHalfBF16) && point_bytes * p.npad > kCached && room >= 2 &&
+      pixels <= 0x7fffffff) {
     const int64_t passes = (point_bytes * p.npad + kPassBytes - 1) / kPassBytes;
     const int64_t chunk = (p.npad / 64 + passes - 1) / passes * 64;
     if (chunk >= kMinChunk) {

@@ -32,7 +32,7 @@ template <int R, int S>
 __global__ __launch_bounds__(kPlainWaves * kWave) void fwd_plain_kernel(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
     const float* __restrict__ a, int64_t n, int npad, double pitch, double wavelength, int nx,
-    int ny, unsigned tiles_x, float* __restrict__ out, const float* __restrict__ tgt,
+    int ny, float* __restrict__ out, const float* __restrict__ tgt,
     float* __restrict__ res) {
   constexpr int kQuads = R / 4, kGroup = kPlainWaves / S;
   __shared__ float4 recs[2][kTile];                         // {x, y, Prev, A}
@@ -41,9 +41,10 @@ __global__ __launch_bounds__(kPlainWaves * kWave) void fwd_plain_kernel(
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int part = wave / kGroup, w = wave % kGroup;
-  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int x0 = (int)(tile % tiles_x) * kWave, col = x0 + lane;
-  const int y0 = ((int)(tile / tiles_x) * kGroup + w) * R;
+  // (two dimensions, so that neither exceeds 2^32 threads on the largest holograms)
+  const unsigned tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int x0 = (int)(tile % gridDim.x) * kWave, col = x0 + lane;
+  const int y0 = ((int)(tile / gridDim.x) * kGroup + w) * R;
   const float xh = (float)col;
 
   // The tile's stage: lane l has point l.  Every wave of part 0 forms its own
@@ -148,11 +149,11 @@ hipError_t launch(const Plan& p, const float* x, const float* y, const float* z,
                   float* residual, hipStream_t s) {
   constexpr int kRows = kPlainWaves / S * R;
   const int64_t tiles_x = (p.nx + kWave - 1) / kWave;
-  const int64_t tiles = tiles_x * (((int64_t)p.ny + kRows - 1) / kRows);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fwd_plain_kernel<R, S>), dim3((unsigned)tiles), dim3(kPlainWaves * kWave), 0,
-                     s, x, y, z, a, p.n, (int)p.npad, pitch, wavelength, p.nx, p.ny,
-                     (unsigned)tiles_x, out, target, residual);
+  const int64_t tiles_y = ((int64_t)p.ny + kRows - 1) / kRows;
+  if (tiles_x * tiles_y > 0x7fffffff || tiles_y > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((fwd_plain_kernel<R, S>), dim3((unsigned)tiles_x, (unsigned)tiles_y),
+                     dim3(kPlainWaves * kWave), 0, s, x, y, z, a, p.n, (int)p.npad, pitch,
+                     wavelength, p.nx, p.ny, out, target, residual);
   return hipGetLastError();
 }
 

@@ -42,7 +42,7 @@ template <int K, int R>
 __global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
     const float* __restrict__ a, int64_t n, int npad, double pitch, double wavelength, int nx,
-    int ny, unsigned tiles_x, float* __restrict__ out, const float* __restrict__ tgt,
+    int ny, float* __restrict__ out, const float* __restrict__ tgt,
     float* __restrict__ res) {
   constexpr int kMine = kTile / kParts;
   __shared__ float4 recs[2][kTile];  // {x, Prev, A, Delta}
@@ -51,9 +51,11 @@ __global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
   __shared__ float sums[kParts / 2 * R * K * kWave];
   const int lane = threadIdx.x & (kWave - 1);
   const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const unsigned tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int x0 = ((int)(tile % tiles_x) * kWave + lane) * K;
-  const int y0 = (int)(tile / tiles_x) * R;
+  // (two dimensions, so that neither exceeds 2^32 threads on the largest holograms:
+  // row blocks along x, up to 2^20, column blocks along y)
+  const unsigned tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
+  const int x0 = ((int)(tile % gridDim.y) * kWave + lane) * K;
+  const int y0 = (int)(tile / gridDim.y) * R;
   const float xh = (float)x0;
 
   // The tile's stage, by the first wave: lane l has point l.
@@ -150,13 +152,12 @@ template <int K, int R>
 hipError_t launch(const Plan& p, const float* x, const float* y, const float* z, const float* a,
                   double pitch, double wavelength, float* out, const float* target,
                   float* residual, hipStream_t s) {
-  constexpr int kRows = R;
   const int64_t tiles_x = ((int64_t)p.nx + kWave * K - 1) / (kWave * K);
-  const int64_t tiles = tiles_x * (((int64_t)p.ny + kRows - 1) / kRows);
-  if (tiles > 0x7fffffff) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fwd_rec_kernel<K, R>), dim3((unsigned)tiles), dim3(kParts * kWave), 0, s,
-                     x, y, z, a, p.n, (int)p.npad, pitch, wavelength, p.nx, p.ny, (unsigned)tiles_x,
-                     out, target, residual);
+  const int64_t tiles_y = ((int64_t)p.ny + R - 1) / R;
+  if (tiles_x * tiles_y > 0x7fffffff || tiles_x > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((fwd_rec_kernel<K, R>), dim3((unsigned)tiles_y, (unsigned)tiles_x),
+                     dim3(kParts * kWave), 0, s, x, y, z, a, p.n, (int)p.npad, pitch, wavelength,
+                     p.nx, p.ny, out, target, residual);
   return hipGetLastError();
 }
 
