@@ -52,7 +52,10 @@
  *                       two axis phases' sum by the addition theorem and sums over the
  *                       points on the fp16 matrix cores with hi + lo operands, as
  *                       CGH_SEPARABLE_F16X3 (whose error is the smaller of the two forms);
- *                       up to 8 points it takes one cosine per interaction.  The backward
+ *                       up to 8 points, and for many points on few pixels (24 n > nx ny),
+ *                       it takes one cosine per interaction and adds the points in
+ *                       order, so that the result does not depend on how a sum was
+ *                       split.  The backward
  *                       is two such contractions of G, folded per point; below 32 rows it
  *                       sums each interaction's sine and cosine instead.
  *      CGH_SEPARABLE    not the per-interaction cosine: the phase separates

@@ -194,7 +194,7 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
     const size_t want = (size_t)contract_fwd_slices(p.npad, nx, ny);
     const size_t base = off - (p.comp_xtab ? align256((size_t)p.fwd_gx * kWave * np * sizeof(float)) : 0);
     const size_t bytes = align256(want * pixels * sizeof(float));
-    if (n > 8 && want > 1 && want * pixels > np * kAxisRec &&
+    if (n > 8 && !ordered_sum(n, nx, ny) && want > 1 && want * pixels > np * kAxisRec &&
         (base + bytes <= CGH_NOALLOC_SCRATCH_BYTES || base > CGH_NOALLOC_SCRATCH_BYTES)) {
       p.fwd_planes = (int32_t)want;
       p.off_planes = take(bytes);

@@ -26,6 +26,7 @@
 #include <utility>
 
 #include "cgh_internal.h"
+#include "order.h"
 #include "phase.h"
 
 namespace cgh {

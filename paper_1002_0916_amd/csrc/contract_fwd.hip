@@ -815,7 +815,9 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
     // both take the time of their launches there (17 us a call at 101x121,
     // N = 1), and of a single point the direct form keeps the exact eightfold
     // symmetry, since A multiplies the whole cosine and not the row factor.
-    if (p.n <= 8) return false;
+    // Sums that keep the order of the points are its own too: the matrix cores add
+    // 16 products at a time.
+    if (p.n <= 8 || ordered_sum(p.n, p.nx, p.ny)) return false;
     c.mode = kHalfF16x3;
     c.rows_y = p.groups * kCompRows;
     c.cols_x = p.fwd_gx * kWave;

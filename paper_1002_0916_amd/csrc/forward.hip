@@ -1,5 +1,6 @@
 // Direct forward kernels: the compensated sum of Eq. (1) (Section 1) of a few
-// points, and the FP64 one where the contraction's tables have no room.  The plain
+// points and of many points on few pixels (order.h), and the FP64 one where the
+// contraction's tables have no room.  The plain
 // form is in plain.hip, Eq. (2) in recurrence.hip, the contractions in
 // contract_fwd.hip and contract_f64.hip.
 //

@@ -1,0 +1,56 @@
+"""The order of addition of holograms of many points for their pixels.
+
+Where the points' terms add up in phase, a residual I - T is a small difference
+of large sums and shows their rounding, so the forwards keep one order of
+addition there: the compensated and plain ones add the points one after the
+other.
+
+At z = 1e30 every phase is below 1e-25 revolutions, every cosine 1 and every sine
+lost against it, so a pixel is the sum of the amplitudes, which NumPy's running
+FP32 sum gives to the bit in any stated order.
+"""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import device, say, to_dev
+from paper_1002_0916_amd import binding as B
+from paper_1002_0916_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def cloud(n, nx, ny, seed):
+    c = W.random_cloud(seed, n, nx, ny, alo=0.5, ahi=1.0)
+    return W.Cloud(c.x, c.y, np.full(n, 1e30, dtype=np.float32), c.a)
+
+
+def chain(a):
+    """The FP32 sum of a, one after the other."""
+    return np.add.accumulate(a.astype(np.float32), dtype=np.float32)[-1]
+
+
+def check(c, nx, ny, variant, want):
+    """I of all three entry points, and I - T, from the value of every pixel."""
+    dev = device()
+    say("order", (nx, ny, c.n), variant)
+    x, y, z, a = to_dev(c, dev)
+    T = torch.from_numpy(np.random.default_rng(7).standard_normal((ny, nx)).astype(np.float32))
+    T = T.to(dev)
+    I, G = B.forward_residual(x, y, z, a, T, nx, ny, variant=variant)
+    J = B.forward(x, y, z, a, nx, ny, variant=variant)
+    K = B.forward_noalloc(x, y, z, a, nx, ny, variant=variant)
+    assert torch.equal(I, J) and torch.equal(I, K) and torch.equal(G, I - T)
+    assert np.array_equal(I.cpu().numpy(), np.full((ny, nx), want, dtype=np.float32))
+
+
+# The smallest number of points that keeps the order (24 n > pixels), remainders of
+# the tiles and of 64 points, and many points on few pixels.
+MANY = [(64, 48, 129), (130, 97, 526), (129, 95, 30001), (1, 1, 100), (365, 339, 10048)]
+
+
+@pytest.mark.parametrize("shape", MANY)
+def test_compensated_adds_the_points_in_order(shape):
+    nx, ny, n = shape
+    c = cloud(n, nx, ny, 2000 + n)
+    check(c, nx, ny, "compensated", chain(c.a))
