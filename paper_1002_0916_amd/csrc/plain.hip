@@ -12,11 +12,13 @@
 // wave bounds the phase of every point of a tile over its own pixels.  That
 // leaves an fma, a product, the cosine and an fma, 4.1 clocks, and 0.2 for dx^2.
 // Several groups of waves share the pixels and split the points, so that small
-// holograms fill the SIMDs too.  1920x1024, N = 1024: 281 us a call, where 8 rows
+// holograms fill the SIMDs too, but for many points on few pixels (order.h), where
+// one group adds them all in order.  1920x1024, N = 1024: 281 us a call, where 8 rows
 // per lane with the points in SGPRs took 384; 333x197, N = 700: 19 and 124.
 #include <type_traits>
 
 #include "cgh_internal.h"
+#include "order.h"
 #include "phase.h"
 
 namespace cgh {
@@ -37,7 +39,7 @@ __global__ __launch_bounds__(kPlainWaves * kWave) void fwd_plain_kernel(
   constexpr int kQuads = R / 4, kGroup = kPlainWaves / S;
   __shared__ float4 recs[2][kTile];                         // {x, y, Prev, A}
   __shared__ float4 dys[2][kGroup][kTile][kQuads];
-  __shared__ float sums[(S - 1) * R * kGroup * kWave];
+  __shared__ float sums[S > 1 ? (S - 1) * R * kGroup * kWave : 1];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int part = wave / kGroup, w = wave % kGroup;
@@ -112,7 +114,7 @@ __global__ __launch_bounds__(kPlainWaves * kWave) void fwd_plain_kernel(
         }
       }
     };
-    constexpr unsigned long long kAll = (1ull << kMine) - 1;
+    constexpr unsigned long long kAll = ~0ull >> (kTile - kMine);
     if (((__ballot(exact) >> (part * kMine)) & kAll) == kAll)
       points(std::false_type{});
     else
@@ -120,18 +122,20 @@ __global__ __launch_bounds__(kPlainWaves * kWave) void fwd_plain_kernel(
     if (t + 1 < ntiles) store(b ^ 1);
     __syncthreads();
   }
-  float* d = sums + w * R * kWave + lane;
-  constexpr int kPart = kGroup * R * kWave;
-  if (part > 0) {
+  if constexpr (S > 1) {
+    float* d = sums + w * R * kWave + lane;
+    constexpr int kPart = kGroup * R * kWave;
+    if (part > 0) {
 #pragma unroll
-    for (int i = 0; i < R; ++i) d[(part - 1) * kPart + i * kWave] = acc[i];
+      for (int i = 0; i < R; ++i) d[(part - 1) * kPart + i * kWave] = acc[i];
+    }
+    __syncthreads();
+    if (part > 0) return;
+#pragma unroll
+    for (int q = 0; q < S - 1; ++q)
+#pragma unroll
+      for (int i = 0; i < R; ++i) acc[i] += d[q * kPart + i * kWave];
   }
-  __syncthreads();
-  if (part > 0) return;
-#pragma unroll
-  for (int q = 0; q < S - 1; ++q)
-#pragma unroll
-    for (int i = 0; i < R; ++i) acc[i] += d[q * kPart + i * kWave];
   if (col < nx) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -163,6 +167,8 @@ hipError_t launch_fwd_plain(const Plan& p, const float* x, const float* y, const
                             const float* a, double pitch, double wavelength, float* out,
                             const float* target, float* residual, hipStream_t s) {
   auto go = [&](auto f) { return f(p, x, y, z, a, pitch, wavelength, out, target, residual, s); };
+  // Many points on few pixels: all of them in one sum, in order.
+  if (ordered_sum(p.n, p.nx, p.ny)) return go(launch<4, 1>);
   // Waves of 64 x 4 pixels, of which the chip holds 8192: few of them split the
   // points further, and many let a lane keep 8 rows, which share a point's dx^2
   // and reads.  (us at 4 rows and 8 parts, 4 and 4, 8 and 2: 640x480, N = 512:

@@ -54,3 +54,10 @@ def test_compensated_adds_the_points_in_order(shape):
     nx, ny, n = shape
     c = cloud(n, nx, ny, 2000 + n)
     check(c, nx, ny, "compensated", chain(c.a))
+
+
+@pytest.mark.parametrize("shape", MANY)
+def test_plain_adds_the_points_in_order(shape):
+    nx, ny, n = shape
+    c = cloud(n, nx, ny, 2100 + n)
+    check(c, nx, ny, "plain", chain(c.a))
