@@ -19,18 +19,21 @@
 // as broadcasts.  The eight waves of a workgroup share the pixels and take eight
 // points of every tile each, since a lane's K x R pixels leave few waves (1024 of
 // 64 K x 4 at 1920x1024, for 8192 places); their sums are added in a fixed order.
+// For many points on few pixels (order.h) the order of addition is that of two
+// halves of the points, each in order.
 // 1920x1080, N = 8192: 2345 us a call, where records in SGPRs and two groups of
 // waves took 2671; 3840x2160, N = 1024: 1046 and 1166; 333x197, N = 700: 18 and 45.
 #include <type_traits>
 
 #include "cgh_internal.h"
+#include "order.h"
 #include "phase.h"
 
 namespace cgh {
 
 namespace {
 
-constexpr int kParts = 8;  // waves of a workgroup, each with its part of the points
+constexpr int kWaves = 8;  // per workgroup
 
 // A point's y_h - y_j at a lane's rows.
 template <int R>
@@ -38,44 +41,52 @@ struct alignas(4 * R) Dy {
   float v[R];
 };
 
-template <int K, int R>
-__global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
+// K pixels x R rows per lane; P parts of the points, each with kWaves / P waves on
+// rows of their own.  Eight parts take eight points of every tile each; two take one
+// half of all points each, in order.
+template <int K, int R, int P>
+__global__ __launch_bounds__(kWaves * kWave, 8) void fwd_rec_kernel(
     const float* __restrict__ x, const float* __restrict__ y, const float* __restrict__ z,
     const float* __restrict__ a, int64_t n, int npad, double pitch, double wavelength, int nx,
     int ny, float* __restrict__ out, const float* __restrict__ tgt,
     float* __restrict__ res) {
-  constexpr int kMine = kTile / kParts;
+  constexpr int kMine = kTile / P, kGroups = kWaves / P;
   __shared__ float4 recs[2][kTile];  // {x, Prev, A, Delta}
-  __shared__ Dy<R> dys[2][kTile];
+  __shared__ Dy<R> dys[2][kGroups][kTile];
   // The upper half of the parts leaves its sums for the lower half, and so on.
-  __shared__ float sums[kParts / 2 * R * K * kWave];
+  __shared__ float sums[kWaves / 2 * R * K * kWave];
   const int lane = threadIdx.x & (kWave - 1);
-  const int part = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int part = wave / kGroups, w = wave % kGroups;
   // (two dimensions, so that neither exceeds 2^32 threads on the largest holograms:
   // row blocks along x, up to 2^20, column blocks along y)
   const unsigned tile = xcd_tile(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int x0 = ((int)(tile % gridDim.y) * kWave + lane) * K;
-  const int y0 = (int)(tile / gridDim.y) * R;
+  const int y0 = ((int)(tile / gridDim.y) * kGroups + w) * R;
   const float xh = (float)x0;
 
-  // The tile's stage, by the first wave: lane l has point l.
+  // The tile's stage: lane l has point l of it.  Every wave of part 0 forms its own
+  // rows' dy, and the first one the records.
   float px = 0.0f, py = 0.0f, pz = 1.0f, pa = 0.0f;
   auto load = [&](int t) {
-    const int64_t j = (int64_t)t * kTile + lane;
-    const bool in = part == 0 && j < n;
-    px = in ? x[j] : 0.0f;
+    const int64_t j = P == 2 ? (int64_t)(lane / kMine) * (npad / 2) + t * kMine + lane % kMine
+                             : (int64_t)t * kTile + lane;
+    const bool in = part == 0 && j < n, first = in && w == 0;
     py = in ? y[j] : 0.0f;
-    pz = in ? z[j] : 1.0f;
-    pa = in ? a[j] : 0.0f;
+    px = first ? x[j] : 0.0f;
+    pz = first ? z[j] : 1.0f;
+    pa = first ? a[j] : 0.0f;
   };
   auto store = [&](int b) {
     if (part != 0) return;
-    const float prev = (float)((pitch * pitch) / (2.0 * wavelength * (double)pz));
-    recs[b][lane] = make_float4(px, prev, pa, fract(prev + prev));
+    if (w == 0) {
+      const float prev = (float)((pitch * pitch) / (2.0 * wavelength * (double)pz));
+      recs[b][lane] = make_float4(px, prev, pa, fract(prev + prev));
+    }
     Dy<R> dy;
 #pragma unroll
     for (int i = 0; i < R; ++i) dy.v[i] = (float)(y0 + i) - py;
-    dys[b][lane] = dy;
+    dys[b][w][lane] = dy;
   };
 
   float acc[R][K];
@@ -94,7 +105,7 @@ __global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
     for (int q = 0; q < kMine; ++q) {
       const int p = part * kMine + q;
       const float4 r = recs[b][p];
-      const Dy<R> dy = dys[b][p];
+      const Dy<R> dy = dys[b][w][p];
       const float dx = xh - r.x;
       const float dx2 = dx * dx;
       float d = fract(r.y * __builtin_fmaf(2.0f, dx, 1.0f));
@@ -117,8 +128,8 @@ __global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
     __syncthreads();
   }
 #pragma unroll
-  for (int left = kParts / 2; left >= 1; left /= 2) {
-    float* at = sums + (part % left) * R * K * kWave + lane;
+  for (int left = P / 2; left >= 1; left /= 2) {
+    float* at = sums + (part % left * kGroups + w) * R * K * kWave + lane;
     if (part >= left && part < 2 * left) {
 #pragma unroll
       for (int i = 0; i < R; ++i)
@@ -148,15 +159,16 @@ __global__ __launch_bounds__(kParts * kWave, 8) void fwd_rec_kernel(
   }
 }
 
-template <int K, int R>
+template <int K, int R, int P>
 hipError_t launch(const Plan& p, const float* x, const float* y, const float* z, const float* a,
                   double pitch, double wavelength, float* out, const float* target,
                   float* residual, hipStream_t s) {
   const int64_t tiles_x = ((int64_t)p.nx + kWave * K - 1) / (kWave * K);
-  const int64_t tiles_y = ((int64_t)p.ny + R - 1) / R;
+  constexpr int kRows = kWaves / P * R;
+  const int64_t tiles_y = ((int64_t)p.ny + kRows - 1) / kRows;
   if (tiles_x * tiles_y > 0x7fffffff || tiles_x > 65535) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((fwd_rec_kernel<K, R>), dim3((unsigned)tiles_y, (unsigned)tiles_x),
-                     dim3(kParts * kWave), 0, s, x, y, z, a, p.n, (int)p.npad, pitch, wavelength,
+  hipLaunchKernelGGL((fwd_rec_kernel<K, R, P>), dim3((unsigned)tiles_y, (unsigned)tiles_x),
+                     dim3(kWaves * kWave), 0, s, x, y, z, a, p.n, (int)p.npad, pitch, wavelength,
                      p.nx, p.ny, out, target, residual);
   return hipGetLastError();
 }
@@ -169,6 +181,17 @@ hipError_t launch_fwd_rec(const Plan& p, const float* x, const float* y, const f
   auto go = [&](auto f) { return f(p, x, y, z, a, pitch, wavelength, out, target, residual, s); };
   auto shape = [&](auto k) {
     constexpr int K = decltype(k)::value;
+    // Many points on few pixels: two sums of half the points each, in order.  Its
+    // workgroups run in rounds of 256, one a CU, and a round of 2 rows per lane takes
+    // 1.7 times one of 1 row, 4 rows as long as two of 2.  (us at 1 and 2 rows:
+    // 365x339, N = 10048: 469 and 764; 213x1332, N = 14185: 1166 and 1084; 1065x967, N
+    // = 51492: 8642 and 10371; 1786x835, N = 65536: 14832 and 13446.)
+    if (ordered_sum(p.n, p.nx, p.ny)) {
+      const int64_t cols = ((int64_t)p.nx + kWave * K - 1) / (kWave * K);
+      const int64_t one = (cols * (((int64_t)p.ny + 3) / 4) + 255) / 256;
+      const int64_t two = (cols * (((int64_t)p.ny + 7) / 8) + 255) / 256;
+      return 10 * one < 17 * two ? go(launch<K, 1, 2>) : go(launch<K, 2, 2>);
+    }
     // Waves of 64 K x 4 pixels: few of them take fewer rows per lane, so that there
     // are more waves, at more seeds per pixel.  (us at 4, 2 and 1 rows: 160x245, N =
     // 2612: 107, 59, 40; 640x480, N = 512: 34, 33, 35; 1865x300, N = 2246: 238, 193,
@@ -176,9 +199,9 @@ hipError_t launch_fwd_rec(const Plan& p, const float* x, const float* y, const f
     const int64_t waves = ((int64_t)p.nx + kWave * K - 1) / (kWave * K) * (((int64_t)p.ny + 3) / 4);
     // (with so few K is 4)
     if constexpr (K == 4)
-      if (waves <= 80) return go(launch<K, 1>);
-    if (waves <= 430) return go(launch<K, 2>);
-    return go(launch<K, 4>);
+      if (waves <= 80) return go(launch<K, 1, 8>);
+    if (waves <= 430) return go(launch<K, 2, 8>);
+    return go(launch<K, 4, 8>);
   };
   if (p.rec_k == 4) return shape(std::integral_constant<int, 4>{});
   if (p.rec_k == 6) return shape(std::integral_constant<int, 6>{});

@@ -3,7 +3,8 @@
 Where the points' terms add up in phase, a residual I - T is a small difference
 of large sums and shows their rounding, so the forwards keep one order of
 addition there: the compensated and plain ones add the points one after the
-other.
+other, the recurrence adds two halves of the points (padded to a multiple of 64)
+so and then the two sums.
 
 At z = 1e30 every phase is below 1e-25 revolutions, every cosine 1 and every sine
 lost against it, so a pixel is the sum of the amplitudes, which NumPy's running
@@ -61,3 +62,16 @@ def test_plain_adds_the_points_in_order(shape):
     nx, ny, n = shape
     c = cloud(n, nx, ny, 2100 + n)
     check(c, nx, ny, "plain", chain(c.a))
+
+
+# The recurrence's lane shapes there: K = 4, 6 and 8 pixels, one and two rows.
+@pytest.mark.parametrize("shape", MANY + [(133, 1130, 6300), (357, 628, 11209), (331, 1665, 23000),
+                                          (441, 861, 18985), (437, 1109, 24231)])
+def test_recurrence_adds_two_halves_in_order(shape):
+    nx, ny, n = shape
+    c = cloud(n, nx, ny, 2200 + n)
+    half = -(-n // 64) * 32
+    want = chain(c.a[:half])
+    if n > half:
+        want = np.float32(want + chain(c.a[half:]))
+    check(c, nx, ny, "recurrence", want)
