@@ -64,7 +64,9 @@
  *                       into a dense real contraction, and the forward and
  *                       adjoint run on the FP32 matrix cores.
  *                       Needs a larger workspace (tables of 2N floats per row
- *                       and per column, plus partial planes).
+ *                       and per column, plus partial planes).  For many points on few
+ *                       pixels (3 n > nx ny) this and the variants below add the
+ *                       points in order, in parts that depend on the sizes alone.
  *      CGH_SEPARABLE_F16X3, CGH_SEPARABLE_F16, CGH_SEPARABLE_BF16
  *                       CGH_SEPARABLE with the contractions on the fp16 / bf16
  *                       matrix cores (FP32 accumulation).  The cosines, sines and

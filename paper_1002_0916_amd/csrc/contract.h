@@ -131,13 +131,13 @@ __device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
 
 // The power of two that an operand with the largest magnitude m (float bits of
 // a finite m) is multiplied by, and its inverse.  frexp's exponent e (m < 2^e)
-// is clamped so that both stay normal floats.
-template <int MODE>
+// is clamped so that both stay normal floats.  The largest value is then below 2^TOP.
+template <int MODE, int TOP = MODE == kHalfF16x3 ? 15 : 0>
 __device__ __forceinline__ void operand_scale(unsigned max_bits, float& mul, float& undo) {
   int e = 0;
   const float m = __uint_as_float(max_bits);
   if (m > 0.0f) (void)frexpf(m, &e);
-  e -= MODE == kHalfF16x3 ? 15 : 0;
+  e -= TOP;
   e = max(-126, min(126, e));
   undo = ldexpf(1.0f, e);
   mul = ldexpf(1.0f, -e);
@@ -178,6 +178,7 @@ struct FwdOperands {
   int rows_y, cols_x;
 };
 
+constexpr int kOrdered = 6;  // the shape whose slices are sums of their points in order
 struct ContractFwd {
   int mode;           // the operand format
   bool direct;        // one launch without tables (few points), else:
@@ -188,7 +189,7 @@ struct ContractFwd {
   void* xq;
   float4* rec;
   float* amp;
-  unsigned* amax;     // [kWave] maxima of |A| as float bits (single planes)
+  unsigned* amax;     // [kWave] maxima of |A| as float bits (single planes, kOrdered)
   int64_t chunk;      // points per pass where the tables of all have no room (else 0)
   int slices;         // the points are cut into this many slices,
   float* planes;      //   with a plane [ny][nx] each when there are several

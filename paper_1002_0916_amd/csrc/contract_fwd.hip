@@ -18,9 +18,15 @@
 // leaves it in LDS (double buffered), in the layout in which all of them read
 // it back (a wave reads or writes 1 KB of consecutive bytes: no bank
 // conflicts).  The row operand stays in the registers of the wave that forms
-// it.  The KS groups (two or more) split the points of the same pixels; their
-// sums are added in group order through LDS at the end (a fixed order: bitwise
-// reproducible), which also keeps every chain of additions short.
+// it.  The KS groups split the points of the same pixels; their sums are added in
+// group order through LDS at the end (a fixed order: bitwise reproducible), which
+// also keeps every chain of additions short.
+//
+// With one group of one wave (KS = 1) a slice is one chain of additions in the order
+// of its points.  The separable variants use it for many points on few pixels
+// (order.h), with their plan's K splits as slices, so that a sum is the same however
+// the other shapes cut it: the operands are then without the factor 1 + 2^-24, the
+// f16x3 ones below 1, and FP32 pairs point p of 16 with point p + 8.
 //
 // The FP32 format (v_mfma_f32_32x32x2, 4 flops per interaction) is bound by the
 // FP32 matrix cores, whose instructions occupy the vector unit as well: a cosine
@@ -46,12 +52,12 @@ __device__ __forceinline__ Frag frag_of_phases(float4 ph) {
                       cos_rev(ph.z), sin_rev(ph.z), cos_rev(ph.w), sin_rev(ph.w)};
   return make_frag<MODE>(v);
 }
-template <int MODE>
+template <int MODE, bool RAISE = true>
 __device__ __forceinline__ Frag frag_of_phases(float4 ph, float4 a) {
   const float v[8] = {a.x * cos_rev(ph.x), -(a.x * sin_rev(ph.x)), a.y * cos_rev(ph.y),
                       -(a.y * sin_rev(ph.y)), a.z * cos_rev(ph.z), -(a.z * sin_rev(ph.z)),
                       a.w * cos_rev(ph.w), -(a.w * sin_rev(ph.w))};
-  return make_frag<MODE, true>(v);
+  return make_frag<MODE, RAISE>(v);
 }
 
 // One quad's phases at coordinate h from its records {c, ph, pl, b, d}.
@@ -70,6 +76,8 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     const unsigned* __restrict__ amax, float* __restrict__ out, const float* __restrict__ tgt,
     float* __restrict__ res) {
   constexpr bool kForms = MODE == kHalfF16x3;  // from phases; else the tables hold operands
+  constexpr bool kInOrder = KS == 1;
+  constexpr int kFar = kInOrder && MODE == kF32 ? 2 : 1;  // quads between the lanes' halves
   constexpr int kThreads = kWave * WM * KS;
   constexpr int kPlanes = kForms || MODE == kF32 ? 2 : 1;  // uint4 per operand share
   constexpr int kLoad = MODE == kF32 ? 2 : 1;              // and per table entry
@@ -119,10 +127,14 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
   unsigned yoff[MI], xoff[NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
-    yoff[i] = (unsigned)(half * o.rows_y + min(y0 + i * 32 + l32, o.rows_y - 1)) * 16u;
+    yoff[i] = (unsigned)(half * kFar * o.rows_y + min(y0 + i * 32 + l32, o.rows_y - 1)) * 16u;
 #pragma unroll
   for (int n = 0; n < NJ; ++n)
-    xoff[n] = (unsigned)(half * o.cols_x + min(x0 + n * 32 + l32, o.cols_x - 1)) * 16u;
+    xoff[n] = (unsigned)(half * kFar * o.cols_x + min(x0 + n * 32 + l32, o.cols_x - 1)) * 16u;
+  // The first half's quad of step t.
+  auto quad = [&](int t) -> int64_t {
+    return kFar == 2 ? 4 * (int64_t)(t >> 1) + (t & 1) : 2 * (int64_t)t;
+  };
   struct Entry {
     uint4 q[kLoad];
   };
@@ -134,7 +146,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
   const int64_t yplane = (int64_t)(npad / 4) * o.rows_y * 16;
   const int64_t xplane = (int64_t)(npad / 4) * o.cols_x * 16;
   auto load_y = [&](int t, RowPhases& r) {
-    const char* base = yt + (int64_t)t * o.rows_y * 32;
+    const char* base = yt + quad(t) * o.rows_y * 16;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -145,7 +157,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
   auto load_x = [&](int t, int n) -> Entry {
     Entry p;
     if constexpr (XTAB) {
-      const char* base = xt + (int64_t)t * o.cols_x * 32;
+      const char* base = xt + quad(t) * o.cols_x * 16;
 #pragma unroll
       for (int k = 0; k < kLoad; ++k)
         p.q[k] = *reinterpret_cast<const uint4*>(base + k * xplane + xoff[n]);
@@ -196,7 +208,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 
   // Scale of the amplitudes from their largest magnitude.
   unsigned m = 0;
-  if (MODE == kHalfF16x3) {
+  if (MODE == kHalfF16x3 && !kInOrder) {
     for (int j = threadIdx.x * 4; j < npad; j += kThreads * 4) {
       const float4 v = *reinterpret_cast<const float4*>(o.amp + j);
       m = max(m, max(max(__float_as_uint(fabsf(v.x)), __float_as_uint(fabsf(v.y))),
@@ -207,12 +219,15 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     m = group_max<kWave>(amax[lane], red);
   }
   float mul = 1.0f, undo = 1.0f;
-  if (MODE != kF32) operand_scale<MODE>(m, mul, undo);
+  if (kInOrder && MODE != kF32)
+    operand_scale<MODE, 0>(m, mul, undo);
+  else if (MODE != kF32)
+    operand_scale<MODE>(m, mul, undo);
   auto form_y = [&](const RowPhases& r, float mul, Frag (&A)[MI]) {
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       if constexpr (kForms) {
-        A[i] = frag_of_phases<MODE>(
+        A[i] = frag_of_phases<MODE, !kInOrder>(
             __builtin_bit_cast(float4, r.p[i].q[0]),
             make_float4(r.a.x * mul, r.a.y * mul, r.a.z * mul, r.a.w * mul));
       } else {
@@ -623,7 +638,8 @@ hipError_t launch_shape(const Plan& p, const ContractFwd& c, float* out, const f
   if (tiles > 0x7fffffff) return hipErrorInvalidValue;
   if (tiles * c.slices > 0x7fffffff) return hipErrorInvalidValue;
   const FwdOperands o{c.yq, c.xtab ? c.xq : nullptr, c.rec, c.amp, c.rows_y, c.cols_x};
-  const int per_slice = (int)((p.npad / 64 + c.slices - 1) / c.slices * 64);
+  constexpr int kUnit = KS == 1 ? 16 : 64;  // points
+  const int per_slice = (int)((p.npad / kUnit + c.slices - 1) / c.slices * kUnit);
   const bool one = c.slices == 1;
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(tiles * c.slices)), dim3(kWave * WM * KS), 0, s, o,
@@ -635,7 +651,7 @@ hipError_t launch_shape(const Plan& p, const ContractFwd& c, float* out, const f
       go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, true, true>);
     else
       go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, true, false>);
-  } else if constexpr (MODE == kHalfF16x3) {
+  } else if constexpr (MODE == kHalfF16x3 && KS > 1) {
     if (res && one)
       go(contract_fwd_kernel<MODE, MI, NJ, WM, KS, false, true>);
     else
@@ -745,6 +761,12 @@ hipError_t launch_mode(const Plan& p, const ContractFwd& c, float* out, const fl
     case 3: return launch_shape<MODE, 2, 2, 1, 8>(p, c, out, tgt, res, s);
     case 4: return launch_shape<MODE, 1, 2, 1, 8>(p, c, out, tgt, res, s);
     case 5: return launch_shape<MODE, 1, 1, 1, 8>(p, c, out, tgt, res, s);
+    // (us at 1 x 1, 1 x 2 and 2 x 2 blocks: 448x336, N = 42208: FP32 332, 362, 431; f16x3
+    // 240, 216, 222; f16 119, 104, 93.  146x121, N = 25918: FP32 62, 67, 74.)
+    case kOrdered: {
+      constexpr int kSide = MODE == kF32 ? 1 : 2;
+      return launch_shape<MODE, kSide, kSide, 1, 1>(p, c, out, tgt, res, s);
+    }
     default: return hipErrorInvalidValue;
   }
 }
@@ -835,6 +857,12 @@ bool plan_contract_fwd(const Plan& p, const Workspace& w, ContractFwd& c) {
   c.rec = (float4*)w.xrec;
   c.amp = w.amp;
   c.amax = w.hmax;
+  if (p.variant != 1 && ordered_splits(p.n, p.nx, p.ny)) {
+    c.shape = kOrdered;
+    c.slices = p.sep_splits;
+    c.planes = w.sep_c;
+    return true;
+  }
   // Planes of the point slices: the plan's own, the split planes of the
   // separable plans, or the y records (which this path does not use).
   const int64_t pixels = (int64_t)p.nx * p.ny;
@@ -882,7 +910,8 @@ hipError_t launch_contract_fwd_tables(const Plan& p, const ContractFwd& c, const
   const int yslices = (c.rows_y + kTabRows - 1) / kTabRows;
   const int xslices = c.xtab ? (c.cols_x + kTabRows - 1) / kTabRows : 0;
   const dim3 grid((unsigned)(p.npad / 16), (unsigned)(yslices + xslices));
-  if ((c.mode == kHalfF16 || c.mode == kHalfBF16) && p.n > kAmaxInline)
+  const bool single = c.mode == kHalfF16 || c.mode == kHalfBF16;
+  if ((single && p.n > kAmaxInline) || (c.mode == kHalfF16x3 && c.shape == kOrdered))
     hipLaunchKernelGGL(contract_amax_kernel, dim3(kWave), dim3(256), 0, s, a, p.n, c.amax);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, x, y, z, a, p.n, pitch, wavelength, yslices,

@@ -17,4 +17,11 @@ inline bool ordered_sum(int64_t n, int32_t nx, int32_t ny) {
   return 24 * n > (int64_t)nx * ny;
 }
 
+// The same for the separable variants, whose sums are the plan's K splits, each in
+// order, and then the splits in order: those are shorter, and another cut moves the
+// residual by up to 1.2e-5 at this line and 1.4e-4 beyond it (136x105, n = 64690).
+inline bool ordered_splits(int64_t n, int32_t nx, int32_t ny) {
+  return 3 * n > (int64_t)nx * ny;
+}
+
 }  // namespace cgh
