@@ -203,12 +203,12 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
       float v[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        // (FP32 has no scale, and a select keeps an infinity or NaN at the edge
-        // out of the padding)
-        if constexpr (MODE == kF32)
-          v[e] = mul_u[k] != 0.0f && vv + e < nv ? gv[k][e] : 0.0f;
-        else
+        // A select keeps an infinity or NaN at the edge out of the padding.  (f16x3
+        // sums a G that holds one term by term; FP32 has no scale, mul is 1.)
+        if constexpr (MODE == kHalfF16x3)
           v[e] = gv[k][e] * (vv + e < nv ? mul_u[k] : 0.0f);
+        else
+          v[e] = mul_u[k] != 0.0f && vv + e < nv ? gv[k][e] * mul : 0.0f;
       }
       const Frag f = make_frag<MODE>(v);
       uint4* d = lds + (s & 1) * kBuf + ((oct >> 1) * kBlocks + (u >> 5)) * kPlanes * kWave +

@@ -1,0 +1,46 @@
+"""Infinities and NaN in the inputs of the contraction kernels: what one element
+gives stays that element's, at the edges of the hologram and of the tiles too."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import device, say, to_dev
+from paper_1002_0916_amd import binding as B
+from paper_1002_0916_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SEPARABLE = ["separable", "separable_f16", "separable_bf16"]
+
+
+def axis_cos_sin(c, axis, at):
+    """cos and sin of each point's phase on one axis at pixel `at`, float64."""
+    v = (c.x if axis == "x" else c.y).astype(np.float64)
+    rho = W.PITCH ** 2 / (2 * W.WAVELENGTH * c.z.astype(np.float64)) * (at - v) ** 2
+    return np.cos(2 * np.pi * rho), np.sin(2 * np.pi * rho)
+
+
+# Tiled (1200x900) and one tile a workgroup (150x110); the last pixel, the last row
+# and column, and one inside.
+@pytest.mark.parametrize("variant", SEPARABLE)
+@pytest.mark.parametrize("shape", [(1201, 903, 1000), (150, 110, 40)])
+@pytest.mark.parametrize("where", ["corner", "row", "column", "inside"])
+def test_adjoint_infinite_gradient_in_separable_form(variant, shape, where):
+    """dL/dA_j = sum_x (cX U - sX V), U = sum_y G cY, V = sum_y G sY: an infinite G
+    makes both terms of its column infinite, and the difference the first one's
+    infinity or, where they have one sign, NaN."""
+    nx, ny, n = shape
+    dev = device()
+    say("infinite G", shape, variant, where)
+    c = W.random_cloud(1701, n, nx, ny, zlo=0.3, zhi=1.0, alo=0.5, ahi=1.0)
+    px = nx - 1 if where in ("corner", "column") else nx // 3
+    py = ny - 1 if where in ("corner", "row") else ny // 3
+    g = torch.from_numpy(np.random.default_rng(5).standard_normal((ny, nx)).astype(np.float32))
+    g = g.to(dev)
+    g[py, px] = float("inf")
+    ga = B.backward(*to_dev(c, dev), g, nx, ny, variant=variant)[3].cpu().numpy()
+    (cx, sx), (cy, sy) = axis_cos_sin(c, "x", px), axis_cos_sin(c, "y", py)
+    clear = np.min(np.abs([cx, sx, cy, sy]), axis=0) > 1e-2
+    want = np.where(cx * cy * sx * sy > 0, np.nan, np.where(cx * cy > 0, np.inf, -np.inf))
+    assert clear.sum() > n // 2 and np.isinf(want[clear]).any()
+    assert np.array_equal(ga[clear], want[clear].astype(np.float32), equal_nan=True)
