@@ -207,7 +207,8 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
   p.off_ctab = (direct_adj && p.adj_kind == kAdjCompensated)
                    ? take((size_t)p.nsx * kAdjCols * np * sizeof(float))
                    : 0;
-  p.off_partial = direct_adj ? take((size_t)p.regions * np * sizeof(float4)) : 0;
+  const size_t gmax_bytes = kMaxGBlocks * sizeof(unsigned);
+  p.off_partial = direct_adj ? take((size_t)p.regions * np * sizeof(float4) + gmax_bytes) : 0;
   p.off_gpad = (direct_adj && p.need_gpad)
                    ? take((size_t)p.nsx * kAdjCols * (size_t)ny * sizeof(float))
                    : 0;
@@ -234,7 +235,7 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
     p.fold_planes = std::max<int64_t>(p.fold_planes, (nx + 31) / 32 + (ny + 31) / 32);
   else if (f32)
     p.fold_planes = std::max<int64_t>(p.fold_planes, 4 * tiles);
-  p.off_fold = (sep && bwd) ? take((size_t)p.fold_planes * np * sizeof(float4)) : 0;
+  p.off_fold = (sep && bwd) ? take((size_t)p.fold_planes * np * sizeof(float4) + gmax_bytes) : 0;
   // The contraction's tables hold 4 bytes a point and coordinate; the f16x3 ones
   // take the room of two 16-bit planes of cosines and sines, so that the problems
   // the static scratch holds do not depend on how a table is laid out.

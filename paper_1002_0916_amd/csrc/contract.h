@@ -228,6 +228,7 @@ hipError_t launch_contract_f64(const Plan& p, const Workspace& w, const float* x
 // Tables of the adjoint, a quad of coordinates at a time (lane = point):
 //   f16x3, f32   float [ceil(size / 4)][npad][4]   the axis phase
 //   f16, bf16    two planes uint32 [ceil(size / 8)][npad][4]: cosines, sines
+constexpr int kMaxGBlocks = 512;  // block maxima of |G|, behind the partial planes
 struct ContractAdj {
   int mode;
   bool direct;        // no tables: the points' records and 32-wide tiles

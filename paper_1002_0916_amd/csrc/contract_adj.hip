@@ -691,9 +691,9 @@ bool plan_contract_adj(const Plan& p, const Workspace& w, ContractAdj& c) {
     c.partial = w.fold;
     capacity = p.fold_planes;
   }
-  c.gmax = (unsigned*)w.plain;
+  c.gmax = (unsigned*)(c.partial + capacity * p.npad);
   // (the FP32 operands take no scale)
-  c.gblocks = c.mode == kF32 ? 0 : (int)std::min<int64_t>(512, ceil_div((int64_t)p.nx * p.ny, 256 * 8));
+  c.gblocks = c.mode == kF32 ? 0 : (int)std::min<int64_t>(kMaxGBlocks, ceil_div((int64_t)p.nx * p.ny, 256 * 8));
   // Tiles per workgroup and slices of v.  A workgroup takes, in units of one
   // stage, kStart to begin with and for each of its tiles the slice's stages and
   // fold for the fold; 512 run at once, two a CU, and one alone on its CU takes
