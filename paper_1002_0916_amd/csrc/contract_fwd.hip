@@ -691,29 +691,33 @@ __global__ __launch_bounds__(256) void contract_fwd_add_kernel(const float* __re
 }
 
 // Tile shapes <MI, NJ, WM, KS>: pixels per workgroup and the terms of its time
-// on this GPU: microseconds per launch beside the loop, and per 1000 points and
-// round of 256 workgroups (one a CU), for f16x3, for the single planes and for
-// FP32, each in a launch of one round and of more.  Larger tiles form fewer operands per
+// on this GPU: microseconds per launch beside the loop; per round of 256 workgroups
+// (one a CU) for its sums and stores, which count where few points light many pixels
+// (below; us with the first shape and with the one that the other terms prefer:
+// 6029x4883, N = 9 in bf16: 45 and 91; 3840x2160, N = 256: 28 and 37; N = 64 in FP32: 39
+// and 63); and per 1000 points and round, for f16x3, for the single planes and for FP32, each in a
+// launch of one round and of more.  Larger tiles form fewer operands per
 // product (per pixel <2, 4, 2, 2> takes 0.7 of <2, 2, 1, 4>'s time and 0.4 of
 // <1, 1, 1, 8>'s); smaller ones and more point groups put a small hologram on
 // more CUs.  Measured at 50 random sizes (64 to 3840 by 64 to 2160, 64 to 65,536
 // points), the choice is within 4% of the best shape on average, 21% at most.
 struct Shape {
   int rows, cols, groups;
-  float fixed, split_one, split, single_one, single, f32_one, f32;
+  float fixed, round, split_one, split, single_one, single, f32_one, f32;
 };
 constexpr Shape kShapes[] = {
-    {128, 128, 2, 9.5f, 47.0f, 47.0f, 29.0f, 29.0f, 132.0f, 140.0f},  // <2, 4, 2, 2>
-    {64, 128, 8, 9.0f, 26.0f, 26.0f, 12.0f, 12.0f, 77.0f, 77.0f},   // <2, 4, 1, 8>
-    {64, 64, 4, 7.0f, 18.5f, 15.5f, 10.0f, 7.8f, 40.6f, 38.5f},     // <2, 2, 1, 4>
-    {64, 64, 8, 8.0f, 15.2f, 16.0f, 8.0f, 8.0f, 36.6f, 39.5f},      // <2, 2, 1, 8>
-    {32, 64, 8, 6.5f, 10.5f, 10.3f, 6.2f, 5.6f, 19.6f, 20.5f},      // <1, 2, 1, 8>
-    {32, 32, 8, 5.0f, 7.5f, 7.0f, 4.2f, 4.0f, 11.0f, 10.6f},        // <1, 1, 1, 8>
+    {128, 128, 2, 9.5f, 2.2f, 47.0f, 47.0f, 29.0f, 29.0f, 132.0f, 140.0f},  // <2, 4, 2, 2>
+    {64, 128, 8, 9.0f, 5.5f, 26.0f, 26.0f, 12.0f, 12.0f, 77.0f, 77.0f},   // <2, 4, 1, 8>
+    {64, 64, 4, 7.0f, 1.1f, 18.5f, 15.5f, 10.0f, 7.8f, 40.6f, 38.5f},     // <2, 2, 1, 4>
+    {64, 64, 8, 8.0f, 2.5f, 15.2f, 16.0f, 8.0f, 8.0f, 36.6f, 39.5f},      // <2, 2, 1, 8>
+    {32, 64, 8, 6.5f, 1.3f, 10.5f, 10.3f, 6.2f, 5.6f, 19.6f, 20.5f},      // <1, 2, 1, 8>
+    {32, 32, 8, 5.0f, 0.8f, 7.5f, 7.0f, 4.2f, 4.0f, 11.0f, 10.6f},        // <1, 1, 1, 8>
 };
 
-// Shape, slices and their time in microseconds for plan p.  Cutting the points into slices (as far as the
-// plan has room for their planes) puts a small hologram of many points on more
-// CUs, at one more launch (6 us) and the planes' traffic (at 3 TB/s); a slice
+// Shape and slices for plan p, and the least time in microseconds without the stores
+// (which use_direct and plan_chunks compare with times without them).  Cutting the
+// points into slices (as far as the plan has room for their planes) puts a small
+// hologram of many points on more CUs, at one more launch (6 us) and the planes' traffic (at 3 TB/s); a slice
 // has at least 512 points.  (128x96, N = 60000: 410 us in one slice, 36 in 21.)
 // The sums are cut into at least min_parts parts (slices times point groups),
 // which bounds the error of the FP32 additions: it grows as the square root of
@@ -722,10 +726,15 @@ constexpr Shape kShapes[] = {
 int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices,
                  int64_t min_parts, int& slices, float& best_time) {
   int best = 0;
+  float best_cost = 0.0f;
   best_time = 0.0f;
   slices = 1;
   const int64_t units = npad / 64;  // points are cut in units of 64
   const int64_t most = mode == kF32 ? 4096 : 1024;  // workgroups of a sliced launch
+  const bool count_stores =
+      mode == kF32         ? npad <= 64
+      : mode == kHalfF16x3 ? npad <= 512 && (int64_t)nx * ny > int64_t(1) << 23
+                           : npad <= 2048 && (int64_t)nx * ny > int64_t(5) << 20;
   const float plane_us = (float)nx * (float)ny * (8.0f / 3e6f);
   for (int k = 0; k < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++k) {
     const Shape& q = kShapes[k];
@@ -739,13 +748,15 @@ int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_sli
       const float per_k = mode == kHalfF16x3 ? (rounds == 1 ? q.split_one : q.split)
                           : mode == kF32     ? (rounds == 1 ? q.f32_one : q.f32)
                                              : (rounds == 1 ? q.single_one : q.single);
+      const float stores = count_stores ? (float)rounds * q.round : 0.0f;
       const float time = q.fixed + (float)rounds * (float)(per * 64) * 1e-3f * per_k +
                          (n > 1 ? 6.0f + (float)n * plane_us : 0.0f);
-      if (best_time == 0.0f || time < best_time) {
+      if (best_time == 0.0f || time + stores < best_cost) {
         best = k;
-        best_time = time;
+        best_cost = time + stores;
         slices = (int)n;
       }
+      best_time = best_time == 0.0f ? time : std::min(best_time, time);
     }
   }
   return best;
