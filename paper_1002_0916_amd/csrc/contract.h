@@ -143,6 +143,7 @@ __device__ __forceinline__ void operand_scale(unsigned max_bits, float& mul, flo
   mul = ldexpf(1.0f, -e);
 }
 __device__ __forceinline__ bool finite_bits(unsigned max_bits) { return max_bits < 0x7f800000u; }
+__device__ __forceinline__ bool nan_bits(unsigned max_bits) { return max_bits > 0x7f800000u; }
 
 // Largest of v over a workgroup of T threads, on every thread; `lds` holds one
 // word per wave.  (Non-negative floats order as their bits.)

@@ -320,13 +320,13 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
   float s1 = undo * (float)(d1 + __shfl_xor(d1, 32, 64));
   float s2 = undo * (float)(d2 + __shfl_xor(d2, 32, 64));
 
-  // An infinite or NaN G has no scale: such a call sums term by term (in the
-  // x part's workgroups; the y part's planes are zero), so that its infinities
-  // and NaNs are the direct sum's.
+  // An infinite G has no scale: such a call sums term by term (in the x part's
+  // workgroups; the y part's planes are zero), so that its infinities and NaNs are the
+  // direct sum's.  A NaN makes every sum NaN.
   if (MODE == kHalfF16x3 && !finite_bits(m)) {
-    s0 = s1 = s2 = 0.0f;
-    float sy = 0.0f;
-    if (!PY) {
+    s0 = s1 = s2 = nan_bits(m) ? __builtin_nanf("") : 0.0f;
+    float sy = s0;
+    if (!PY && !nan_bits(m)) {
       for (int v = s_beg * kAdjStage; v < min(s_end * kAdjStage, nv); ++v) {
         const float Y = axis_phase((float)v, vc, rec.ph, rec.pl, vb, vd);
         const float dy = (float)v - rec.y;
@@ -449,10 +449,11 @@ __device__ __forceinline__ void direct_part(const AdjArgs& p, int pb, int plane,
       m = group_max<kDirectThreads>(m, red);
       operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
     }
-    // An infinite or NaN G has no scale: such a tile is summed term by term.
+    // An infinite G has no scale: such a tile is summed term by term.  (A NaN makes
+    // every sum NaN.)
     if (MODE == kHalfF16x3 && !finite_bits(m)) {
-      float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
-      for (int k = 0; k < kDirectTile && u0 + k < nu; ++k) {
+      float s0 = nan_bits(m) ? __builtin_nanf("") : 0.0f, s1 = s0, s2 = s0;
+      for (int k = 0; k < kDirectTile && u0 + k < nu && !nan_bits(m); ++k) {
         const float U = axis_phase((float)(u0 + k), uc, rec.ph, rec.pl, ub, ud);
         const float d = (float)(u0 + k) - pu;
         for (int v = wave * 2 + half; v < nv; v += 2 * kWaves) {

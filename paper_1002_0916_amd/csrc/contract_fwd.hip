@@ -342,14 +342,15 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
     }
   }
 
-  // An infinite or NaN amplitude has no scale: such a call takes the sum term
-  // by term, cos(X + Y) A, so that its infinities and NaNs are the direct sum's.
+  // An infinite amplitude has no scale: such a call takes the sum term by term,
+  // cos(X + Y) A, so that its infinities and NaNs are the direct sum's.  A NaN makes
+  // every pixel NaN and needs no sum.
   if (MODE == kHalfF16x3 && !finite_bits(m)) {
     for (int e = grp * kWave + lane; e < MI * 32 * NJ * 32; e += KS * kWave) {
       const int row = y0 + e / (NJ * 32), col = x0 + e % (NJ * 32);
       if (row >= ny || col >= nx) continue;
-      float v = 0.0f;
-      for (int64_t q = first / 4; q < min(first + per_slice, npad) / 4; ++q) {
+      float v = nan_bits(m) ? __builtin_nanf("") : 0.0f;
+      for (int64_t q = first / 4; !nan_bits(m) && q < min(first + per_slice, npad) / 4; ++q) {
         const float4 Y = static_cast<const float4*>(o.yq)[q * o.rows_y + row];
         const float4 X = XTAB ? static_cast<const float4*>(o.xq)[q * o.cols_x + col]
                               : quad_phases(o.rec, q, (float)col);
@@ -554,6 +555,7 @@ __global__ __launch_bounds__(512) void contract_fwd_direct_kernel(
   const int sum_at = (threadIdx.x >> 6) * 2;  // their registers: sum_at and sum_at + 1
 
   float* recs = reinterpret_cast<float*>(lds);
+  if (nan_bits(m)) direct[0] = direct[1] = __builtin_nanf("");
   for (int base = 0; base < n; base += kDirectPoints) {
     if (base > 0) {
       r = point_record(x, y, z, a, base + threadIdx.x, n, pitch, wavelength);
@@ -572,7 +574,7 @@ __global__ __launch_bounds__(512) void contract_fwd_direct_kernel(
     __syncthreads();
     const int here = min(kDirectPoints, n - base);
     if (MODE == kHalfF16x3 && !finite_bits(m)) {
-      for (int j = 0; j < here; ++j) {
+      for (int j = 0; j < here && !nan_bits(m); ++j) {
         const float* q = recs + j;
         const float X = axis_phase(col, q[5 * kDirectPoints], q[0], q[kDirectPoints],
                                    q[6 * kDirectPoints], q[7 * kDirectPoints]);
