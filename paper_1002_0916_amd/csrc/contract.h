@@ -129,15 +129,17 @@ __device__ __forceinline__ Frag make_frag(const float (&v)[8]) {
   return f;
 }
 
-// The power of two that an operand with the largest magnitude m (float bits of
-// a finite m) is multiplied by, and its inverse.  frexp's exponent e (m < 2^e)
+// The power of two that an operand with the largest magnitude m (its float bits; 1
+// where m is 0 or not finite) is multiplied by, and its inverse.  frexp's exponent e (m < 2^e)
 // is clamped so that both stay normal floats.  The largest value is then below 2^TOP.
 template <int MODE, int TOP = MODE == kHalfF16x3 ? 15 : 0>
 __device__ __forceinline__ void operand_scale(unsigned max_bits, float& mul, float& undo) {
   int e = 0;
   const float m = __uint_as_float(max_bits);
-  if (m > 0.0f) (void)frexpf(m, &e);
-  e -= TOP;
+  if (m > 0.0f && m < __builtin_inff()) {
+    (void)frexpf(m, &e);
+    e -= TOP;
+  }
   e = max(-126, min(126, e));
   undo = ldexpf(1.0f, e);
   mul = ldexpf(1.0f, -e);

@@ -102,7 +102,7 @@ __device__ __forceinline__ void adj_part(const AdjArgs& p, int pb, int plane, ui
     m = group_max<kAdjCThreads>(m, red);
   }
   float mul = 1.0f, undo = 1.0f;
-  if (MODE != kF32) operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
+  if (MODE != kF32) operand_scale<MODE>(m, mul, undo);
 
   double d0 = 0.0, d1 = 0.0, d2 = 0.0;  // {Sc, Sx or Sy, Sr} of the blocks so far
 
@@ -447,7 +447,7 @@ __device__ __forceinline__ void direct_part(const AdjArgs& p, int pb, int plane,
       }
       __syncthreads();  // the last tile's readers of red are done
       m = group_max<kDirectThreads>(m, red);
-      operand_scale<MODE>(finite_bits(m) ? m : 0u, mul, undo);
+      operand_scale<MODE>(m, mul, undo);
     }
     // An infinite G has no scale: such a tile is summed term by term.  (A NaN makes
     // every sum NaN.)

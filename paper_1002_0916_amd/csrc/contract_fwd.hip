@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kWave* WM* KS, 2) void contract_fwd_kernel(
 
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
-// Largest |A| (0 unless finite) of each of kWave parts of the points.
+// Largest |A|, as float bits, of each of kWave parts of the points.
 __global__ __launch_bounds__(256) void contract_amax_kernel(const float* __restrict__ a, int64_t n,
                                                             unsigned* __restrict__ amax) {
   __shared__ unsigned red[4];
@@ -461,7 +461,6 @@ __global__ __launch_bounds__(256) void contract_fwd_tables_kernel(
       }
       if (threadIdx.x < n - 4 * n4) m = max(m, __float_as_uint(fabsf(a[4 * n4 + threadIdx.x])));
       m = group_max<256>(m, red);
-      m = finite_bits(m) ? m : 0u;
       if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < kWave) amax[threadIdx.x] = m;
     } else {
       m = group_max<kWave>(amax[lane], red);
@@ -546,7 +545,7 @@ __global__ __launch_bounds__(512) void contract_fwd_direct_kernel(
     for (int j = kDirectPoints + threadIdx.x; j < n; j += kDirectPoints)
       m = max(m, __float_as_uint(fabsf(a[j])));
     m = group_max<512>(m, red);
-    operand_scale<MODE>(MODE == kHalfF16x3 || finite_bits(m) ? m : 0u, mul, undo);
+    operand_scale<MODE>(m, mul, undo);
   }
   floatx16 acc;
 #pragma unroll

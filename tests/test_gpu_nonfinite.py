@@ -46,6 +46,33 @@ def test_adjoint_infinite_gradient_in_separable_form(variant, shape, where):
     assert np.array_equal(ga[clear], want[clear].astype(np.float32), equal_nan=True)
 
 
+# One launch from the points, tables with max |A| found by each workgroup (up to 8192
+# points) and by a launch of its own, and sums in the order of the points.
+@pytest.mark.parametrize("variant", SEPARABLE)
+@pytest.mark.parametrize("shape", [(150, 110, 40), (400, 330, 5000), (400, 330, 9000),
+                                   (70, 50, 9000)])
+def test_forward_infinite_amplitude_in_separable_form(variant, shape):
+    """A (cY cX - sY sX) with an infinite A: the first product's infinity or, where
+    both products have one sign, NaN."""
+    nx, ny, n = shape
+    dev = device()
+    say("infinite A", shape, variant)
+    c = W.random_cloud(1703, n, nx, ny, zlo=0.3, zhi=1.0, alo=0.5, ahi=1.0)
+    x, y, z, a = to_dev(c, dev)
+    a[n - 2] = float("inf")
+    I = B.forward(x, y, z, a, nx, ny, variant=variant).cpu().numpy()
+    cs = {}
+    for axis, v, size in (("x", c.x, nx), ("y", c.y, ny)):
+        rho = (W.PITCH ** 2 / (2 * W.WAVELENGTH * float(c.z[n - 2]))
+               * (np.arange(size) - float(v[n - 2])) ** 2)
+        cs[axis] = np.cos(2 * np.pi * rho), np.sin(2 * np.pi * rho)
+    cc, ss = (np.outer(cs["y"][k], cs["x"][k]) for k in (0, 1))
+    clear = np.outer(np.min(np.abs(cs["y"]), axis=0) > 1e-2, np.min(np.abs(cs["x"]), axis=0) > 1e-2)
+    want = np.where(cc * ss > 0, np.nan, np.where(cc > 0, np.inf, -np.inf)).astype(np.float32)
+    assert clear.sum() > nx * ny // 4
+    assert np.array_equal(I[clear], want[clear], equal_nan=True)
+
+
 def best_ms(f):
     f()
     times = []
