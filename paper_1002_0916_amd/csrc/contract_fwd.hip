@@ -745,6 +745,9 @@ int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_sli
       const bool few = n * q.groups < min_parts && n < max_slices && n < units;
       if (want > 1 && !few && (units < 8 * want || tiles * want > most) && best_time > 0.0f) break;
       if (few) continue;
+      // (HIP takes 2^32 - 1 threads a launch; the first shape's stay below on any
+      // hologram that fits the memory)
+      if (k > 0 && tiles * n * q.groups * kWave > 0xffffffffll) break;
       const int64_t rounds = (tiles * n + 255) / 256;
       const float per_k = mode == kHalfF16x3 ? (rounds == 1 ? q.split_one : q.split)
                           : mode == kF32     ? (rounds == 1 ? q.f32_one : q.f32)
