@@ -95,6 +95,10 @@ PEAK_MFMA_F32 = 157.3e12
 PEAK_MFMA_F16 = 2.5e15
 MFMA_FLOPS = {"compensated": (12, 24, PEAK_MFMA_F16), "separable": (4, 8, PEAK_MFMA_F32), "separable_f16x3": (12, 24, PEAK_MFMA_F16),
               "separable_f16": (4, 8, PEAK_MFMA_F16), "separable_bf16": (4, 8, PEAK_MFMA_F16)}
+# What the sums' products are formed of (phases and sums are FP32 in every variant).
+_HI_LO = "cosines, sines, amplitudes and G as fp16 hi + lo pairs (three products), FP32 sums"
+OPERANDS = {"compensated": _HI_LO, "separable_f16x3": _HI_LO, "separable_f16": "fp16, FP32 sums",
+            "separable_bf16": "bf16, FP32 sums"}
 ALL_VARIANTS = ("compensated", "plain", "recurrence", "separable", "separable_f16x3",
                 "separable_f16", "separable_bf16")
 
@@ -150,6 +154,9 @@ def parse():
     ap.add_argument("--copy-bytes", type=int, default=0,
                     help="instead of the benchmark, run 5 plain device-to-device copies of this "
                          "many bytes (a known-traffic reference for hardware byte counters)")
+    ap.add_argument("--direct-forms", action="store_true",
+                    help="instead of the benchmark, run the compensated direct kernels 5 times at "
+                         "sizes that take them (for hardware counters)")
     ap.add_argument("--library-gemm", action="store_true",
                     help="instead of the benchmark, time the platform's GEMM (torch.matmul: "
                          "hipBLASLt / rocBLAS) at the separable variants' contraction shapes of "
@@ -171,6 +178,36 @@ def copy_reference(nbytes):
         dst.copy_(src)
     torch.cuda.synchronize()
     print(json.dumps({"copy_bytes": nbytes, "copies": 5}), flush=True)
+
+
+# Sizes that the compensated variant's direct kernels take (many points on few pixels;
+# few rows), since the headline step launches neither: (nx, ny, n).
+DIRECT_FORWARD, DIRECT_ADJOINT = (365, 339, 10048), (1920, 16, 1024)
+
+
+def direct_forms():
+    import numpy as np
+    import torch
+
+    from paper_1002_0916_amd import binding as B
+    from paper_1002_0916_amd import workloads as W
+
+    dev = torch.device("cuda:0")
+
+    def inputs(nx, ny, n):
+        c = W.random_cloud(31, n, nx, ny, zlo=0.5, zhi=1.0, alo=0.5, ahi=1.0)
+        g = np.random.default_rng(32).standard_normal((ny, nx)).astype(np.float32)
+        return [torch.from_numpy(v).to(dev) for v in c.astuple()], torch.from_numpy(g).to(dev)
+
+    for _ in range(5):
+        nx, ny, n = DIRECT_FORWARD
+        p, t = inputs(nx, ny, n)
+        B.forward_residual(*p, t, nx, ny, variant="compensated")
+        nx, ny, n = DIRECT_ADJOINT
+        p, g = inputs(nx, ny, n)
+        B.backward(*p, g, nx, ny, variant="compensated")
+    torch.cuda.synchronize()
+    print(json.dumps({"direct_forms": [DIRECT_FORWARD, DIRECT_ADJOINT]}), flush=True)
 
 
 def measured_traffic(kernel, path=None, key="traffic_bytes"):
@@ -255,9 +292,11 @@ def timed_steps(step, steps, torch):
 
 # The contractions of the headline workload (1920x1024, N = 1024: 2N = 2048
 # table columns) as library products, (name, M, N, K) of C[M][N] = sum_k A(m, k)
-# B(n, k), and the names of the tiled kernels that they were compared with when
-# the separable variants were products of operand tables (fp16 hi/lo as one plain
-# fp16 GEMM of three times the depth: [Ah Ah Al] . [Bh Bl Bh]).
+# B(n, k) (fp16 hi/lo as one plain fp16 GEMM of three times the depth: [Ah Ah Al] .
+# [Bh Bl Bh]), and the kernels they are compared with: the contraction kernels, of
+# which the adjoint's does both of its products in one launch (compared with the sum
+# of the two), or, in the trace of a build that had them, the tiled products of
+# operand tables.
 SEP_GEMMS = (("forward I = Y X^T", 1024, 1920, 2048, 0),
              ("adjoint U, K = rows", 2048, 1920, 1024, 1),
              ("adjoint P, K = columns", 2048, 1024, 1920, 2))
@@ -310,6 +349,9 @@ def main():
         return
     if args.copy_bytes > 0:
         copy_reference(args.copy_bytes)
+        return
+    if args.direct_forms:
+        direct_forms()
         return
     if args.library_gemm:
         library_gemm()
@@ -460,6 +502,7 @@ def main():
             "step": "forward + (I - T) + adjoint (dL/dx, dL/dy, dL/dz, dL/dA); I and I - T "
                     "from one cgh_forward_residual call",
             "variant": args.variant,
+            "operands": OPERANDS.get(args.variant, "FP32"),
             "nx": nx, "ny": ny, "n_points": n,
         },
         "roofline": {
@@ -956,7 +999,7 @@ def summarize_stats(root):
              "I - T) and contract_adj_kernel<format, tables> with their tables kernels (format "
              "2 = fp16 hi/lo: compensated and separable_f16x3, 0 = fp16, 1 = bf16, 3 = FP32: "
              "separable), fwd_plain_kernel<R, S> / adj_partial_kernel<0> (plain), "
-             "fwd_rec_kernel<K, R> / adj_partial_kernel<2> (recurrence).", "", "Durations in microseconds.", "",
+             "fwd_rec_kernel<K, R, P> / adj_partial_kernel<2> (recurrence).", "", "Durations in microseconds.", "",
              "| kernel | calls | avg us | min us | max us | share |", "|---|---|---|---|---|---|"]
     for r in sorted(rows, key=lambda r: -float(r["Percentage"])):
         lines.append("| %s | %s | %.1f | %.1f | %.1f | %.1f%% |" % (
@@ -986,7 +1029,7 @@ def summarize_stats(root):
                  ("adj_partial_kernel<1>", "compensated", "adj"),
                  ("fwd_plain_kernel<4, 4>", "plain", "fwd"),
                  ("adj_partial_kernel<0>", "plain", "adj"),
-                 ("fwd_rec_kernel<8, 4>", "recurrence", "fwd"),
+                 ("fwd_rec_kernel<8, 4, 8>", "recurrence", "fwd"),
                  ("adj_partial_kernel<2>", "recurrence", "adj"),
                  ("contract_adj_kernel<3, true>", "separable", "adj"),
                  ("contract_adj_kernel<0, true>", "separable_f16", "adj"),
@@ -1017,24 +1060,27 @@ def summarize_stats(root):
 
 # Kernels whose traffic is recorded, with the sources their code comes from
 # (bench.py reports a kernel's traffic only while these hash the same) and
-# the algorithmic bytes of one launch at the headline workload.
+# the algorithmic bytes of one launch at the headline workload, or at the size of
+# --direct-forms for the kernels of DIRECT_KERNELS.
+DIRECT_KERNELS = {"fwd_comp_residual_kernel": "%dx%d, N = %d" % DIRECT_FORWARD,
+                  "adj_partial_kernel<1>": "%dx%d, N = %d" % DIRECT_ADJOINT}
 TRAFFIC_KERNELS = {
     "adj_partial_kernel<1>": (["adjoint.hip", "phase.h", "records.h", "cgh_internal.h"],
-                              "G 7.86 MB + row table 8.39 MB + column table 7.86 MB + "
-                              "inputs 0.02 MB + run partials 9.44 MB (576 runs: three rounds "
-                              "of 3 waves per SIMD over 16 point groups) = 33.6 MB"),
+                              "G 0.12 MB + row table 0.13 MB + column table 7.86 MB + "
+                              "inputs 0.02 MB + run partials 1.97 MB (120 runs of 8 "
+                              "strip-rows over 16 point groups) = 10.1 MB"),
     "adj_partial_kernel<0>": (["adjoint.hip", "phase.h", "records.h", "cgh_internal.h"],
                               "G 7.86 MB + inputs 0.02 MB + run partials 12.58 MB (768 runs: "
                               "4 waves per SIMD)"),
     "adj_partial_kernel<2>": (["adjoint.hip", "phase.h", "records.h", "cgh_internal.h"],
                               "G 7.86 MB + inputs 0.02 MB + run partials 9.44 MB (576 runs)"),
     "fwd_comp_residual_kernel": (["forward.hip", "phase.h", "cgh_internal.h"],
-                                 "row table 4.19 MB + column table 7.86 MB + amplitudes + "
-                                 "hologram 7.86 MB + target 7.86 MB + residual 7.86 MB = 35.6 MB"),
+                                 "row table 14.2 MB + column table 15.4 MB + amplitudes + "
+                                 "hologram, target and residual 1.5 MB = 31.1 MB"),
     "fwd_plain_kernel<4, 4>": (["plain.hip", "phase.h", "cgh_internal.h"],
                                "inputs 0.02 MB + hologram 7.86 MB + target 7.86 MB + residual "
                                "7.86 MB"),
-    "fwd_rec_kernel<8, 4>": (["recurrence.hip", "phase.h", "cgh_internal.h"],
+    "fwd_rec_kernel<8, 4, 8>": (["recurrence.hip", "phase.h", "cgh_internal.h"],
                              "inputs 0.02 MB + hologram 7.86 MB + target 7.86 MB + residual "
                              "7.86 MB"),
     "prep_kernel": (["prep.hip", "phase.h", "records.h", "cgh_internal.h"],
@@ -1047,7 +1093,7 @@ TRAFFIC_KERNELS = {
         "inputs 0.02 MB + phase tables 4.2 + 7.9 MB = 12.1 MB"),
     "contract_adj_kernel<2, true>": (
         ["contract_adj.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
-        "phase tables 4.2 + 7.9 MB + G 7.86 MB + partial planes = 20 MB"),
+        "phase tables 4.2 + 7.9 MB + G 7.86 MB + 62 partial planes 1.0 MB = 21 MB"),
     "contract_adj_tables_kernel<2>": (
         ["contract_adj.hip", "contract.h", "phase.h", "records.h", "cgh_internal.h"],
         "inputs 0.02 MB + G 7.86 MB + phase tables 4.2 + 7.9 MB = 20 MB"),
@@ -1087,6 +1133,15 @@ def summarize_traffic(root):
     copy_f = cf["__amd_rocclr_copyBuffer"]["FETCH_SIZE"]
     copy_w = cw["__amd_rocclr_copyBuffer"]["WRITE_SIZE"]
     ff, wf = copy_f * 1024 / copy_bytes, copy_w * 1024 / copy_bytes
+
+    def add_direct(means, name):
+        """The direct kernels' counters, from the runs of --direct-forms."""
+        if os.path.isdir(os.path.join(root, name)):
+            d = _counter_means(_csv_files(os.path.join(root, name), "*counter_collection.csv"))
+            means.update({k: d[k] for k in DIRECT_KERNELS if k in d})
+
+    add_direct(fe, "direct_fetch")
+    add_direct(wr, "direct_write")
     # Read requests by size (optional pass): FETCH_SIZE's gfx950 formula counts
     # a 128-byte request as 64 bytes, so the copy-derived factor is right only
     # for kernels whose reads come in 128-byte requests.
@@ -1095,6 +1150,7 @@ def summarize_traffic(root):
         rq = _counter_means(_csv_files(os.path.join(root, "rdreq"), "*counter_collection.csv"))
         cq = _counter_means(_csv_files(os.path.join(root, "copy_rdreq"),
                                        "*counter_collection.csv"))
+        add_direct(rq, "direct_rdreq")
 
     def sized(c):
         return (32 * c["TCC_EA0_RDREQ_32B_sum"] + 64 * c["TCC_EA0_RDREQ_64B_sum"]
@@ -1111,6 +1167,8 @@ def summarize_traffic(root):
                       "fetch_bytes": f_raw * 1024 / ff, "write_bytes": w_raw * 1024 / wf,
                       "traffic_bytes": f_raw * 1024 / ff + w_raw * 1024 / wf,
                       "source_sha256_16": _sources_hash(sources), "sources": sources}
+        if k in DIRECT_KERNELS:
+            kernels[k]["workload"] = DIRECT_KERNELS[k]
         if k in rq:
             c = rq[k]
             kernels[k].update({
@@ -1119,15 +1177,6 @@ def summarize_traffic(root):
                                   "128B": c["TCC_EA0_RDREQ_128B_sum"]},
                 "read_bytes_sized": sized(c),
                 "traffic_bytes_sized": sized(c) + w_raw * 1024 / wf})
-    # Kernels that this step no longer launches keep the record they have while
-    # their sources are the same.
-    path = os.path.join(PROFILES, "traffic_paper_1920x1024_n1024.json")
-    if os.path.exists(path):
-        with open(path) as f:
-            for k, v in json.load(f)["kernels"].items():
-                if (k in TRAFFIC_KERNELS and k not in kernels
-                        and _sources_hash(v["sources"]) == v["source_sha256_16"]):
-                    kernels[k] = v
     rec = {"workload": "1920x1024 hologram, N=1024 points (bench.py step)",
            "copy_reference_bytes": copy_bytes, "fetch_factor": ff, "write_factor": wf,
            "copy_read_bytes_sized": copy_sized, "kernels": kernels}
@@ -1136,13 +1185,16 @@ def summarize_traffic(root):
     runs = [("fetch", "FETCH_SIZE", "bench.py --steps 3 --warmup 1 --no-cpu-baseline"),
             ("write", "WRITE_SIZE", "bench.py --steps 3 --warmup 1 --no-cpu-baseline"),
             ("copy_fetch", "FETCH_SIZE", "bench.py --copy-bytes %d" % copy_bytes),
-            ("copy_write", "WRITE_SIZE", "bench.py --copy-bytes %d" % copy_bytes)]
+            ("copy_write", "WRITE_SIZE", "bench.py --copy-bytes %d" % copy_bytes),
+            ("direct_fetch", "FETCH_SIZE", "bench.py --direct-forms"),
+            ("direct_write", "WRITE_SIZE", "bench.py --direct-forms")]
     lines = ["# HBM traffic per launch: bench.py step at 1920x1024, N=1024", "",
              "Commands (from the repository root on an MI355X machine, one counter per run), then "
              "`python bench.py --summarize traffic <out>`:", "", "```", _ROCPROF.rstrip(" &")]
     if rq:
         runs += [("rdreq", RDREQ_COUNTERS, "bench.py --steps 3 --warmup 1 --no-cpu-baseline"),
-                 ("copy_rdreq", RDREQ_COUNTERS, "bench.py --copy-bytes %d" % copy_bytes)]
+                 ("copy_rdreq", RDREQ_COUNTERS, "bench.py --copy-bytes %d" % copy_bytes),
+                 ("direct_rdreq", RDREQ_COUNTERS, "bench.py --direct-forms")]
     for d, counter, cmd in runs:
         lines.append("timeout -s KILL 150 rocprofv3 --kernel-trace --pmc %s -f csv -d <out>/%s "
                      "-o %s -- python3 %s" % (counter, d, d, cmd))
@@ -1154,8 +1206,9 @@ def summarize_traffic(root):
               "Counter values are averages over the kernel's dispatches in the run (every "
               "variant of the step).  `traffic_paper_1920x1024_n1024.json` holds the same "
               "figures with a hash of each kernel's sources; bench.py reports the traffic of "
-              "the roofline kernel only while that hash matches.  A kernel that this step no longer "
-              "launches keeps the record of an earlier run.", "",
+              "the roofline kernel only while that hash matches.  This step does not launch the "
+              "compensated direct kernels: theirs are of other sizes, "
+              + ", ".join("`%s` of %s" % kv for kv in DIRECT_KERNELS.items()) + ".", "",
               "| kernel | FETCH_SIZE KiB (raw) | WRITE_SIZE KiB (raw) | fetch | write | total | "
               "algorithmic bytes |", "|---|---|---|---|---|---|---|"]
     for k, v in kernels.items():
@@ -1188,16 +1241,20 @@ def summarize_traffic(root):
 RDREQ_COUNTERS = ("TCC_EA0_RDREQ_32B_sum TCC_EA0_RDREQ_64B_sum TCC_EA0_RDREQ_128B_sum "
                   "TCC_EA0_RDREQ_sum")
 
-# Algorithmic bytes of one launch of the compensated kernels at 3840x2160,
-# N = 16384 (npad 16384): tables of FP32 per (row or column, point).
+# Algorithmic bytes of one launch of the compensated variant's kernels at 3840x2160,
+# N = 16384: phase tables of 4 bytes per (row or column, point).
 FIT4K_ALGORITHMIC = {
-    "fwd_comp_kernel": (2160 * 16384 * 4 + 3840 * 16384 * 4 + 2160 * 3840 * 4,
-                        "row table 141.6 MB + column table 251.7 MB + hologram 33.2 MB"),
-    "adj_partial_kernel<1>": (2160 * 3840 * 4 + 2160 * 16384 * 8 + 3840 * 16384 * 4
-                              + 36 * 16384 * 16,
-                              "G 33.2 MB + row table 283.1 MB + column table 251.7 MB + "
-                              "run partials 9.4 MB (36 runs: three rounds of 3 waves per SIMD "
-                              "over 256 point groups)"),
+    "contract_fwd_kernel<2, 2, 4, 2, 2, true, false>": (
+        2160 * 16384 * 4 + 3840 * 16384 * 4 + 2160 * 3840 * 4,
+        "phase tables 141.6 + 251.7 MB + hologram 33.2 MB"),
+    "contract_fwd_tables_kernel<2>": (2160 * 16384 * 4 + 3840 * 16384 * 4,
+                                      "phase tables 141.6 + 251.7 MB"),
+    "contract_adj_kernel<2, true>": (
+        2160 * 3840 * 4 + 2160 * 16384 * 4 + 3840 * 16384 * 4 + 47 * 16384 * 16,
+        "G 33.2 MB + phase tables 141.6 + 251.7 MB + 47 partial planes 12.3 MB"),
+    "contract_adj_tables_kernel<2>": (
+        2160 * 3840 * 4 + 2160 * 16384 * 4 + 3840 * 16384 * 4,
+        "G 33.2 MB + phase tables 141.6 + 251.7 MB"),
 }
 
 
@@ -1247,7 +1304,7 @@ COUNTER_KERNELS = {
     "compensated": {"fwd_comp_residual_kernel": "fwd_compensated",
                     "adj_partial_kernel<1>": "adj_compensated"},
     "plain": {"fwd_plain_kernel<4, 4>": "fwd_plain", "adj_partial_kernel<0>": "adj_plain"},
-    "recurrence": {"fwd_rec_kernel<8, 4>": "fwd_recurrence",
+    "recurrence": {"fwd_rec_kernel<8, 4, 8>": "fwd_recurrence",
                    "adj_partial_kernel<2>": "adj_recurrence"},
 }
 
@@ -1476,11 +1533,12 @@ def summarize_library(root):
     import csv
 
     lib = _json_lines(root, "library_gemm")[-1]
-    ours = {}
+    ours, calls = {}, {}
     for f in _csv_files(os.path.join(root, "stats"), "*kernel_stats.csv"):
         with open(f) as fh:
             for r in csv.DictReader(fh):
                 ours[_kernel_short(r["Name"])] = float(r["AverageNs"]) / 1e3
+                calls[_kernel_short(r["Name"])] = int(r["Calls"])
     lines = ["# The separable GEMMs against the platform's GEMM library, 1920x1024, N = 1024",
              "", "Commands (from the repository root on an MI355X machine): the kernel-stats run "
              "of the default benchmark (`profiles/bench_paper_1920x1024_n1024_kernel_stats.md`) "
@@ -1490,28 +1548,45 @@ def summarize_library(root):
              "`torch.matmul` (torch %s: hipBLASLt / rocBLAS), timed by events over 50 launches "
              "(launch gaps included, so its figures are upper bounds on its kernel time), on "
              "plain operands of the same shape: its output is in the operand type and has no "
-             "epilogue, while this library's kernels write FP32 and the adjoint ones fold "
-             "their output per point in the epilogue.  fp16 hi/lo runs as one fp16 GEMM of "
-             "three times the depth.  Rates in TFLOP/s of the format's work (f16x3: three "
+             "epilogue, while this library's kernels form their operands (f16x3), write FP32 and "
+             "the residual, and the adjoint ones fold their output per point.  fp16 hi/lo runs as "
+             "one fp16 GEMM of three times the depth.  Rates in TFLOP/s of the format's work (f16x3: three "
              "products); %% of the dense peak (FP32 157.3 TFLOP/s, fp16/bf16 2.5 PFLOP/s)."
              % lib["torch"], "",
              "| contraction (M x N x K) | format | library us | library TFLOP/s | % peak | "
              "this library us | TFLOP/s | % peak | speed-up |", "|---|---|---|---|---|---|---|---|---|"]
+    mode = {"f16": 0, "bf16": 1, "f16x3": 2, "f32": 3}
+
+    def contraction(fmt, adjoint):
+        """Average us of the format's contraction kernel, the one with most calls."""
+        prefix = "contract_%s_kernel<%d," % ("adj" if adjoint else "fwd", mode[fmt])
+        found = [k for k in ours if k.startswith(prefix)]
+        return ours[max(found, key=lambda k: calls[k])] if found else None
+
+    def row(name, shape, fmt, us, flops, mine):
+        peak = 157.3e12 if fmt == "f32" else 2.5e15
+        lt = flops / (us * 1e-6)
+        text = "| %s%s | %s | %.1f | %.0f | %.1f%% |" % (name, shape, fmt, us, lt / 1e12,
+                                                        100 * lt / peak)
+        if not mine:
+            return text + " - | - | - | - |"
+        mt = flops / (mine * 1e-6)
+        return text + " %.1f | %.0f | %.1f%% | %.2fx |" % (mine, mt / 1e12, 100 * mt / peak,
+                                                         us / mine)
+
+    both = {}
     for r in lib["results"]:
-        peak = 157.3e12 if r["format"] == "f32" else 2.5e15
-        key = SEP_OURS[r["format"]] % (SEP_F32_ARGS[r["fold"]] if r["format"] == "f32"
-                                       else r["fold"])
-        mine = ours.get(key)
-        lt = r["flops"] / (r["us"] * 1e-6)
-        row = "| %s (%d x %d x %d) | %s | %.1f | %.0f | %.1f%% |" % (
-            r["gemm"], r["M"], r["N"], r["K"], r["format"], r["us"], lt / 1e12, 100 * lt / peak)
-        if mine:
-            mt = r["flops"] / (mine * 1e-6)
-            row += " %.1f | %.0f | %.1f%% | %.2fx |" % (mine, mt / 1e12, 100 * mt / peak,
-                                                      r["us"] / mine)
-        else:
-            row += " - | - | - | - |"
-        lines.append(row)
+        fmt = r["format"]
+        key = SEP_OURS[fmt] % (SEP_F32_ARGS[r["fold"]] if fmt == "f32" else r["fold"])
+        mine = ours.get(key) or (None if r["fold"] else contraction(fmt, False))
+        lines.append(row(r["gemm"], " (%d x %d x %d)" % (r["M"], r["N"], r["K"]), fmt, r["us"],
+                         r["flops"], mine))
+        if r["fold"]:
+            us, flops = both.get(fmt, (0.0, 0.0))
+            both[fmt] = us + r["us"], flops + r["flops"]
+    for fmt, (us, flops) in both.items():
+        if contraction(fmt, True):
+            lines.append(row("adjoint, both", "", fmt, us, flops, contraction(fmt, True)))
     _write_md("gemm_library_comparison_1920x1024.md", lines)
 
 

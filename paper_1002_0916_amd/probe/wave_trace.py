@@ -1,4 +1,4 @@
-"""Wave trace of the compensated adjoint kernel (a diagnostic, not part of the
+"""Wave trace of the recurrence's adjoint kernel (a diagnostic, not part of the
 library): when each wave starts and ends, on which XCD, CU and SIMD it runs,
 and at what shader clock.
 
@@ -73,15 +73,15 @@ def run(out):
         t0, k = time.perf_counter(), 0
         while k < 5 or time.perf_counter() - t0 < WARM_S:
             for _ in range(5):  # enqueued back to back, then one wait
-                B.backward(x, y, z, a, G, wl.nx, wl.ny, wl.pitch, wl.wavelength, "compensated")
+                B.backward(x, y, z, a, G, wl.nx, wl.ny, wl.pitch, wl.wavelength, "recurrence")
             torch.cuda.synchronize()
             k += 5
-        B.profile_read(B.KERNEL_ADJ_COMPENSATED)
+        B.profile_read(B.KERNEL_ADJ_RECURRENCE)
         B.profile_enable(True)
-        B.backward(x, y, z, a, G, wl.nx, wl.ny, wl.pitch, wl.wavelength, "compensated")
+        B.backward(x, y, z, a, G, wl.nx, wl.ny, wl.pitch, wl.wavelength, "recurrence")
         torch.cuda.synchronize()
         B.profile_enable(False)
-        kernel_ms = float(B.profile_read_each(B.KERNEL_ADJ_COMPENSATED)[-1])
+        kernel_ms = float(B.profile_read_each(B.KERNEL_ADJ_RECURRENCE)[-1])
         buf = np.zeros((MAX_WAVES, 4), dtype=np.uint64)
         if lib.cgh_wave_trace_read(buf.ctypes.data, buf.nbytes) != 0:
             raise SystemExit("cgh_wave_trace_read failed")
@@ -149,7 +149,7 @@ def summarize(out):
     with open(os.path.join(out, "meta.json")) as f:
         meta = json.load(f)
     lines = [
-        "# Wave trace of the compensated adjoint kernel",
+        "# Wave trace of the recurrence's adjoint kernel",
         "",
         "Commands (from the repository root; the build here, the run on an MI355X machine):",
         "",
