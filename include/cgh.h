@@ -51,7 +51,11 @@
  *                       633 nm and z_j >= 0.2 m.  The forward takes the cosine of the
  *                       two axis phases' sum by the addition theorem and sums over the
  *                       points on the fp16 matrix cores with hi + lo operands, as
- *                       CGH_SEPARABLE_F16X3 (whose error is the smaller of the two forms);
+ *                       CGH_SEPARABLE_F16X3 (whose error is the smaller of the two forms).
+ *                       The operands are then 16-bit pairs, not FP32: A_j cos and A_j sin
+ *                       keep 2^-23 of their value, the other axis' cosine and sine are
+ *                       off by up to 2^-24, and the first carry a factor 1 + 2^-24 that
+ *                       takes back the native cosine's mean error;
  *                       up to 8 points, and for many points on few pixels (24 n > nx ny),
  *                       it takes one cosine per interaction and adds the points in
  *                       order, so that the result does not depend on how a sum was
@@ -157,9 +161,8 @@ int cgh_forward(const float* x, const float* y, const float* z, const float* a, 
  * Forward with the residual of a target, for a loss L = 0.5 ||I - T||^2 whose
  * upstream gradient dL/dI = I - T feeds cgh_backward (the chain rule on
  * Eq. (1), Section 1).  Writes I exactly as cgh_forward (the same bits) and
- *   residual[h] = hologram[h] - target[h]   (one FP32 subtraction each),
- * in the compensated forward's own store pass, after the other forwards as
- * one more kernel on the same stream.
+ *   residual[h] = hologram[h] - target[h]   (one FP32 subtraction each)
+ * in the pass that stores the hologram.
  *   target       device float32[ny][nx], read only.
  *   hologram     device float32[ny][nx], overwritten with I.
  *   residual     device float32[ny][nx], overwritten with I - T.

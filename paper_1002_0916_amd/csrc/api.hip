@@ -51,7 +51,8 @@ inline int split_count(int64_t tiles, int64_t k) {
 }
 
 // Consecutive pixels per lane of the recurrence forward, K in {4, 6, 8}.  A lane
-// starts Eq. (2) anew at its first pixel, so K is part of the result.  It is that
+// starts Eq. (2) anew at its first pixel, so K is part of the result and its rule does
+// not follow the launch (fwd_rec_kernel's rows and workgroups are others).  It is that
 // of the shape of K pixels x R rows, R in {1, 2, 4}, with the least work per CU:
 // the workgroups of four waves that each of the 256 CUs runs, times K R, times the
 // slots per interaction,
@@ -224,11 +225,12 @@ Plan make_plan(int64_t n, int32_t nx, int32_t ny, int32_t variant, int32_t op,
                     ? take((size_t)p.sep_splits * nyp * nxp * sizeof(float))
                     : 0;
   // Planes of the adjoint's partial sums: with few points as many as the
-  // contraction can use to fill the chip (12 MB at most), else as many as K
-  // slices of 128-wide tiles of both axes.  In FP32, whose workgroups run longest,
-  // at least four a tile, so that slices can fill the last round (2104x1335, N =
-  // 5414: 1277 us a call with one a tile, 1122 with four; 182x382, N = 13668: 137
-  // and 110).
+  // contraction can use to fill the chip, one per 32 coordinates of each axis (half a
+  // byte a point and coordinate, where the tables take 4 to 8: 12 MB at 3840x2160, N =
+  // 4096), else as many as K slices of 128-wide tiles of both axes.  In FP32, whose
+  // workgroups run longest, at least four a tile, so that slices can fill the last
+  // round (2104x1335, N = 5414: 1277 us a call with one a tile, 1122 with four;
+  // 182x382, N = 13668: 137 and 110).
   const int64_t tiles = p.nxp / 128 + p.nyp / 128;
   p.fold_planes = (int64_t)p.sep_splits_u * (p.nxp / 128) + (int64_t)p.sep_splits_p * (p.nyp / 128);
   if (n <= 4096)
@@ -450,8 +452,7 @@ int scratch_address(void** out) {
 // caller's workspace, or the static scratch), after the argument checks.
 // timed = false skips the event timing (which creates events), for the
 // allocation-free entry point.  With target and residual it also writes
-// residual = hologram - target: fused into the compensated forward's store,
-// a separate elementwise launch after the other forwards.
+// residual = hologram - target, in the pass that stores the hologram.
 int forward_run(const Plan& p, void* workspace, const float* x, const float* y, const float* z,
                 const float* a, double pitch, double wavelength, float* hologram,
                 hipStream_t s, bool timed = true, const float* target = nullptr,

@@ -9,7 +9,9 @@
 // these formats (FP32 accumulation in all):
 //
 //   kHalfF16x3  v = hi + lo, hi = fp16(v), lo = fp16(v - hi), three products
-//               hi*hi + hi*lo + lo*hi: the two planes hold 22 to 24 bits of v
+//               hi*hi + hi*lo + lo*hi: the planes are off by 2^-23 |v| at most or,
+//               as lo's smallest step is 2^-24, by 2^-25 where that is more (|v|
+//               below 1/4: a small cosine has fewer bits of its own, 20 at 1/32),
 //               and what is dropped, lo*lo, is below 2^-22 of the product.
 //   kHalfF16, kHalfBF16   v rounded once to 16 bits, one product.
 //   kF32        v itself, on the FP32 matrix cores.
@@ -92,9 +94,12 @@ __device__ __forceinline__ uint32_t pack16(float v0, float v1) {
 // differences v - hi (exact) and another pack.  The two empty asm statements
 // keep the compiler from converting each value a second time for the
 // difference and from turning the fma into a conversion and a subtraction.
-// With RAISE the planes hold v (1 + 2^-24) instead: the native cosine and sine are
-// 3.3e-8 too small on average (measured as the scale of a hologram), so a product
-// of two is 6.6e-8 too small, which one raised operand takes back.
+// With RAISE the planes hold v (1 + 2^-24) instead, an empirical gain: the native
+// cosine and sine are 3.3e-8 too small on average (measured as the scale of a
+// hologram), so a product of two is 6.6e-8 too small, which one raised operand takes
+// back.  It is in lo, so it is exact for the scaled operand that the forward raises
+// (scale -6.6e-8 without, -0.9e-8 with); of the cosines and sines that the adjoint
+// raises, near lo's smallest step, 0.7 to 1.04 of it arrives by octave of v.
 template <bool RAISE>
 __device__ __forceinline__ void split16(float v0, float v1, uint32_t& hi, uint32_t& lo) {
   uint32_t h = pack16<kHalfF16x3>(v0, v1);

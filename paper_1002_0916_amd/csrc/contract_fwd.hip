@@ -723,7 +723,9 @@ constexpr Shape kShapes[] = {
 // The sums are cut into at least min_parts parts (slices times point groups),
 // which bounds the error of the FP32 additions: it grows as the square root of
 // a part's length (3332x341, N = 60771: 2.97e-6 of the result in 2 parts,
-// 4.3e-7 in 64).
+// 4.3e-7 in 64).  min_parts is the plan's K splits for f16x3 and FP32 and 1 for the
+// compensated variant, whose direct form is one chain of all points (1.5e-8 sqrt(N)
+// of the result, 3.7e-6 there).
 int choose_shape(int64_t npad, int32_t nx, int32_t ny, int mode, int64_t max_slices,
                  int64_t min_parts, int& slices, float& best_time) {
   int best = 0;

@@ -2,7 +2,7 @@
 // pixel x_h + n follows from two additions, Gamma_n = Gamma_{n-1} + delta_{n-1}
 // and delta_n = delta_{n-1} + Delta, from Gamma_0 = P r^2 at x_h, delta_0 = P (2
 // (x_h - x_j) + 1) and Delta = 2 P (here in revolutions, P -> Prev).  Lane l
-// covers the K consecutive pixels x0 + K l ... x0 + K l + K - 1 of kRecRows rows
+// covers the K consecutive pixels x0 + K l ... x0 + K l + K - 1 of R rows
 // (the paper's work-item covers eight consecutive pixels of one row).  delta and
 // Delta depend on the column only, so the lane's rows share them: per point the
 // lane forms dx and delta_0 once and Gamma_0 = fract(Prev r^2) (the plain phase)
